@@ -740,76 +740,159 @@ int affine_act(int dtype, void* Y, int64_t n, int c, const Epilogue& ep, hipStre
 // non-spatial functions after a convolution; the chain rule per element):
 // g = dy where the ReLU passed (y > 0; everywhere without it), dz = g * scale,
 // and per channel dscale = sum over rows of g * z, dshift = sum of g, with z
-// recovered from y as (y - shift) / scale on the rows where g counts.  Rows
-// are split into kAbChunks chunks at most; a block sums its chunk per channel
-// (lane l of a channel takes rows l, l + L, ...; the L lanes are added in
-// lane order), the chunk sums go to part, and a second kernel adds them in
-// chunk order (so the sums are deterministic).
+// recovered from y as (y - shift) / scale on the rows where g counts.  The
+// division is by one number per channel, so the sums hold g * (y - shift) and
+// their total is divided once (a channel with scale 0 and a row that counts is
+// marked by a NaN partial).  Rows are split into kAbChunks chunks at most; a
+// block sums its chunk per channel (lane l of a channel takes rows l, l + L,
+// ...; the L lanes are added in lane order), the chunk sums go to part, and a
+// second kernel adds them in a fixed order (so the sums are deterministic).
+//
+// Bound: HBM (two reads and a write of n x c).  A thread owns V adjacent
+// channels (16 bytes) of a row, kAbRows rows in flight, where rows are whole
+// 16-byte groups and all three arrays are 16-byte aligned; otherwise V = 1.
+// 480,288 x 128 bf16 (369 MB): one element per thread and a division each took
+// 252 us; 239,878 x 64 float32 (184 MB) 76 us.
 constexpr int kAbThreads = 256;
 constexpr int64_t kAbChunks = 1024;
+constexpr int kAbRows = 4;
 
 static int64_t ab_chunks(int64_t n) {
     const int64_t c = (n + 63) / 64;
     return c < 1 ? 1 : (c > kAbChunks ? kAbChunks : c);
 }
 
-template <typename T>
+// V elements of T as one load or store (16 bytes when V > 1)
+template <typename T, int V>
+struct alignas(sizeof(T) * V) AbVec {
+    T v[V];
+};
+
+template <typename T, int V>
 __global__ void __launch_bounds__(kAbThreads) k_affine_act_bwd(const T* __restrict__ y, const T* __restrict__ dy,
                                                                int64_t n, int c, Epilogue ep, T* __restrict__ dz,
                                                                float* __restrict__ part_s, float* __restrict__ part_t) {
-    __shared__ float ss[kAbThreads], st[kAbThreads];
+    typedef AbVec<T, V> Vec;
+    __shared__ float ss[V][kAbThreads], st[V][kAbThreads];
     const int64_t chunks = gridDim.x;
     const int64_t r0 = n * blockIdx.x / chunks, r1 = n * (blockIdx.x + 1) / chunks;
-    const int L = c < kAbThreads ? kAbThreads / c : 1;   // lanes per channel
+    const int cv = c / V;                                 // channel groups of a row
+    const int span = cv < kAbThreads ? cv : kAbThreads;   // groups a block takes at a time
+    const int L = kAbThreads / span;                      // lanes per group
     const int t = threadIdx.x;
-    for (int cb = 0; cb < c; cb += kAbThreads) {   // channels cb .. cb + (L > 1 ? c : 256) - 1
-        const int lane = t / (L > 1 ? c : kAbThreads);
-        const int ch = cb + t % (L > 1 ? c : kAbThreads);
-        float gs = 0.f, gt = 0.f;
-        if (lane < L && ch < c) {
-            const float sc = ep.scale ? ep.scale[ch] : 1.f;
-            const float sh = ep.shift ? ep.shift[ch] : 0.f;
-            for (int64_t r = r0 + lane; r < r1; r += L) {
-                const int64_t i = r * c + ch;
-                const float yv = to_f32(y[i]);
-                const float g = ep.relu && !(yv > 0.f) ? 0.f : to_f32(dy[i]);
-                store_out(&dz[i], g * sc);
-                if (part_s && g != 0.f) {
-                    gs += g * ((yv - sh) / sc);
-                    gt += g;
+    const int lane = t / span, gi = t % span;
+    for (int gb = 0; gb < cv; gb += span) {
+        const int grp = gb + gi;
+        float gs[V], gt[V], sc[V], sh[V];
+        bool any[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            gs[e] = gt[e] = 0.f;
+            any[e] = false;
+        }
+        if (lane < L && grp < cv) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                sc[e] = ep.scale ? ep.scale[grp * V + e] : 1.f;
+                sh[e] = ep.shift ? ep.shift[grp * V + e] : 0.f;
+            }
+            for (int64_t rb = r0 + lane; rb < r1; rb += kAbRows * L) {
+                Vec yv[kAbRows], gv[kAbRows];
+#pragma unroll
+                for (int i = 0; i < kAbRows; ++i) {   // rows past the chunk re-read its last one of this lane
+                    const int64_t r = rb + i * L < r1 ? rb + i * L : rb;
+                    yv[i] = reinterpret_cast<const Vec*>(y)[r * cv + grp];
+                    gv[i] = reinterpret_cast<const Vec*>(dy)[r * cv + grp];
+                }
+#pragma unroll
+                for (int i = 0; i < kAbRows; ++i) {
+                    if (rb + i * L >= r1) break;
+                    Vec o;
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        const float yf = to_f32(yv[i].v[e]);
+                        const float g = ep.relu && !(yf > 0.f) ? 0.f : to_f32(gv[i].v[e]);
+                        store_out(&o.v[e], g * sc[e]);
+                        const bool counts = g != 0.f;
+                        gs[e] += counts ? g * (yf - sh[e]) : 0.f;
+                        gt[e] += g;
+                        any[e] = any[e] || counts;
+                    }
+                    reinterpret_cast<Vec*>(dz)[(rb + i * L) * cv + grp] = o;
                 }
             }
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (sc[e] == 0.f && any[e]) gs[e] = __builtin_nanf("");
         }
         if (part_s) {
-            __syncthreads();   // the previous channel group's sums are read
-            ss[t] = gs;
-            st[t] = gt;
+            __syncthreads();   // the previous channel groups' sums are read
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                ss[e][t] = gs[e];
+                st[e][t] = gt[e];
+            }
             __syncthreads();
-            const int span = L > 1 ? c : kAbThreads;
-            if (t < span && cb + t < c) {
+            for (int i = t; i < span * V; i += kAbThreads) {
+                const int e = i % V, g2 = i / V;
+                if (gb + g2 >= cv) continue;
                 float a = 0.f, b = 0.f;
                 for (int l = 0; l < L; ++l) {
-                    a += ss[l * span + t];
-                    b += st[l * span + t];
+                    a += ss[e][l * span + g2];
+                    b += st[e][l * span + g2];
                 }
-                part_s[(int64_t)blockIdx.x * c + cb + t] = a;
-                part_t[(int64_t)blockIdx.x * c + cb + t] = b;
+                part_s[(int64_t)blockIdx.x * c + (gb + g2) * V + e] = a;
+                part_t[(int64_t)blockIdx.x * c + (gb + g2) * V + e] = b;
             }
         }
     }
 }
 
-__global__ void k_affine_act_bwd_sum(const float* __restrict__ part_s, const float* __restrict__ part_t,
-                                     int64_t chunks, int c, float* __restrict__ dscale, float* __restrict__ dshift) {
-    const int ch = blockIdx.x * blockDim.x + threadIdx.x;
-    if (ch >= c) return;
+// The channel sums from the chunk sums: a block takes kAbSumCh channels, lane
+// l of a channel adds chunks l, l + kAbSumLanes, ... in double, and the lanes'
+// sums are added pairwise.  Bound: latency (1 MB of partials); a thread per
+// channel adding its 1,024 chunks one after another took 260 us.
+constexpr int kAbSumCh = 16, kAbSumLanes = 64;
+
+__global__ void __launch_bounds__(kAbSumCh * kAbSumLanes)
+k_affine_act_bwd_sum(const float* __restrict__ part_s, const float* __restrict__ part_t, int64_t chunks, int c,
+                     const float* __restrict__ scale, float* __restrict__ dscale, float* __restrict__ dshift) {
+    __shared__ double sa[kAbSumLanes][kAbSumCh], sb[kAbSumLanes][kAbSumCh];
+    const int ci = threadIdx.x % kAbSumCh, l = threadIdx.x / kAbSumCh;
+    const int ch = blockIdx.x * kAbSumCh + ci;
     double a = 0.0, b = 0.0;
-    for (int64_t k = 0; k < chunks; ++k) {
-        a += part_s[k * c + ch];
-        b += part_t[k * c + ch];
+    if (ch < c) {
+#pragma unroll 4
+        for (int64_t k = l; k < chunks; k += kAbSumLanes) {
+            a += part_s[k * c + ch];
+            b += part_t[k * c + ch];
+        }
     }
-    if (dscale) dscale[ch] = (float)a;
-    if (dshift) dshift[ch] = (float)b;
+    sa[l][ci] = a;
+    sb[l][ci] = b;
+    for (int d = kAbSumLanes / 2; d > 0; d >>= 1) {
+        __syncthreads();
+        if (l < d) {
+            sa[l][ci] += sa[l + d][ci];
+            sb[l][ci] += sb[l + d][ci];
+        }
+    }
+    if (l == 0 && ch < c) {
+        const float sc = scale ? scale[ch] : 1.f;
+        // scale 0: the sum is NaN when a row counted, else 0
+        if (dscale) dscale[ch] = (float)(sc == 0.f ? sa[0][ci] : sa[0][ci] / (double)sc);
+        if (dshift) dshift[ch] = (float)sb[0][ci];
+    }
+}
+
+template <typename T>
+static void launch_affine_act_bwd(const void* Y, const void* dY, int64_t n, int c, const Epilogue& ep, void* dZ,
+                                  float* part_s, float* part_t, hipStream_t s) {
+    constexpr int V = 16 / sizeof(T);
+    const bool wide = c % V == 0 && (((uintptr_t)Y | (uintptr_t)dY | (uintptr_t)dZ) & 15) == 0;
+    auto* kern = wide ? k_affine_act_bwd<T, V> : k_affine_act_bwd<T, 1>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)ab_chunks(n)), dim3(kAbThreads), 0, s, reinterpret_cast<const T*>(Y),
+                       reinterpret_cast<const T*>(dY), n, c, ep, reinterpret_cast<T*>(dZ), part_s, part_t);
 }
 
 }  // namespace gsc
@@ -1233,17 +1316,13 @@ int gsc_affine_act_bwd(int32_t dtype, const void* Y, const void* dY, int64_t n, 
                                                     al256((size_t)chunks * c * sizeof(float)))
                          : nullptr;
     if (dtype == GSC_BF16)
-        hipLaunchKernelGGL(k_affine_act_bwd<uint16_t>, dim3((unsigned)chunks), dim3(kAbThreads), 0, s,
-                           reinterpret_cast<const uint16_t*>(Y), reinterpret_cast<const uint16_t*>(dY), n, c, ep,
-                           reinterpret_cast<uint16_t*>(dZ), part_s, part_t);
+        launch_affine_act_bwd<uint16_t>(Y, dY, n, c, ep, dZ, part_s, part_t, s);
     else
-        hipLaunchKernelGGL(k_affine_act_bwd<float>, dim3((unsigned)chunks), dim3(kAbThreads), 0, s,
-                           reinterpret_cast<const float*>(Y), reinterpret_cast<const float*>(dY), n, c, ep,
-                           reinterpret_cast<float*>(dZ), part_s, part_t);
+        launch_affine_act_bwd<float>(Y, dY, n, c, ep, dZ, part_s, part_t, s);
     GSC_LAUNCH_CHECK();
     if (sums) {
-        hipLaunchKernelGGL(k_affine_act_bwd_sum, dim3((unsigned)((c + 255) / 256)), dim3(256), 0, s, part_s, part_t,
-                           chunks, c, dscale, dshift);
+        hipLaunchKernelGGL(k_affine_act_bwd_sum, dim3((unsigned)((c + kAbSumCh - 1) / kAbSumCh)),
+                           dim3(kAbSumCh * kAbSumLanes), 0, s, part_s, part_t, chunks, c, scale, dscale, dshift);
         GSC_LAUNCH_CHECK();
     }
     return GSC_OK;
