@@ -79,9 +79,14 @@ int gsc_abi_version(void);
 /* a1. Coordinate hash table (Sec. 3; hash-table neighbour search, Sec. 2).  */
 /* ------------------------------------------------------------------------ */
 /* Bytes of a table for n coordinates: a 256-byte header (key packing,
- * bounding box, status) followed by a power-of-two number (>= 4n, >= 64) of
- * 16-byte slots {uint64 key, int32 row, int32 hi}.  Open addressing with
- * linear probing; the key is the row packed into <= 92 bits relative to the
+ * bounding box, status) followed by the memory of a power-of-two number (>=
+ * 4n, >= 64) of 16-byte slots.  The build chooses one of two forms on the
+ * device.  A bounding box of up to about 192 cells per row becomes an
+ * occupancy grid: words {uint32 bits, uint32 before} of 32 cells each (in
+ * units of the coordinates' common power-of-two step), and the row numbers of
+ * the occupied cells, a cell's at place before + the word's occupied cells
+ * below it.  A larger box is hashed: slots {uint64 key, int32 row, int32 hi},
+ * open addressing with linear probing; the key is the row packed into <= 92 bits relative to the
  * bounding box of the coordinates (batch column most significant): up to 62
  * bits in `key` alone, a wider key with its low 62 bits in `key` and the rest
  * in `hi` (an insert claims a slot by an atomic compare-and-swap on `key`
@@ -98,7 +103,7 @@ size_t gsc_table_bytes(int64_t n);
  * more than 92 key bits), EDUP (a repeated row), EFULL (no free slot: not
  * reached at the table's load factor of at most 1/4; the environment variable
  * GSC_TABLE_CAP_LIMIT, a test hook read by gsc_table_bytes and the builds,
- * caps the slot count to force it), EHIP.  n == 0 builds an empty table. */
+ * turns grids off and caps the slot count to force it), EHIP.  n == 0 builds an empty table. */
 int gsc_coords_build(const int32_t* coords, int64_t n, int32_t D,
                      void* table, size_t table_bytes, void* stream);
 

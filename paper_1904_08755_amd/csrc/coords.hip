@@ -1,11 +1,17 @@
-// Coordinate hash table (a1) and output coordinates of a strided
-// convolution (a2).
+// Coordinate table (a1) and output coordinates of a strided convolution (a2).
 //
-// The table is open addressing with linear probing over 16-byte slots in
-// HBM.  A coordinate row (b, x_1..x_D) is packed into a key relative to the
-// bounding box of the rows (computed on the device, so the build needs no
-// host round trip before the insert), batch column in the high bits, so the
-// numeric order of keys is the lexicographic order of rows.
+// A table holds the rows (b, x_1..x_D) relative to their bounding box, which
+// the device finds, so a build needs no host round trip.  It takes one of two
+// forms, decided on the device from the box:
+//   grid:  one bit per cell of the box and the row numbers of the occupied
+//          cells (GridWord), when the box has at most as many cells as the
+//          table's memory holds words for (see grid_layout);
+//   hash:  open addressing with linear probing over 16-byte slots, the row
+//          packed into a key relative to the box, batch column in the high
+//          bits: any box of up to kMaxKeyBits key bits.
+// At 300,000 rows of two rooms at 2 cm (120 cells per row) a grid takes 33 us
+// to build and a map of 27 offsets 37 us, hashed slots 41 and 90 us.
+#include <algorithm>
 #include <climits>
 
 #include <cstddef>
@@ -18,196 +24,515 @@ namespace gsc {
 constexpr int kThreads = 256;
 
 struct StrideArg {
-    int32_t s[kMaxCols];   // s[0] = 1 (batch), s[c] = stride of spatial column c
-    int32_t on;            // 0: identity transform
+    int32_t s[kMaxCols];   // s[0] = 1 (batch), s[c] = stride of spatial column c (all 1: the rows as they are)
 };
 
-__device__ __forceinline__ void load_row(const int32_t* coords, int64_t r, int ncol, const StrideArg& st,
-                                         int64_t* v) {
+static StrideArg unit_stride() {
+    StrideArg st;
+    for (int c = 0; c < kMaxCols; ++c) st.s[c] = 1;
+    return st;
+}
+
+template <int NC>
+__device__ __forceinline__ void load_row(const int32_t* __restrict__ coords, bool vec, int64_t r, int ncol,
+                                         const StrideArg& st, int32_t* v, bool* bad) {
+    int32_t raw[NC];
+    if (NC == 4 && vec) {   // uniform: rows of four columns from a 16-byte aligned array
+        const int4 q = reinterpret_cast<const int4*>(coords)[r];
+        raw[0] = q.x;
+        raw[1 % NC] = q.y;
+        raw[2 % NC] = q.z;
+        raw[3 % NC] = q.w;
+    } else {
 #pragma unroll
-    for (int c = 0; c < kMaxCols; ++c) {
-        int64_t x = c < ncol ? coords[r * ncol + c] : 0;
-        if (st.on && c > 0 && c < ncol) x = floor_mul(x, st.s[c]);
-        v[c] = x;
+        for (int c = 0; c < NC; ++c) raw[c] = c < ncol ? coords[r * ncol + c] : 0;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) v[c] = c > 0 && c < ncol ? floor_mul(raw[c], st.s[c], bad) : raw[c];
+}
+
+// The memory of a table for n rows of cap slots: the words of a grid, the box
+// kernel's per-block results, then one row number per row.
+struct GridLayout {
+    int64_t word_bytes;   // words that the build clears, and so the most a grid may use
+    size_t part;          // byte offsets from the table's start
+    size_t rowof;
+    int64_t max_cells;    // 0: hashed slots only
+};
+
+constexpr int kBoxThreads = 512;
+constexpr int kBoxBlocks = 256;                 // at most; four per lane of the wave that combines them
+constexpr int kBoxInts = 4 * kMaxCols + 1;      // lo, hi, or, and per column; out of range
+constexpr int kBoxRows = 4;                     // rows in flight per thread (half as many points)
+
+// blocks of the box kernel; their results fit the slots' memory
+static int box_blocks(int64_t n, int64_t cap) {
+    const int64_t per = kBoxThreads * 2;
+    const int64_t b = std::min((n + per - 1) / per, cap * (int64_t)sizeof(Slot) / (kBoxInts * 4));
+    return (int)std::clamp<int64_t>(b, 1, kBoxBlocks);
+}
+
+// A grid may have kGridCells cells per row (48 bytes of words each: three
+// quarters of the table's memory at its smallest), or, with few rows, as many
+// cells as kSmallRows rows where the table has room for their words.  The build
+// of more rows clears that much before it knows the box, which at 300,000 rows
+// (14 MB) costs about 3 us.  Rooms voxelised at 2 cm have 112 to
+// 120 cells per row, at 4 to 5 cm 20 to 30; boxes past the limit are hashed.
+// The environment variable GSC_TABLE_CAP_LIMIT (a test hook for the hashed
+// slots) turns grids off.
+constexpr int64_t kGridCells = 192;
+constexpr int kSmallPer = 3, kSmallThreads = 1024;               // see k_small
+constexpr int kSmallRows = kSmallThreads * kSmallPer;
+constexpr int kSmallWords = kSmallRows * (int)kGridCells / 32;
+
+static GridLayout grid_layout(int64_t n, int64_t cap) {
+    GridLayout g{};
+    const int64_t region = cap * (int64_t)sizeof(Slot);
+    const int64_t rows = (4 * n + 15) / 16 * 16, part = ((int64_t)box_blocks(n, cap) * kBoxInts * 4 + 15) / 16 * 16;
+    const int64_t want = n <= kSmallRows ? kSmallWords * (int64_t)sizeof(GridWord) : n * (kGridCells / 4);
+    const int64_t room = region - rows - part;
+    const bool on = n > 0 && room >= 16 && cap >= 4 * n && !getenv("GSC_TABLE_CAP_LIMIT");
+    g.word_bytes = on ? std::min(want, room) / 16 * 16 : 0;
+    g.max_cells = g.word_bytes / (int64_t)sizeof(GridWord) * 32;
+    // the boxes lie behind the words (without a grid anywhere: the slots are set after they have been read)
+    g.part = kHeaderBytes + (on ? (size_t)(region - rows - part) : 0);
+    g.rowof = kHeaderBytes + (on ? (size_t)(region - rows) : 0);
+    return g;
+}
+
+// Bounding box of a set of values per column.
+struct Box {
+    int32_t lo[kMaxCols], hi[kMaxCols], all_or[kMaxCols], all_and[kMaxCols];
+    int32_t bad;
+};
+
+template <int NC>
+__device__ __forceinline__ void box_wave(Box& x, int ncol) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (c >= ncol) break;   // uniform
+            x.lo[c] = min(x.lo[c], __shfl_xor(x.lo[c], d, 64));
+            x.hi[c] = max(x.hi[c], __shfl_xor(x.hi[c], d, 64));
+            x.all_or[c] |= __shfl_xor(x.all_or[c], d, 64);
+            x.all_and[c] &= __shfl_xor(x.all_and[c], d, 64);
+        }
+        x.bad |= __shfl_xor(x.bad, d, 64);
     }
 }
 
-__global__ void __launch_bounds__(kThreads) k_table_init(TableHeader* h, Slot* slots, int64_t cap, int ncol,
-                                                         int64_t n, int32_t init_val) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += stride) {
-        Slot e;
-        e.key = kEmptyKey;
-        e.val = init_val;
-        e.hi = kHiUnset;
-        slots[i] = e;
+template <int NC>
+__device__ __forceinline__ void box_empty(Box& x) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        x.lo[c] = INT_MAX;
+        x.hi[c] = INT_MIN;
+        x.all_or[c] = 0;
+        x.all_and[c] = -1;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        h->magic = kTableMagic;
-        h->ncol = ncol;
-        h->capacity = cap;
-        h->n = n;
-        h->status = 0;
-        h->total_bits = 0;
-        for (int c = 0; c < kMaxCols; ++c) {
-            h->lo[c] = INT_MAX;
-            h->hi[c] = INT_MIN;
-            h->shift[c] = 0;
-            h->bits[c] = 0;
-        }
-        h->nblk = 0;
-        for (int i = 0; i < 3; ++i) h->blk_shift[i] = 0;
-        for (int c = 0; c < kMaxCols; ++c) h->vary[c] = 0;
-    }
+    x.bad = 0;
 }
 
-// Bounding box of the (optionally strided) rows: per-thread min/max, wave
-// shuffles, then LDS across the block's waves, so the header sees one atomic
-// per column per block.
-__global__ void __launch_bounds__(kThreads) k_bbox(const int32_t* coords, int64_t n, int ncol, StrideArg st,
-                                                   TableHeader* h) {
-    __shared__ int sh_lo[kThreads / 64][kMaxCols], sh_hi[kThreads / 64][kMaxCols], sh_or[kThreads / 64][kMaxCols];
-    int64_t lo[kMaxCols], hi[kMaxCols], v0[kMaxCols];
-    int vary[kMaxCols];
-    for (int c = 0; c < kMaxCols; ++c) {
-        lo[c] = INT_MAX;
-        hi[c] = INT_MIN;
-        vary[c] = 0;
+// field f of box i of `count` boxes at p[f * count + i]
+template <int NC>
+__device__ __forceinline__ void box_store(const Box& x, int ncol, int32_t* p, int count, int i) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if (c >= ncol) break;
+        p[(4 * c) * count + i] = x.lo[c];
+        p[(4 * c + 1) * count + i] = x.hi[c];
+        p[(4 * c + 2) * count + i] = x.all_or[c];
+        p[(4 * c + 3) * count + i] = x.all_and[c];
     }
-    load_row(coords, 0, ncol, st, v0);   // n > 0 here
-    bool out_of_range = false;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    // kBboxRows rows per thread and round, all loaded before any is used
-    constexpr int kBboxRows = 4;
-    for (int64_t r0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r0 < n; r0 += kBboxRows * stride) {
-        int32_t raw[kBboxRows][kMaxCols];
+    p[(kBoxInts - 1) * count + i] = x.bad;
+}
+
+template <int NC>
+__device__ __forceinline__ void box_add(Box& x, int ncol, const int32_t* p, int count, int i) {
 #pragma unroll
-        for (int i = 0; i < kBboxRows; ++i) {
-            const int64_t r = r0 + i * stride;
-            const int64_t rr = r < n ? r : r0;   // a row past the end repeats the first one
+    for (int c = 0; c < NC; ++c) {
+        if (c >= ncol) break;
+        x.lo[c] = min(x.lo[c], p[(4 * c) * count + i]);
+        x.hi[c] = max(x.hi[c], p[(4 * c + 1) * count + i]);
+        x.all_or[c] |= p[(4 * c + 2) * count + i];
+        x.all_and[c] &= p[(4 * c + 3) * count + i];
+    }
+    x.bad |= p[(kBoxInts - 1) * count + i];
+}
+
+// Sparse tensor quantization (Sec. 4.1, Alg. 1): the rows are (b, floor(p/v))
+// of points, which the box kernel works out and stores (qc) as it reads them.
+struct VoxelArg {
+    float v[kMaxCols - 1];   // voxel size per spatial axis
+};
+struct PointsArg {
+    const float* points;     // null: no points, the rows are coords
+    const int32_t* batch;
+    int32_t* qc;
+    VoxelArg voxel;
+};
+
+// (batch[r] or 0, floor(p_d / v_d)), the floor of the exact quotient of the
+// stored float32 values; *bad: a coordinate outside +-2^30.
+template <int NC>
+__device__ __forceinline__ void quantize_row(const PointsArg& pa, int64_t r, int ncol, int32_t* v, bool* bad_out) {
+    const int D = ncol - 1;
+    bool bad = false;
+    v[0] = pa.batch ? pa.batch[r] : 0;
 #pragma unroll
-            for (int c = 0; c < kMaxCols; ++c) raw[i][c] = c < ncol ? coords[rr * ncol + c] : 0;
+    for (int c = 1; c < NC; ++c) {
+        v[c] = 0;
+        if (c >= ncol) continue;
+        // The quotient rounded to double is at least floor(p / v) (every integer
+        // below 2^53 is a double) and at most floor(p / v) + 1; the fma
+        // residual p - f v is rounded once, so its sign is that of the exact
+        // residual, and a negative one means f overshoots by one.
+        const double p = (double)pa.points[r * D + c - 1], w = (double)pa.voxel.v[c - 1];
+        double f = floor(p / w);
+        if (fma(-f, w, p) < 0.0) f -= 1.0;
+        bad = bad || !(f >= -1073741824.0 && f <= 1073741824.0);   // also NaN
+        v[c] = bad ? 0 : (int32_t)f;
+    }
+    *bad_out = *bad_out || bad;
+}
+
+// First kernel of a build: the table's header, the words of a grid cleared,
+// the row numbers set to row_init, and the box of every block's rows (also
+// their common bits: the lowest bit that varies is the column's step).
+// Blocks past the first `boxes` only clear.  Bound: the 16 bytes of a row read
+// and about 50 cleared.  The blocks' boxes are combined by every block of the
+// next kernel; atomics on one box in the header took most of the 11.7 us that
+// this kernel's forerunner took at 300,000 rows (12-20 us up to 600,000),
+// beside a kernel of 9 us that cleared slots.
+template <int NC, bool POINTS>
+__global__ void __launch_bounds__(kBoxThreads, NC <= 5 ? 6 : 4) k_box(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol,
+                                                     StrideArg st, PointsArg pa, void* table, int64_t cap, GridLayout g,
+                                                     int boxes, int64_t header_n, int32_t row_init) {
+    constexpr int W = kBoxThreads / 64;
+    __shared__ int32_t sh[kBoxInts * W];
+    TableHeader* h = reinterpret_cast<TableHeader*>(table);
+    if ((int)blockIdx.x >= boxes) {
+        const int64_t i0 = (int64_t)(blockIdx.x - boxes) * kBoxThreads + threadIdx.x,
+                      step = (int64_t)(gridDim.x - boxes) * kBoxThreads;
+        int4* words = reinterpret_cast<int4*>(grid_words(table));
+        for (int64_t i = i0; i < g.word_bytes / 16; i += step) words[i] = int4{0, 0, 0, 0};
+        if (g.max_cells > 0 && row_init >= 0) {   // (a table without repeated rows writes every entry)
+            int32_t* rowof = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + g.rowof);
+            for (int64_t i = i0; i < n; i += step) rowof[i] = row_init;
+        }
+        return;
+    }
+    const int64_t first = (int64_t)blockIdx.x * kBoxThreads + threadIdx.x, stride = (int64_t)boxes * kBoxThreads;
+    Box x;
+    box_empty<NC>(x);
+    // a row past the end repeats the thread's first one
+    constexpr int B = POINTS ? kBoxRows / 2 : kBoxRows;
+    bool bad = false;
+    for (int64_t r0 = first; r0 < n; r0 += B * stride) {
+        int32_t v[B][NC];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const int64_t r = r0 + i * stride < n ? r0 + i * stride : r0;
+            if constexpr (POINTS) {
+                quantize_row<NC>(pa, r, ncol, v[i], &bad);
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    if (c < ncol) pa.qc[r * ncol + c] = v[i][c];
+            } else {
+                load_row<NC>(coords, vec, r, ncol, st, v[i], &bad);
+            }
         }
 #pragma unroll
-        for (int i = 0; i < kBboxRows; ++i) {
+        for (int i = 0; i < B; ++i) {
 #pragma unroll
-            for (int c = 0; c < kMaxCols; ++c) {
+            for (int c = 0; c < NC; ++c) {
                 if (c >= ncol) break;
-                int64_t x = raw[i][c];
-                if (st.on && c > 0) x = floor_mul(x, st.s[c]);
-                out_of_range |= x < INT_MIN || x > INT_MAX;   // strided value left int32
-                lo[c] = x < lo[c] ? x : lo[c];
-                hi[c] = x > hi[c] ? x : hi[c];
-                vary[c] |= (int)(x ^ v0[c]);
+                x.lo[c] = min(x.lo[c], v[i][c]);
+                x.hi[c] = max(x.hi[c], v[i][c]);
+                x.all_or[c] |= v[i][c];
+                x.all_and[c] &= v[i][c];
             }
         }
     }
-    if (out_of_range) atomicOr(&h->status, ST_RANGE);
-    const int w = threadIdx.x >> 6;
-    for (int c = 0; c < ncol; ++c) {
-        int a = (int)max(lo[c], (int64_t)INT_MIN), b = (int)min(hi[c], (int64_t)INT_MAX), o = vary[c];
-        for (int d = 32; d > 0; d >>= 1) {
-            int ta = __shfl_xor(a, d, 64), tb = __shfl_xor(b, d, 64), to = __shfl_xor(o, d, 64);
-            a = ta < a ? ta : a;
-            b = tb > b ? tb : b;
-            o |= to;
-        }
-        if (__lane_id() == 0) {
-            sh_lo[w][c] = a;
-            sh_hi[w][c] = b;
-            sh_or[w][c] = o;
-        }
-    }
+    x.bad = bad;
+    box_wave<NC>(x, ncol);
+    if ((threadIdx.x & 63) == 0) box_store<NC>(x, ncol, sh, W, threadIdx.x >> 6);
     __syncthreads();
-    if (threadIdx.x < ncol) {
-        const int c = threadIdx.x;
-        int a = sh_lo[0][c], b = sh_hi[0][c], o = sh_or[0][c];
-        for (int i = 1; i < kThreads / 64; ++i) {
-            a = sh_lo[i][c] < a ? sh_lo[i][c] : a;
-            b = sh_hi[i][c] > b ? sh_hi[i][c] : b;
-            o |= sh_or[i][c];
-        }
-        atomicMin(&h->lo[c], a);
-        atomicMax(&h->hi[c], b);
-        if (o) atomicOr(&h->vary[c], o);
+    if (threadIdx.x < 64) {
+        box_empty<NC>(x);
+        if (threadIdx.x < W) box_add<NC>(x, ncol, sh, W, threadIdx.x);
+        box_wave<NC>(x, ncol);
+        if (threadIdx.x == 0)
+            box_store<NC>(x, ncol, reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + g.part), boxes,
+                          blockIdx.x);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        h->ncol = ncol;
+        h->capacity = cap;
+        h->n = header_n;
+        h->total = 0;
+        h->rowof16 = (uint32_t)(g.rowof / 16);
     }
 }
 
-// The packed key's layout from the bounding box: bit widths and shifts per
-// column, and the blocked columns of the slot hash (see home_slot).
-struct KeyLayout {
-    int32_t shift[kMaxCols], bits[kMaxCols];
-    int32_t total_bits, nblk, blk_shift[3];
+__device__ __forceinline__ Slot empty_slot(int32_t val) {
+    Slot e;
+    e.key = kEmptyKey;
+    e.val = val;
+    e.hi = kHiUnset;
+    return e;
+}
+
+// The slots whose memory the box kernel's results take.
+struct SlotSpan {
+    int64_t first, end;
+};
+__device__ __forceinline__ SlotSpan part_slots(const GridLayout& g, int parts) {
+    const int64_t at = (int64_t)(g.part - kHeaderBytes);
+    return SlotSpan{at / (int64_t)sizeof(Slot), (at + (int64_t)parts * kBoxInts * 4 + (int64_t)sizeof(Slot) - 1) / (int64_t)sizeof(Slot)};
+}
+
+// The header of a table over no rows (every query misses: lo > hi).
+__global__ void __launch_bounds__(kThreads) k_table_empty(TableHeader* h, Slot* slots, int64_t cap, int ncol) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += (int64_t)gridDim.x * blockDim.x)
+        slots[i] = empty_slot(-1);
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    h->magic = kTableMagic;
+    h->ncol = ncol;
+    h->capacity = cap;
+    h->n = 0;
+    h->status = 0;
+    h->total_bits = 0;
+    for (int c = 0; c < kMaxCols; ++c) {
+        h->lo[c] = INT_MAX;
+        h->hi[c] = INT_MIN;
+        h->shift[c] = h->bits[c] = h->vary[c] = 0;
+    }
+    h->nblk = 0;
+    for (int i = 0; i < 3; ++i) h->blk_shift[i] = 0;
+}
+
+// The box of all rows, in LDS.
+struct BoxPlan {
+    int32_t lo[kMaxCols], hi[kMaxCols], vary[kMaxCols], step[kMaxCols];
+    int32_t bad;
 };
 
-__device__ void key_layout(const TableHeader* h, int ncol, KeyLayout* kl) {
+// Column c of the box of all rows from that of `count` parts (c == ncol: the
+// range flag), by one wave: four parts per lane, then the lanes.
+__device__ __forceinline__ void box_column(BoxPlan& bp, const int32_t* part, int count, int c, int ncol) {
+    const int lane = threadIdx.x & 63;
+    constexpr int B = kBoxBlocks / 64;
+    const int f0 = c < ncol ? 4 * c : kBoxInts - 4;   // the range flag is the last field
+    int32_t f[4][B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        const int at = min(64 * i + lane, count - 1);   // (a repeated part changes nothing)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e][i] = c < ncol || e == 3 ? part[(f0 + e) * count + at] : 0;
+    }
+    int32_t lo = f[0][0], hi = f[1][0], all_or = f[2][0], all_and = f[3][0], bad = f[3][0];
+#pragma unroll
+    for (int i = 1; i < B; ++i) {
+        lo = min(lo, f[0][i]);
+        hi = max(hi, f[1][i]);
+        all_or |= f[2][i];
+        all_and &= f[3][i];
+        bad |= f[3][i];
+    }
+    if (c == ncol) {   // uniform
+        const bool any = __any(bad != 0);
+        if (lane == 0) bp.bad = any;
+        return;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        lo = min(lo, __shfl_xor(lo, d, 64));
+        hi = max(hi, __shfl_xor(hi, d, 64));
+        all_or |= __shfl_xor(all_or, d, 64);
+        all_and &= __shfl_xor(all_and, d, 64);
+    }
+    if (lane == 0) {
+        bp.lo[c] = lo;
+        bp.hi[c] = hi;
+        bp.vary[c] = all_or ^ all_and;
+        bp.step[c] = all_or != all_and ? __ffs(all_or ^ all_and) - 1 : 0;
+    }
+}
+
+// The strides of a grid's cells (the product of the columns after each one),
+// and whether the table takes that form.
+template <int NC>
+__device__ __forceinline__ bool grid_strides(const BoxPlan& bp, int ncol, const GridLayout& g, uint32_t* mul) {
+    bool grid = g.max_cells > 0 && !bp.bad;
+    int64_t cells = 1;
+#pragma unroll
+    for (int c = NC - 1; c >= 0; --c) {
+        mul[c] = (uint32_t)cells;
+        if (c >= ncol) continue;
+        const int64_t span = (int64_t)bp.hi[c] - bp.lo[c];
+        grid = grid && span < kGridMaxSpan;
+        if (grid) cells *= (span >> bp.step[c]) + 1;   // both factors below 2^31
+        grid = grid && cells <= g.max_cells;
+    }
+    return grid;
+}
+
+// The header's fields that follow from the box (one thread).
+template <int NC>
+__device__ __forceinline__ void write_layout(TableHeader* h, const BoxPlan& bp, int ncol, bool grid,
+                                             const uint32_t* mul) {
     int total = 0;
-    for (int c = 0; c < kMaxCols; ++c) {
-        int b = 0;
-        if (c < ncol) {
-            const int64_t range = (int64_t)h->hi[c] - (int64_t)h->lo[c];
-            if (range > 0) b = 64 - __clzll((unsigned long long)range);
-            if (h->lo[c] > h->hi[c]) b = 0;   // no rows
-        }
-        kl->bits[c] = b;
-        total += b;
+    int32_t bits[NC], shift[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        bits[c] = 0;
+        if (c >= ncol) continue;
+        const int64_t range = (int64_t)bp.hi[c] - bp.lo[c];
+        bits[c] = range > 0 ? 64 - __clzll((unsigned long long)range) : 0;
+        total += bits[c];
     }
     int sh = 0;
-    for (int c = kMaxCols - 1; c >= 0; --c) {
-        kl->shift[c] = c < ncol ? sh : 0;
-        if (c < ncol) sh += kl->bits[c];
+#pragma unroll
+    for (int c = NC - 1; c >= 0; --c) {
+        shift[c] = sh;
+        sh += bits[c];
     }
-    kl->total_bits = total;
     int nb = 0;
-    for (int i = 0; i < 3; ++i) kl->blk_shift[i] = 0;
-    for (int c = 1; c < ncol && nb < 3; ++c) {
-        const int t = h->vary[c] ? __ffs(h->vary[c]) - 1 : -1;   // lowest varying bit
-        if (t >= 0 && t < kl->bits[c]) kl->blk_shift[nb++] = kl->shift[c] + t;
-    }
-    kl->nblk = nb;
-}
-
-// the layout into the header (ST_RANGE when the key needs more than kMaxKeyBits)
-__device__ void store_key_layout(TableHeader* h, int ncol, const KeyLayout& kl) {
-    for (int c = 0; c < ncol; ++c) {
-        h->shift[c] = kl.shift[c];
-        h->bits[c] = kl.bits[c];
-    }
-    h->total_bits = kl.total_bits;
-    if (kl.total_bits > kMaxKeyBits) atomicOr(&h->status, ST_RANGE);
-    for (int i = 0; i < 3; ++i) h->blk_shift[i] = kl.blk_shift[i];
-    h->nblk = kl.nblk;
-}
-
-// one thread: the key layout of a table with no rows to insert
-__global__ void k_plan(TableHeader* h) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    KeyLayout kl;
-    key_layout(h, h->ncol, &kl);
-    store_key_layout(h, h->ncol, kl);
-}
-
-// The insert kernels work the key layout out from the bounding box
-// themselves (thread 0 of every block, into LDS), so no launch of its own
-// sits between the box and the inserts; block 0 also stores it in the header
-// for the kernels after them.  Returns the view a query needs and whether
-// the key fits (all blocks compute the same).
-__device__ __forceinline__ bool block_key_view(TableHeader* h, int ncol, KeyLayout* kl_s, TableView* tv) {
-    if (threadIdx.x == 0) {
-        key_layout(h, ncol, kl_s);
-        if (blockIdx.x == 0) store_key_layout(h, ncol, *kl_s);
-    }
-    __syncthreads();
-    tv->sh.mask = (unsigned long long)h->capacity - 1;
-    tv->sh.nblk = kl_s->nblk;
-    for (int i = 0; i < 3; ++i) tv->sh.blk_shift[i] = kl_s->blk_shift[i];
-    tv->ncol = ncol;
+    int32_t blk[3] = {0, 0, 0};
+#pragma unroll
     for (int c = 0; c < kMaxCols; ++c) {
-        tv->lo[c] = c < ncol ? h->lo[c] : 0;
-        tv->hi[c] = c < ncol ? h->hi[c] : 0;
-        tv->shift[c] = kl_s->shift[c];
+        const bool in = c < NC && c < ncol;
+        const int cc = c < NC ? c : 0;
+        h->lo[c] = in ? bp.lo[c] : INT_MAX;
+        h->hi[c] = in ? bp.hi[c] : INT_MIN;
+        h->shift[c] = in ? shift[cc] : 0;
+        h->bits[c] = in ? bits[cc] : 0;
+        h->vary[c] = in ? bp.vary[c] : 0;
+        h->step[c] = in ? (int8_t)bp.step[c] : 0;
+        h->cstride[c] = in ? mul[cc] : 0;
+        // the lowest varying key bit of the first three spatial columns that vary (see home_slot)
+        if (c > 0 && in && bp.vary[c] && bp.step[c] < bits[cc]) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (nb == i) blk[i] = shift[cc] + bp.step[c];
+            nb = nb < 3 ? nb + 1 : 3;
+        }
     }
-    return kl_s->total_bits <= kMaxKeyBits;
+    for (int i = 0; i < 3; ++i) h->blk_shift[i] = blk[i];
+    h->nblk = nb;
+    h->total_bits = total;
+    h->status = total > kMaxKeyBits || bp.bad ? ST_RANGE : 0;
+    h->magic = grid ? kGridMagic : kTableMagic;
+}
+
+// Second kernel of a build: every block combines the boxes of the first one's
+// blocks and decides the table's form; block 0 writes the header.  A grid:
+// each row sets the bit of its cell, rows of a wave that share a word
+// (neighbours of a sorted row list) in one atomic.
+template <int NC>
+__global__ void __launch_bounds__(kThreads) k_mark(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol,
+                                                   StrideArg st, void* table, int64_t cap, GridLayout g, int parts,
+                                                   int32_t init_val) {
+    __shared__ BoxPlan bp;
+    TableHeader* h = reinterpret_cast<TableHeader*>(table);
+    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
+    int32_t v[NC];
+    bool unused = false;   // the box kernel has found values outside int32
+    load_row<NC>(coords, vec, r < n ? r : 0, ncol, st, v, &unused);   // in flight during the box
+    const int32_t* part = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + g.part);
+    for (int c = threadIdx.x >> 6; c <= ncol; c += kThreads / 64) box_column(bp, part, parts, c, ncol);   // a wave per column
+    __syncthreads();
+    uint32_t mul[NC];
+    const bool grid = grid_strides<NC>(bp, ncol, g, mul);
+    if (blockIdx.x == 0 && threadIdx.x == 0) write_layout<NC>(h, bp, ncol, grid, mul);
+    if (!grid) {   // empty slots, but for those that hold the boxes, which other blocks may still read
+        const SlotSpan p = part_slots(g, parts);
+        Slot* slots = table_slots(table);
+        for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < cap; i += (int64_t)gridDim.x * kThreads)
+            if (i < p.first || i >= p.end) slots[i] = empty_slot(init_val);
+        return;
+    }
+    uint32_t word = ~0u, bits = 0;
+    if (r < n) {
+        uint32_t cell = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (c < ncol) cell += ((uint32_t)(v[c] - bp.lo[c]) >> bp.step[c]) * mul[c];
+        word = cell >> 5;
+        bits = 1u << (cell & 31);
+    }
+    // the bits of a run of lanes with the same word, collected in its first lane
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t ow = __shfl_down(word, d, 64), ob = __shfl_down(bits, d, 64);
+        if ((int)(threadIdx.x & 63) + d < 64 && ow == word) bits |= ob;
+    }
+    const uint32_t pw = __shfl_up(word, 1, 64);
+    if (r < n && ((threadIdx.x & 63) == 0 || pw != word)) atomicOr(&grid_words(table)[word].bits, bits);
+}
+
+// Third kernel.  A grid: the row numbers' places.  A block takes a share of
+// the words, adds up their occupied cells and claims that many places with
+// one atomic; a word's `before` is its block's start plus the cells of the
+// block's words before it (the order of the blocks is arbitrary and seen by
+// nobody: a place only has to be the word's own).  A hash: the empty slots
+// that the second kernel left out.
+constexpr int kIndexThreads = 1024;
+constexpr int kIndexWords = 6;
+
+__global__ void __launch_bounds__(kIndexThreads) k_index(void* table, GridLayout g, int parts,
+                                                         int32_t init_val) {
+    TableHeader* h = reinterpret_cast<TableHeader*>(table);
+    const int64_t first = (int64_t)blockIdx.x * kIndexThreads + threadIdx.x,
+                  stride = (int64_t)gridDim.x * kIndexThreads;
+    if (h->magic != kGridMagic) {   // uniform
+        const SlotSpan p = part_slots(g, parts);
+        for (int64_t i = p.first + first; i < p.end; i += stride) table_slots(table)[i] = empty_slot(init_val);
+        return;
+    }
+    __shared__ uint32_t wsum[kIndexThreads / 64];
+    __shared__ uint32_t base_sh;
+    GridWord* words = grid_words(table);
+    const int64_t range0 = (int64_t)h->hi[0] - h->lo[0];
+    const int64_t cells = ((range0 >> h->step[0]) + 1) * (int64_t)h->cstride[0];
+    const int64_t nw = (cells + 31) / 32;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // kIndexWords words per thread and round, in registers: one round from about 1,400 rows on
+    for (int64_t i0 = (int64_t)blockIdx.x * kIndexThreads; i0 < nw; i0 += kIndexWords * stride) {
+        uint32_t bits[kIndexWords];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int u = 0; u < kIndexWords; ++u) {
+            const int64_t i = i0 + u * stride + threadIdx.x;
+            bits[u] = i < nw ? words[i].bits : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kIndexWords; ++u) sum += (uint32_t)__popc(bits[u]);
+        uint32_t inc = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        __syncthreads();   // the previous round's sums have been read
+        if (lane == 63) wsum[wave] = inc;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+        for (int i = 0; i < kIndexThreads / 64; ++i) {
+            if (i < wave) before += wsum[i];
+            all += wsum[i];
+        }
+        if (threadIdx.x == 0) base_sh = all ? atomicAdd(&h->total, all) : 0u;
+        __syncthreads();
+        uint32_t run = base_sh + before + inc - sum;
+#pragma unroll
+        for (int u = 0; u < kIndexWords; ++u) {
+            if (bits[u]) words[i0 + u * stride + threadIdx.x].before = run;   // (an empty word's is never read)
+            run += (uint32_t)__popc(bits[u]);
+        }
+    }
 }
 
 // Wide keys: the CAS claims a slot by the key's low 62 bits and the claiming
@@ -234,173 +559,134 @@ __device__ __forceinline__ int wide_round(Slot* slots, unsigned long long s, uns
     return h2 == kHiUnset ? 3 : (h2 == hi ? 2 : 0);
 }
 
-// a row of a table with wide keys (k_insert)
-__device__ void insert_wide(const TableView& tv, const int64_t* v, int64_t r, TableHeader* h, Slot* slots) {
-    u128 key;
-    if (!pack_key_wide(tv, v, &key)) {   // cannot happen: the box holds every row
-        atomicOr(&h->status, ST_RANGE);
-        return;
-    }
-    const unsigned long long lo = wide_lo(key), mask = tv.sh.mask;
-    const int32_t hi = wide_hi(key);
-    unsigned long long s = home_slot_wide(tv.sh, key);
-    int polls = 0;
-    for (unsigned long long i = 0; i <= mask;) {
-        const int res = wide_round(slots, s, lo, hi);
-        if (res == 1) {
-            slots[s].val = (int32_t)r;
-            return;
-        }
-        if (res == 2) {
-            atomicOr(&h->status, ST_DUP);
-            return;
-        }
-        if (res == 3) {
-            if (++polls > kWidePolls) break;
-            continue;
-        }
-        s = (s + 1) & mask;
-        ++i;
-    }
-    atomicOr(&h->status, ST_FULL);
-}
-
-__global__ void __launch_bounds__(kThreads) k_insert(const int32_t* coords, int64_t n, TableHeader* h,
-                                                     Slot* slots) {
-    __shared__ KeyLayout kl_s;
-    const int ncol = h->ncol;
-    TableView tv;
-    const bool fits = block_key_view(h, ncol, &kl_s, &tv);
-    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (r >= n || !fits) return;
-    if (h->status & ST_RANGE) return;   // set by the box: a row outside int32
+// Hash: the slot that holds the row's key, claimed if none did: 1 claimed,
+// 2 found, 0 none free (or a key outside the box, which cannot happen).
+template <int NC>
+__device__ __forceinline__ int find_or_insert(const TableView& tv, const int32_t* v, int total_bits, TableHeader* h,
+                                              Slot* slots, unsigned long long* slot) {
     const unsigned long long mask = tv.sh.mask;
-    int64_t v[kMaxCols];
-    StrideArg none{};
-    load_row(coords, r, ncol, none, v);
-    if (kl_s.total_bits > kNarrowKeyBits) {   // uniform
-        insert_wide(tv, v, r, h, slots);
-        return;
+    if (total_bits > kNarrowKeyBits) {   // uniform
+        u128 key;
+        if (!pack_key_wide<NC>(tv, v, &key)) {
+            atomicOr(&h->status, ST_RANGE);
+            return 0;
+        }
+        const unsigned long long lo = wide_lo(key);
+        const int32_t hi = wide_hi(key);
+        unsigned long long s = home_slot_wide(tv.sh, key);
+        int polls = 0;
+        for (unsigned long long i = 0; i <= mask;) {
+            const int res = wide_round(slots, s, lo, hi);
+            if (res == 1 || res == 2) {
+                *slot = s;
+                return res;
+            }
+            if (res == 3) {
+                if (++polls > kWidePolls) break;
+                continue;
+            }
+            s = (s + 1) & mask;
+            ++i;
+        }
+        atomicOr(&h->status, ST_FULL);
+        return 0;
     }
     unsigned long long key;
-    if (!pack_key(tv, v, &key)) {  // cannot happen: the box holds every row
+    if (!pack_key<NC>(tv, v, &key)) {
         atomicOr(&h->status, ST_RANGE);
-        return;
+        return 0;
     }
     unsigned long long s = home_slot(tv.sh, key);
     for (unsigned long long i = 0; i <= mask; ++i) {
-        unsigned long long prev = atomicCAS(&slots[s].key, kEmptyKey, key);
-        if (prev == kEmptyKey) {
-            slots[s].val = (int32_t)r;
-            return;
-        }
-        if (prev == key) {
-            atomicOr(&h->status, ST_DUP);
-            return;
+        const unsigned long long prev = atomicCAS(&slots[s].key, kEmptyKey, key);
+        if (prev == kEmptyKey || prev == key) {
+            *slot = s;
+            return prev == key ? 2 : 1;
         }
         s = (s + 1) & mask;
     }
     atomicOr(&h->status, ST_FULL);
+    return 0;
 }
 
-// strided: find-or-insert the strided key, keep the smallest input row that
-// produces it; remember the slot of every row.
-// Rows of one wave are consecutive, so rows with the same (strided) key are
-// often neighbouring lanes: only the first lane of each run of equal keys
-// inserts (its row is the run's smallest) and the others take its slot by a
-// shuffle, which spares the contended atomics on the shared slot.
-__global__ void __launch_bounds__(kThreads) k_insert_min(const int32_t* coords, int64_t n, StrideArg st,
-                                                         TableHeader* h, Slot* slots, int64_t* slot_of) {
-    __shared__ KeyLayout kl_s;
-    const int ncol = h->ncol;
-    TableView tv;
-    const bool fits = block_key_view(h, ncol, &kl_s, &tv);
-    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+// The row number that a table keeps at place s: a slot of a hash, an entry of
+// a grid's row numbers.
+__device__ __forceinline__ int32_t* row_number(void* table, bool grid, const TableHeader* h, unsigned long long s) {
+    return grid ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + (size_t)h->rowof16 * 16) + s
+                : &table_slots(table)[s].val;
+}
+
+// Fourth kernel: every row's number into the table.  MIN (strided and
+// quantized rows, which repeat): the smallest row of each key stays, and the
+// place of every row is kept in slot_of.  Rows of a wave are consecutive, so
+// rows with the same key are often neighbouring lanes: only the first lane of
+// each run of equal keys updates the place (its row is the run's smallest)
+// and, in a hash, inserts; the others take its place by a shuffle.
+template <int NC, bool MIN>
+__global__ void __launch_bounds__(kThreads) k_place(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol,
+                                                    StrideArg st, void* table, int64_t* __restrict__ slot_of) {
+    TableHeader* h = reinterpret_cast<TableHeader*>(table);
+    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
     const bool valid = r < n;
-    if (!fits || (h->status & ST_RANGE)) {   // uniform (the box's flag is set before this kernel)
-        if (valid) slot_of[r] = 0;
+    const bool grid = h->magic == kGridMagic;   // uniform
+    if (h->status & ST_RANGE) {                 // uniform (set before this kernel)
+        if (MIN && valid) slot_of[r] = 0;
         return;
     }
-    const unsigned long long mask = tv.sh.mask;
-    const bool wide = kl_s.total_bits > kNarrowKeyBits;   // uniform
-    unsigned long long key = 0;   // a narrow key, or a wide key's low 62 bits
-    int32_t khi = 0;              // a wide key's high bits
-    u128 wkey = 0;
-    bool ok = false;
-    if (valid) {
-        int64_t v[kMaxCols];
-        load_row(coords, r, ncol, st, v);
-        if (wide) {
-            ok = pack_key_wide(tv, v, &wkey);
-            key = wide_lo(wkey);
-            khi = wide_hi(wkey);
-        } else {
-            ok = pack_key(tv, v, &key);
+    int32_t v[NC];
+    bool unused = false;
+    load_row<NC>(coords, vec, valid ? r : 0, ncol, st, v, &unused);
+    const int lane = threadIdx.x & 63;
+    if (grid) {
+        uint32_t cell = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (c < ncol) cell += ((uint32_t)(v[c] - h->lo[c]) >> h->step[c]) * h->cstride[c];
+        const uint32_t place = grid_place(grid_words(table)[cell >> 5], cell);
+        int32_t* rowof = row_number(table, true, h, 0);
+        if (!MIN) {
+            if (valid) rowof[place] = (int32_t)r;
+            // fewer cells than rows: a row occurs twice
+            if (blockIdx.x == 0 && threadIdx.x == 0 && h->total != (uint32_t)n) atomicOr(&h->status, ST_DUP);
+            return;
         }
-        if (!ok) {
-            atomicOr(&h->status, ST_RANGE);
-            slot_of[r] = 0;
-        }
+        const uint32_t prev = __shfl_up(place, 1, 64);
+        if (valid && (lane == 0 || prev != place)) atomicMin(&rowof[place], (int32_t)r);
+        if (valid) slot_of[r] = (int64_t)place;
+        return;
     }
-    const int lane = __lane_id();
-    const unsigned long long pkey = __shfl_up(key, 1, 64);
-    const int32_t phi = __shfl_up(khi, 1, 64);
-    const bool pok = __shfl_up((int)ok, 1, 64) != 0;
-    const bool follower = ok && lane > 0 && pok && pkey == key && phi == khi;
-    const unsigned long long leaders = __ballot(ok && !follower);
+    const TableView tv = table_view(h, ncol);
+    Slot* slots = table_slots(table);
+    const int total_bits = h->total_bits;
     unsigned long long s = 0;
-    if (ok && !follower) {
-        bool placed = false;
-        if (wide) {   // see insert_wide
-            s = home_slot_wide(tv.sh, wkey);
-            int polls = 0;
-            for (unsigned long long i = 0; i <= mask;) {
-                const int res = wide_round(slots, s, key, khi);
-                if (res == 1 || res == 2) {
-                    atomicMin(&slots[s].val, (int32_t)r);
-                    placed = true;
-                    break;
-                }
-                if (res == 3) {
-                    if (++polls > kWidePolls) break;
-                    continue;
-                }
-                s = (s + 1) & mask;
-                ++i;
-            }
-        } else {
-            s = home_slot(tv.sh, key);
-            for (unsigned long long i = 0; i <= mask; ++i) {
-                const unsigned long long prev = atomicCAS(&slots[s].key, kEmptyKey, key);
-                if (prev == kEmptyKey || prev == key) {
-                    atomicMin(&slots[s].val, (int32_t)r);
-                    placed = true;
-                    break;
-                }
-                s = (s + 1) & mask;
-            }
-        }
-        if (!placed) {
-            atomicOr(&h->status, ST_FULL);
-            s = 0;
-        }
+    if (!MIN) {
+        if (!valid) return;
+        const int res = find_or_insert<NC>(tv, v, total_bits, h, slots, &s);
+        if (res == 1) slots[s].val = (int32_t)r;
+        if (res == 2) atomicOr(&h->status, ST_DUP);
+        return;
     }
+    bool follower = valid && lane > 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) follower = (__shfl_up(v[c], 1, 64) == v[c]) && follower;
+    const unsigned long long leaders = __ballot(valid && !follower);
+    if (valid && !follower && find_or_insert<NC>(tv, v, total_bits, h, slots, &s)) atomicMin(&slots[s].val, (int32_t)r);
     // a follower's run starts at the highest leader lane at or below it
     const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
     const unsigned long long lm = leaders & upto;
     const int ld = lm ? 63 - __clzll(lm) : lane;
     const unsigned long long ls = __shfl(s, ld, 64);
-    if (ok) slot_of[r] = (int64_t)(follower ? ls : s);
+    if (valid) slot_of[r] = (int64_t)ls;
 }
 
-// mark representatives (slot holds this row) and count them per 64-row group
-__global__ void __launch_bounds__(kThreads) k_rep_count(int64_t n, const TableHeader* h, const Slot* slots,
-                                                        int64_t* slot_of, int32_t* cnt) {
+// mark representatives (the place holds this row) and count them per 64-row group
+__global__ void __launch_bounds__(kThreads) k_rep_count(int64_t n, void* table, int64_t* slot_of, int32_t* cnt) {
+    const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
     const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     bool rep = false;
     if (r < n && h->status == 0) {
         const int64_t s = slot_of[r];
-        rep = slots[s].val == (int32_t)r;
+        rep = *row_number(table, h->magic == kGridMagic, h, (unsigned long long)s) == (int32_t)r;
         if (rep) slot_of[r] = ~s;   // negative: representative
     }
     const unsigned long long m = __ballot(rep);
@@ -408,9 +694,16 @@ __global__ void __launch_bounds__(kThreads) k_rep_count(int64_t n, const TableHe
     if (__lane_id() == 0 && g * 64 < n) cnt[g] = __popcll(m);
 }
 
-__global__ void __launch_bounds__(kThreads) k_rep_write(const int32_t* coords, int64_t n, StrideArg st,
-                                                        TableHeader* h, Slot* slots, const int64_t* slot_of,
-                                                        const int64_t* off, int32_t* out_coords, int32_t* rep_row) {
+// The representatives become the output rows, in row order: their coordinates,
+// their numbers in the table, and (quantization) their input rows and labels.
+template <int NC>
+__global__ void __launch_bounds__(kThreads) k_rep_write(const int32_t* __restrict__ coords, bool vec, int64_t n,
+                                                        int ncol, StrideArg st, void* table, const int64_t* slot_of,
+                                                        const int64_t* off, int32_t* __restrict__ out_coords,
+                                                        int32_t* __restrict__ rep_row,
+                                                        const int32_t* __restrict__ labels,
+                                                        int32_t* __restrict__ out_labels) {
+    const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
     const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     bool rep = false;
     int64_t s = 0;
@@ -422,82 +715,238 @@ __global__ void __launch_bounds__(kThreads) k_rep_write(const int32_t* coords, i
     const unsigned long long m = __ballot(rep);
     if (!rep) return;
     const int64_t row = off[r >> 6] + __popcll(m & lanemask_lt());
-    const int ncol = h->ncol;
-    int64_t v[kMaxCols];
-    load_row(coords, r, ncol, st, v);
-    for (int c = 0; c < ncol; ++c) out_coords[row * ncol + c] = (int32_t)v[c];
-    slots[s].val = (int32_t)row;
+    int32_t v[NC];
+    bool unused = false;
+    load_row<NC>(coords, vec, r, ncol, st, v, &unused);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (c < ncol) out_coords[row * ncol + c] = v[c];
+    *row_number(table, h->magic == kGridMagic, h, (unsigned long long)s) = (int32_t)row;
     if (rep_row) rep_row[row] = (int32_t)r;
+    if (out_labels) out_labels[row] = labels[r];
 }
 
-// ---------------------------------------------------------------------------
-// Sparse tensor quantization (Sec. 4.1, Alg. 1): integer rows (b, floor(p/v))
-// deduplicated through the table exactly as strided output coordinates are
-// (first point of a voxel is its representative, rows in the order of their
-// representatives), then labels merged per voxel.
-// ---------------------------------------------------------------------------
-struct VoxelArg {
-    float v[kMaxCols - 1];   // voxel size per spatial axis
-};
-
-// qc[r] = (batch[r] or 0, floor(p_d / v_d)), the floor of the exact quotient
-// of the stored float32 values.  A coordinate outside +-2^30 sets the range
-// status.
-__global__ void __launch_bounds__(kThreads) k_quantize(const float* __restrict__ points,
-                                                       const int32_t* __restrict__ batch, int64_t n, int D, VoxelArg va,
-                                                       int32_t* __restrict__ qc, TableHeader* h) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const int ncol = D + 1;
-    qc[r * ncol] = batch ? batch[r] : 0;
-    bool bad = false;
-    for (int d = 0; d < D; ++d) {
-        // floor of the exact quotient p / v of the stored float32 values.  The
-        // quotient rounded to double is at least floor(p / v) (every integer
-        // below 2^53 is a double) and at most floor(p / v) + 1; the fma
-        // residual p - f v is rounded once, so its sign is that of the exact
-        // residual, and a negative one means f overshoots by one.
-        const double p = (double)points[r * D + d], v = (double)va.v[d];
-        double f = floor(p / v);
-        if (fma(-f, v, p) < 0.0) f -= 1.0;
-        bad |= !(f >= -1073741824.0 && f <= 1073741824.0);   // also NaN
-        qc[r * ncol + 1 + d] = bad ? 0 : (int32_t)f;
-    }
-    if (bad) atomicOr(&h->status, ST_RANGE);
-}
-
-// per voxel: the row of every point (inverse) and the min / max label of its points
-__global__ void __launch_bounds__(kThreads) k_quant_labels(int64_t n, const TableHeader* h, const Slot* slots,
+// Quantization: the voxel of every point (inverse), and ignore_label for a
+// voxel of which a point has another label than its first one (f of Alg. 1;
+// every writer of a voxel's label here stores the same value).
+__global__ void __launch_bounds__(kThreads) k_quant_labels(int64_t n, void* table,
                                                            const int64_t* __restrict__ slot_of,
+                                                           const int32_t* __restrict__ rep,
                                                            const int32_t* __restrict__ labels,
-                                                           int32_t* __restrict__ inverse, int32_t* __restrict__ lmin,
-                                                           int32_t* __restrict__ lmax) {
+                                                           int32_t ignore_label, int32_t* __restrict__ inverse,
+                                                           int32_t* __restrict__ out_labels) {
+    const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n || h->status != 0) return;
     int64_t sl = slot_of[r];
     if (sl < 0) sl = ~sl;   // a representative
-    const int32_t o = slots[sl].val;
+    const int32_t o = *row_number(table, h->magic == kGridMagic, h, (unsigned long long)sl);
     if (o < 0 || o >= n) return;
     if (inverse) inverse[r] = o;
-    if (labels) {
-        atomicMin(&lmin[o], labels[r]);
-        atomicMax(&lmax[o], labels[r]);
+    if (out_labels && labels[r] != labels[rep[o]]) out_labels[o] = ignore_label;
+}
+
+// ---------------------------------------------------------------------------
+// Few rows: the whole build in one block
+// ---------------------------------------------------------------------------
+// Up to kSmallRows rows, the steps above by one block whose grid words, row
+// numbers and output numbers lie in LDS; MIN also numbers the distinct keys
+// and writes the output rows (as k_rep_count to k_quant_labels do).  Bound:
+// latency.  At 2,000 rows the launches of the separate kernels take 4 to 7 us
+// each, one after another: a build four of them, a strided one seven, a
+// quantization eight.
+struct SmallOut {   // MIN
+    int32_t *out_coords, *rep_row, *inverse, *out_labels;
+    const int32_t* labels;
+    int32_t ignore_label;
+};
+
+template <int NC, bool MIN, bool POINTS>
+__global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restrict__ coords, bool vec, int n, int ncol,
+                                                         StrideArg st, PointsArg pa, void* table, int64_t cap,
+                                                         GridLayout g, int64_t header_n, SmallOut out) {
+    constexpr int W = kSmallThreads / 64;
+    __shared__ BoxPlan bp;
+    __shared__ int32_t sh[kBoxInts * W];
+    __shared__ uint32_t bits[kSmallWords];
+    __shared__ uint16_t before[kSmallWords];
+    __shared__ int32_t first[kSmallRows];    // a grid's row numbers
+    __shared__ int32_t number[kSmallRows];   // output row of a representative, by its input row
+    __shared__ uint8_t differs[MIN ? kSmallRows : 1];
+    __shared__ int32_t wsum[W * kSmallPer];
+    TableHeader* h = reinterpret_cast<TableHeader*>(table);
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    int32_t v[kSmallPer][NC];
+    Box x;
+    box_empty<NC>(x);
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) {
+        const int r = min(i * kSmallThreads + t, n - 1);   // a row past the end repeats the last one
+        if constexpr (POINTS) quantize_row<NC>(pa, r, ncol, v[i], &bad);
+        else load_row<NC>(coords, vec, r, ncol, st, v[i], &bad);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (c >= ncol) break;
+            x.lo[c] = min(x.lo[c], v[i][c]);
+            x.hi[c] = max(x.hi[c], v[i][c]);
+            x.all_or[c] |= v[i][c];
+            x.all_and[c] &= v[i][c];
+        }
     }
-}
-
-__global__ void __launch_bounds__(kThreads) k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-// voxel label: the points' common label, else ignore_label (f of Alg. 1)
-__global__ void __launch_bounds__(kThreads) k_quant_final(int64_t cap, const TableHeader* h,
-                                                          const int32_t* __restrict__ lmin,
-                                                          const int32_t* __restrict__ lmax, int32_t ignore_label,
-                                                          int32_t* __restrict__ out_labels) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= cap || o >= h->n || h->status != 0) return;
-    out_labels[o] = lmin[o] == lmax[o] ? lmin[o] : ignore_label;
+    x.bad = bad;
+    box_wave<NC>(x, ncol);
+    if (lane == 0) box_store<NC>(x, ncol, sh, W, wave);
+    __syncthreads();
+    for (int c = wave; c <= ncol; c += W) box_column(bp, sh, W, c, ncol);
+    __syncthreads();
+    uint32_t mul[NC];
+    const bool grid = grid_strides<NC>(bp, ncol, g, mul);   // (max_cells fits the words in LDS)
+    if (t == 0) {
+        h->ncol = ncol;
+        h->capacity = cap;
+        h->n = header_n;
+        h->total = 0;
+        h->rowof16 = (uint32_t)(g.rowof / 16);
+        write_layout<NC>(h, bp, ncol, grid, mul);
+    }
+    if (bp.bad) return;
+    int32_t place[kSmallPer], fst[kSmallPer];
+    unsigned long long slot[kSmallPer];
+    Slot* slots = table_slots(table);
+    int32_t* rowof = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + g.rowof);
+    if (grid) {
+        const int64_t span0 = (int64_t)bp.hi[0] - bp.lo[0];
+        const int nw = (int)((((span0 >> bp.step[0]) + 1) * (int64_t)mul[0] + 31) / 32);
+        for (int i = t; i < nw; i += kSmallThreads) bits[i] = 0;
+        for (int i = t; i < n; i += kSmallThreads) first[i] = INT_MAX;
+        __syncthreads();
+        uint32_t cell[kSmallPer];
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            cell[i] = 0;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                if (c < ncol) cell[i] += ((uint32_t)(v[i][c] - bp.lo[c]) >> bp.step[c]) * mul[c];
+            if (i * kSmallThreads + t < n) atomicOr(&bits[cell[i] >> 5], 1u << (cell[i] & 31));
+        }
+        __syncthreads();
+        // a thread's share of the words is contiguous here: an odd number of words, so that the lanes' reads
+        // spread over the banks
+        const int per = ((nw + kSmallThreads - 1) / kSmallThreads) | 1;
+        const int w0 = min(t * per, nw), w1 = min(w0 + per, nw);
+        uint32_t sum = 0;
+        for (int i = w0; i < w1; ++i) sum += (uint32_t)__popc(bits[i]);
+        uint32_t inc = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        if (lane == 63) wsum[wave] = (int32_t)inc;
+        __syncthreads();
+        uint32_t run = inc - sum, total = 0;
+        for (int i = 0; i < W; ++i) {
+            if (i < wave) run += (uint32_t)wsum[i];
+            total += (uint32_t)wsum[i];
+        }
+        for (int i = w0; i < w1; ++i) {
+            before[i] = (uint16_t)run;
+            run += (uint32_t)__popc(bits[i]);
+        }
+        if (t == 0) {
+            h->total = total;
+            if (!MIN && total != (uint32_t)n) h->status |= ST_DUP;   // fewer cells than rows: a row occurs twice
+        }
+        __syncthreads();
+        GridWord* words = grid_words(table);
+        for (int i = t; i < nw; i += kSmallThreads) words[i] = GridWord{bits[i], before[i]};
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int r = i * kSmallThreads + t;
+            const uint32_t w = cell[i] >> 5;
+            place[i] = (int32_t)grid_place(GridWord{bits[w], before[w]}, cell[i]);
+            if (r < n) atomicMin(&first[place[i]], r);
+        }
+        __syncthreads();
+        if (!MIN) {
+            for (int i = t; i < (int)total; i += kSmallThreads) rowof[i] = first[i];
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) fst[i] = first[place[i]];
+    } else {
+        for (int64_t i = t; i < cap; i += kSmallThreads) slots[i] = empty_slot(MIN ? INT_MAX : -1);
+        __threadfence();   // the header and the empty slots, before other waves use them
+        __syncthreads();
+        if (h->status & ST_RANGE) return;   // uniform: set by write_layout only
+        const TableView tv = table_view(h, ncol);
+        const int total_bits = h->total_bits;
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int r = i * kSmallThreads + t;
+            slot[i] = 0;
+            if (r >= n) continue;
+            const int res = find_or_insert<NC>(tv, v[i], total_bits, h, slots, &slot[i]);
+            if (MIN) {
+                if (res) atomicMin(&slots[slot[i]].val, r);
+            } else {
+                if (res == 1) slots[slot[i]].val = r;
+                if (res == 2) atomicOr(&h->status, ST_DUP);
+            }
+        }
+        if (!MIN) return;
+        __threadfence();
+        __syncthreads();
+        if (__hip_atomic_load(&h->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;   // full
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i)
+            fst[i] = __hip_atomic_load(&slots[slot[i]].val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if constexpr (MIN) {
+        // number the representatives (the first row of each key) in row order
+        unsigned long long rep[kSmallPer];
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int r = i * kSmallThreads + t;
+            rep[i] = __ballot(r < n && fst[i] == r);
+            if (lane == 0) wsum[i * W + wave] = (int32_t)__popcll(rep[i]);
+            if (r < n) differs[r] = 0;
+        }
+        __syncthreads();
+        int32_t base[kSmallPer], n_out = 0;
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i)
+            for (int w = 0; w < W; ++w) {
+                if (w == wave) base[i] = n_out;
+                n_out += wsum[i * W + w];
+            }
+        if (t == 0) h->n = n_out;
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int r = i * kSmallThreads + t;
+            if (r >= n) continue;
+            if (fst[i] == r) number[r] = base[i] + (int32_t)__popcll(rep[i] & lanemask_lt());
+            // a point with another label than the voxel's first one (every writer stores the same)
+            else if (out.out_labels && out.labels[r] != out.labels[fst[i]]) differs[fst[i]] = 1;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int r = i * kSmallThreads + t;
+            if (r >= n) continue;
+            const int32_t o = number[fst[i]];
+            if (out.inverse) out.inverse[r] = o;
+            if (fst[i] != r) continue;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                if (c < ncol) out.out_coords[(int64_t)o * ncol + c] = v[i][c];
+            if (grid) rowof[place[i]] = o;
+            else slots[slot[i]].val = o;
+            if (out.rep_row) out.rep_row[o] = r;
+            if (out.out_labels) out.out_labels[o] = differs[r] ? out.ignore_label : out.labels[r];
+        }
+    }
 }
 
 static unsigned grid_for(int64_t n, int per = kThreads) {
@@ -506,12 +955,8 @@ static unsigned grid_for(int64_t n, int per = kThreads) {
     return (unsigned)g;
 }
 
-static unsigned grid_capped(int64_t n, int64_t cap = 2048) {
-    int64_t g = (n + kThreads - 1) / kThreads;
-    if (g < 1) g = 1;
-    if (g > cap) g = cap;
-    return (unsigned)g;
-}
+// rows that load as one 16-byte word each
+static bool rows_vec(const int32_t* coords, int ncol) { return ncol == 4 && ((uintptr_t)coords & 15) == 0; }
 
 static int read_status(const void* table, hipStream_t s, TableHeader* out) {
     GSC_HIP(hipMemcpyAsync(out, table, sizeof(TableHeader), hipMemcpyDeviceToHost, s));
@@ -525,6 +970,80 @@ static int status_to_code(const TableHeader& h, const char* what) {
                     h.total_bits);
     if (h.status & ST_DUP) return fail(GSC_EDUP, "%s: a coordinate row occurs more than once", what);
     if (h.status & ST_FULL) return fail(GSC_EFULL, "%s: hash table full", what);
+    return GSC_OK;
+}
+
+// The table of no rows.
+static int empty_enqueue(int ncol, void* table, hipStream_t s) {
+    const int64_t cap = table_capacity(0);
+    hipLaunchKernelGGL(k_table_empty, dim3(1), dim3(kThreads), 0, s, reinterpret_cast<TableHeader*>(table),
+                       table_slots(table), cap, ncol);
+    GSC_LAUNCH_CHECK();
+    return GSC_OK;
+}
+
+// The kernels that build a table over n > 0 rows: one for few rows (with MIN,
+// rows that may repeat, it writes the results in `out` too), else four (with
+// MIN, the places of all rows in slot_of, and reps_enqueue follows); with pa.points the rows are
+// the quantized points, stored in pa.qc (= coords) on the way.
+template <int NC, bool MIN>
+static int table_enqueue_nc(const int32_t* coords, int64_t n, int ncol, const StrideArg& st, const PointsArg& pa,
+                            void* table, int64_t header_n, int64_t* slot_of, const SmallOut& out, hipStream_t s) {
+    const int64_t cap = table_capacity(n);
+    const GridLayout g = grid_layout(n, cap);
+    const bool vec = rows_vec(coords, ncol);
+    if (n <= kSmallRows) {
+        auto* small = MIN && pa.points ? k_small<NC, MIN, MIN> : k_small<NC, MIN, false>;
+        hipLaunchKernelGGL(small, dim3(1), dim3(kSmallThreads), 0, s, coords, vec, (int)n, ncol, st, pa, table, cap, g,
+                           header_n, out);
+        GSC_LAUNCH_CHECK();
+        return GSC_OK;
+    }
+    const int32_t init = MIN ? (int32_t)INT_MAX : -1;
+    const int boxes = box_blocks(n, cap);
+    // the words are cleared by blocks of their own (64 bytes a thread)
+    const int64_t clear = std::min<int64_t>(g.word_bytes / (64 * kBoxThreads) + 1, 2048);
+    auto* box = MIN && pa.points ? k_box<NC, MIN> : k_box<NC, false>;   // points only come with MIN
+    hipLaunchKernelGGL(box, dim3((unsigned)(boxes + clear)), dim3(kBoxThreads), 0, s, coords, vec, n, ncol, st,
+                       pa, table, cap, g, boxes, header_n, init);
+    GSC_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_mark<NC>, dim3(grid_for(n)), dim3(kThreads), 0, s, coords, vec, n, ncol, st, table, cap, g,
+                       boxes, init);
+    GSC_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_index, dim3(grid_for(n, kIndexThreads)), dim3(kIndexThreads), 0, s, table, g, boxes, init);
+    GSC_LAUNCH_CHECK();
+    hipLaunchKernelGGL((k_place<NC, MIN>), dim3(grid_for(n)), dim3(kThreads), 0, s, coords, vec, n, ncol, st, table,
+                       slot_of);
+    GSC_LAUNCH_CHECK();
+    return GSC_OK;
+}
+
+template <bool MIN>
+static int table_enqueue(const int32_t* coords, int64_t n, int ncol, const StrideArg& st, const PointsArg& pa,
+                         void* table, int64_t header_n, int64_t* slot_of, const SmallOut& out, hipStream_t s) {
+    switch (ncol) {   // 3D and 4D rows with the columns unrolled
+        case 4: return table_enqueue_nc<4, MIN>(coords, n, ncol, st, pa, table, header_n, slot_of, out, s);
+        case 5: return table_enqueue_nc<5, MIN>(coords, n, ncol, st, pa, table, header_n, slot_of, out, s);
+        default: return table_enqueue_nc<kMaxCols, MIN>(coords, n, ncol, st, pa, table, header_n, slot_of, out, s);
+    }
+}
+
+// Number the distinct keys of a MIN table in the order of their first rows and
+// write them out; their number ends in the header (n).
+static int reps_enqueue(const int32_t* coords, int64_t n, int ncol, const StrideArg& st, void* table,
+                        int64_t* slot_of, int32_t* cnt, int64_t* off, void* scan_ws, int32_t* out_coords,
+                        int32_t* rep_row, const int32_t* labels, int32_t* out_labels, hipStream_t s) {
+    TableHeader* h = reinterpret_cast<TableHeader*>(table);
+    const int64_t groups = (n + 63) / 64;
+    hipLaunchKernelGGL(k_rep_count, dim3(grid_for(n)), dim3(kThreads), 0, s, n, table, slot_of, cnt);
+    GSC_LAUNCH_CHECK();
+    int rc = scan_counts(cnt, groups, off, &h->n, scan_ws, s);
+    if (rc) return rc;
+    const bool vec = rows_vec(coords, ncol);
+    auto* kern = ncol == 4 ? k_rep_write<4> : (ncol == 5 ? k_rep_write<5> : k_rep_write<kMaxCols>);
+    hipLaunchKernelGGL(kern, dim3(grid_for(n)), dim3(kThreads), 0, s, coords, vec, n, ncol, st, table, slot_of, off,
+                       out_coords, rep_row, labels, out_labels);
+    GSC_LAUNCH_CHECK();
     return GSC_OK;
 }
 
@@ -547,23 +1066,8 @@ static int build_enqueue(const int32_t* coords, int64_t n, int32_t D, void* tabl
     if (n > 0 && !coords) return fail(GSC_EINVAL, "%s: coords is null", what);
     if (table_bytes < gsc_table_bytes(n))
         return fail(GSC_ESHORT, "%s: table needs %zu bytes, got %zu", what, gsc_table_bytes(n), table_bytes);
-    const int ncol = D + 1;
-    const int64_t cap = table_capacity(n);
-    TableHeader* h = reinterpret_cast<TableHeader*>(table);
-    Slot* slots = table_slots(table);
-    hipLaunchKernelGGL(k_table_init, dim3(grid_capped(cap)), dim3(kThreads), 0, s, h, slots, cap, ncol, n, -1);
-    GSC_LAUNCH_CHECK();
-    StrideArg none{};
-    if (n > 0) {
-        hipLaunchKernelGGL(k_bbox, dim3(grid_capped(n, 256)), dim3(kThreads), 0, s, coords, n, ncol, none, h);
-        GSC_LAUNCH_CHECK();
-    }
-    if (n > 0)   // the inserts work out (and store) the key layout themselves
-        hipLaunchKernelGGL(k_insert, dim3(grid_for(n)), dim3(kThreads), 0, s, coords, n, h, slots);
-    else
-        hipLaunchKernelGGL(k_plan, dim3(1), dim3(64), 0, s, h);
-    GSC_LAUNCH_CHECK();
-    return GSC_OK;
+    if (n == 0) return empty_enqueue(D + 1, table, s);
+    return table_enqueue<false>(coords, n, D + 1, unit_stride(), PointsArg{}, table, n, nullptr, SmallOut{}, s);
 }
 
 int gsc_coords_build(const int32_t* coords, int64_t n, int32_t D, void* table, size_t table_bytes, void* stream) {
@@ -590,7 +1094,7 @@ int gsc_table_status(const void* table, void* stream) {
     TableHeader hh;
     int rc = read_status(table, reinterpret_cast<hipStream_t>(stream), &hh);
     if (rc) return rc;
-    if (hh.magic != kTableMagic) return fail(GSC_EINVAL, "table_status: not a table built by gsc_coords_build");
+    if (hh.magic != kTableMagic && hh.magic != kGridMagic) return fail(GSC_EINVAL, "table_status: not a table built by gsc_coords_build");
     return status_to_code(hh, "table");
 }
 
@@ -615,9 +1119,7 @@ static int stride_enqueue(const int32_t* in_coords, int64_t n_in, int32_t D, con
     if (n_in < 0 || n_in > INT32_MAX) return fail(GSC_EINVAL, "%s: n_in=%lld invalid", what, (long long)n_in);
     if (!stride || !out_table) return fail(GSC_EINVAL, "%s: null stride/out_table", what);
     if (n_in > 0 && (!in_coords || !out_coords || !ws)) return fail(GSC_EINVAL, "%s: null in_coords/out_coords/ws", what);
-    StrideArg st{};
-    st.on = 1;
-    st.s[0] = 1;
+    StrideArg st = unit_stride();
     for (int d = 0; d < D; ++d) {
         if (stride[d] < 1) return fail(GSC_EINVAL, "%s: stride[%d]=%d must be >= 1", what, d, stride[d]);
         st.s[d + 1] = stride[d];
@@ -627,17 +1129,7 @@ static int stride_enqueue(const int32_t* in_coords, int64_t n_in, int32_t D, con
     if (n_in > 0 && ws_bytes < gsc_stride_ws_bytes(n_in))
         return fail(GSC_ESHORT, "%s: ws needs %zu bytes, got %zu", what, gsc_stride_ws_bytes(n_in), ws_bytes);
     const int ncol = D + 1;
-    const int64_t cap = table_capacity(n_in);
-    TableHeader* h = reinterpret_cast<TableHeader*>(out_table);
-    Slot* slots = table_slots(out_table);
-    hipLaunchKernelGGL(k_table_init, dim3(grid_capped(cap)), dim3(kThreads), 0, s, h, slots, cap, ncol,
-                       (int64_t)0, (int32_t)INT_MAX);
-    GSC_LAUNCH_CHECK();
-    if (n_in == 0) {
-        hipLaunchKernelGGL(k_plan, dim3(1), dim3(64), 0, s, h);
-        GSC_LAUNCH_CHECK();
-        return GSC_OK;
-    }
+    if (n_in == 0) return empty_enqueue(ncol, out_table, s);
     const int64_t groups = (n_in + 63) / 64;
     char* w = reinterpret_cast<char*>(ws);
     int64_t* slot_of = reinterpret_cast<int64_t*>(w);
@@ -646,21 +1138,11 @@ static int stride_enqueue(const int32_t* in_coords, int64_t n_in, int32_t D, con
     w += ((size_t)groups * sizeof(int32_t) + 255) & ~(size_t)255;
     int64_t* off = reinterpret_cast<int64_t*>(w);
     w += ((size_t)(groups + 1) * sizeof(int64_t) + 255) & ~(size_t)255;
-    void* scan_ws = w;
-
-    hipLaunchKernelGGL(k_bbox, dim3(grid_capped(n_in, 256)), dim3(kThreads), 0, s, in_coords, n_in, ncol, st, h);
-    GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_insert_min, dim3(grid_for(n_in)), dim3(kThreads), 0, s, in_coords, n_in, st, h, slots,
-                       slot_of);
-    GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_rep_count, dim3(grid_for(n_in)), dim3(kThreads), 0, s, n_in, h, slots, slot_of, cnt);
-    GSC_LAUNCH_CHECK();
-    int rc = scan_counts(cnt, groups, off, &h->n, scan_ws, s);   // header n = number of output rows
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_rep_write, dim3(grid_for(n_in)), dim3(kThreads), 0, s, in_coords, n_in, st, h, slots,
-                       slot_of, off, out_coords, (int32_t*)nullptr);
-    GSC_LAUNCH_CHECK();
-    return GSC_OK;
+    int rc = table_enqueue<true>(in_coords, n_in, ncol, st, PointsArg{}, out_table, 0, slot_of,
+                                 SmallOut{out_coords, nullptr, nullptr, nullptr, nullptr, 0}, s);
+    if (rc || n_in <= kSmallRows) return rc;
+    return reps_enqueue(in_coords, n_in, ncol, st, out_table, slot_of, cnt, off, w, out_coords, nullptr, nullptr,
+                        nullptr, s);
 }
 
 int gsc_coords_stride(const int32_t* in_coords, int64_t n_in, int32_t D, const int32_t* stride,
@@ -749,15 +1231,9 @@ int gsc_quantize(const float* points, const int32_t* batch, int64_t n, int32_t D
         return fail(GSC_ESHORT, "quantize: ws needs %zu bytes, got %zu", gsc_quantize_ws_bytes(n, D), ws_bytes);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int ncol = D + 1;
-    const int64_t cap = table_capacity(n);
-    TableHeader* h = reinterpret_cast<TableHeader*>(out_table);
-    Slot* slots = table_slots(out_table);
-    hipLaunchKernelGGL(k_table_init, dim3(grid_capped(cap)), dim3(kThreads), 0, s, h, slots, cap, ncol, (int64_t)0,
-                       (int32_t)INT_MAX);
-    GSC_LAUNCH_CHECK();
     if (n == 0) {
-        hipLaunchKernelGGL(k_plan, dim3(1), dim3(64), 0, s, h);
-        GSC_LAUNCH_CHECK();
+        const int rc0 = empty_enqueue(ncol, out_table, s);
+        if (rc0) return rc0;
         GSC_HIP(hipStreamSynchronize(s));
         *n_out = 0;
         return GSC_OK;
@@ -773,40 +1249,19 @@ int gsc_quantize(const float* points, const int32_t* batch, int64_t n, int32_t D
     w += al((size_t)groups * sizeof(int32_t));
     int64_t* off = reinterpret_cast<int64_t*>(w);
     w += al((size_t)(groups + 1) * sizeof(int64_t));
-    int32_t* lmin = reinterpret_cast<int32_t*>(w);
-    w += al((size_t)n * sizeof(int32_t));
-    int32_t* lmax = reinterpret_cast<int32_t*>(w);
-    w += al((size_t)n * sizeof(int32_t));
-    void* scan_ws = w;
-
-    StrideArg none{};
-    hipLaunchKernelGGL(k_quantize, dim3(grid_for(n)), dim3(kThreads), 0, s, points, batch, n, (int)D, va, qc, h);
-    GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_bbox, dim3(grid_capped(n, 256)), dim3(kThreads), 0, s, qc, n, ncol, none, h);
-    GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_insert_min, dim3(grid_for(n)), dim3(kThreads), 0, s, qc, n, none, h, slots, slot_of);
-    GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_rep_count, dim3(grid_for(n)), dim3(kThreads), 0, s, n, h, slots, slot_of, cnt);
-    GSC_LAUNCH_CHECK();
-    int rc = scan_counts(cnt, groups, off, &h->n, scan_ws, s);   // header n = number of voxels
+    const PointsArg pa{points, batch, qc, va};
+    int rc = table_enqueue<true>(qc, n, ncol, unit_stride(), pa, out_table, 0, slot_of,
+                                 SmallOut{out_coords, rep, inverse, out_labels, labels, ignore_label}, s);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_rep_write, dim3(grid_for(n)), dim3(kThreads), 0, s, qc, n, none, h, slots, slot_of, off,
-                       out_coords, rep);
-    GSC_LAUNCH_CHECK();
-    if (labels) {
-        hipLaunchKernelGGL(k_fill_i32, dim3(grid_capped(n)), dim3(kThreads), 0, s, lmin, n, (int32_t)INT_MAX);
-        GSC_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_fill_i32, dim3(grid_capped(n)), dim3(kThreads), 0, s, lmax, n, (int32_t)INT_MIN);
-        GSC_LAUNCH_CHECK();
+    const bool small = n <= kSmallRows;
+    if (!small) {
+        rc = reps_enqueue(qc, n, ncol, unit_stride(), out_table, slot_of, cnt, off, w, out_coords, rep, labels,
+                          out_labels, s);
+        if (rc) return rc;
     }
-    if (labels || inverse) {
-        hipLaunchKernelGGL(k_quant_labels, dim3(grid_for(n)), dim3(kThreads), 0, s, n, h, slots, slot_of, labels,
-                           inverse, lmin, lmax);
-        GSC_LAUNCH_CHECK();
-    }
-    if (labels && out_labels) {
-        hipLaunchKernelGGL(k_quant_final, dim3(grid_for(n)), dim3(kThreads), 0, s, n, h, lmin, lmax, ignore_label,
-                           out_labels);
+    if (!small && (out_labels || inverse)) {
+        hipLaunchKernelGGL(k_quant_labels, dim3(grid_for(n)), dim3(kThreads), 0, s, n, out_table, slot_of, rep, labels,
+                           ignore_label, inverse, out_labels);
         GSC_LAUNCH_CHECK();
     }
     TableHeader hh;

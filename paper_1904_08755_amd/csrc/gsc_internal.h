@@ -36,7 +36,8 @@ void clear_error();
 // ---------------------------------------------------------------------------
 constexpr int kMaxCols = 8;                       // 1 batch column + up to 7 spatial
 constexpr unsigned long long kEmptyKey = ~0ull;    // Slot::key holds <= 62 key bits
-constexpr uint32_t kTableMagic = 0x54435347u;      // "GSCT"
+constexpr uint32_t kTableMagic = 0x54435347u;      // "GSCT": hashed slots
+constexpr uint32_t kGridMagic = 0x47435347u;       // "GSCG": occupancy grid of the bounding box
 constexpr size_t kHeaderBytes = 256;
 // A packed key of up to kNarrowKeyBits bits lives in Slot::key alone; a wider
 // one (up to kMaxKeyBits) keeps its low 62 bits there and the rest in
@@ -63,8 +64,39 @@ struct TableHeader {
     int32_t vary[kMaxCols];  // OR over rows of (row XOR first row): the bits that vary per column
     int32_t nblk;            // spatial columns whose lowest varying key bit selects the slot in a line
     int32_t blk_shift[3];    // that key bit, per blocked column
+    // a grid table (kGridMagic): cell of a row = sum over columns of
+    // ((x_c - lo_c) >> step_c) * cstride_c
+    int8_t step[kMaxCols];       // lowest varying bit of the column (coordinates of a coarser tensor stride)
+    uint32_t cstride[kMaxCols];
+    uint32_t total;              // occupied cells
+    uint32_t rowof16;            // byte offset of the row numbers from the table's start, / 16
 };
 static_assert(sizeof(TableHeader) <= kHeaderBytes, "header too large");
+
+// A grid table keeps, instead of slots, one bit per cell of the rows' bounding
+// box in words of 32 cells, each with the number of occupied cells that come
+// before it in the (arbitrary, but fixed) order of the row numbers:
+// the row at an occupied cell is rowof[before + occupied cells of the word
+// below it].  A query of an empty cell costs one 8-byte read, a neighbourhood
+// shares words, and a scene's words stay in the XCDs' L2, where the hashed
+// slots of the same rows (64 bytes or more per row) do not.
+struct alignas(8) GridWord {
+    uint32_t bits, before;
+};
+inline __host__ __device__ GridWord* grid_words(void* t) {
+    return reinterpret_cast<GridWord*>(reinterpret_cast<char*>(t) + kHeaderBytes);
+}
+inline __host__ __device__ const GridWord* grid_words(const void* t) {
+    return reinterpret_cast<const GridWord*>(reinterpret_cast<const char*>(t) + kHeaderBytes);
+}
+// The box of a grid table spans less than this per column, so that a query's
+// distance from the box plus an offset stays within 32 bits.
+constexpr int64_t kGridMaxSpan = (int64_t)1 << 30;
+
+// Place of an occupied cell's row number.
+__device__ __forceinline__ uint32_t grid_place(const GridWord& w, uint32_t cell) {
+    return w.before + (uint32_t)__popc(w.bits & ((1u << (cell & 31)) - 1u));
+}
 
 struct alignas(16) Slot {
     unsigned long long key;
@@ -186,18 +218,19 @@ __device__ __forceinline__ TableView table_view(const TableHeader* h, int ncol) 
     return t;
 }
 
-// Pack a coordinate (already offset, in 64-bit) into a key; false if it lies
+// Pack a coordinate into a key; false if it lies
 // outside the table's bounding box (such a coordinate cannot be in the table,
 // so a query for it is a miss, never an alias of another key).  Unrolled
-// over kMaxCols with a guard, so the arrays stay in registers.
-__device__ __forceinline__ bool pack_key(const TableView& t, const int64_t* v, unsigned long long* key) {
+// over NC >= ncol with a guard, so the arrays stay in registers.
+template <int NC>
+__device__ __forceinline__ bool pack_key(const TableView& t, const int32_t* v, unsigned long long* key) {
     unsigned long long k = 0;
     bool in = true;
 #pragma unroll
-    for (int c = 0; c < kMaxCols; ++c) {
+    for (int c = 0; c < NC; ++c) {
         if (c < t.ncol) {
             in = in && v[c] >= t.lo[c] && v[c] <= t.hi[c];
-            k |= (unsigned long long)(v[c] - t.lo[c]) << t.shift[c];
+            k |= (unsigned long long)((int64_t)v[c] - t.lo[c]) << t.shift[c];
         }
     }
     *key = k;
@@ -205,25 +238,29 @@ __device__ __forceinline__ bool pack_key(const TableView& t, const int64_t* v, u
 }
 
 // the same for a wide key
-__device__ __forceinline__ bool pack_key_wide(const TableView& t, const int64_t* v, u128* key) {
+template <int NC>
+__device__ __forceinline__ bool pack_key_wide(const TableView& t, const int32_t* v, u128* key) {
     u128 k = 0;
     bool in = true;
 #pragma unroll
-    for (int c = 0; c < kMaxCols; ++c) {
+    for (int c = 0; c < NC; ++c) {
         if (c < t.ncol) {
             in = in && v[c] >= t.lo[c] && v[c] <= t.hi[c];
-            k |= (u128)(unsigned long long)(v[c] - t.lo[c]) << t.shift[c];
+            k |= (u128)(unsigned long long)((int64_t)v[c] - t.lo[c]) << t.shift[c];
         }
     }
     *key = k;
     return in;
 }
 
-// floor(a / s) * s for s > 0
-__device__ __forceinline__ int64_t floor_mul(int64_t a, int64_t s) {
-    int64_t q = a / s;
-    if ((a % s) != 0 && a < 0) q -= 1;
-    return q * s;
+// floor(a / s) * s for s > 0; *bad: the value lies below int32's range
+__device__ __forceinline__ int32_t floor_mul(int32_t a, int32_t s, bool* bad) {
+    if ((s & (s - 1)) == 0) return a & -s;   // uniform: s is a kernel argument
+    int32_t r = a % s;
+    if (r < 0) r += s;
+    const int32_t v = (int32_t)((uint32_t)a - (uint32_t)r);
+    *bad = *bad || v > a;
+    return v;
 }
 
 // ---------------------------------------------------------------------------

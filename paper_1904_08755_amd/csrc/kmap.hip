@@ -4,28 +4,18 @@
 //          input row found (or -1) goes to a dense offset-major neighbour
 //          table nbr[k][j], and per offset a wave64 ballot of hits gives the
 //          pair count of every 64-row group;
-//   scan:  exclusive scan of the (offset-major, group-minor) counts gives the
-//          start of each group's pairs (the group index gidx) and the total;
+//   scan:  inclusive scan of each offset's group counts (one block per
+//          offset);
 //   fill:  each hit is placed at its group start plus its rank among the
 //          wave's hits (popcount of the lower-lane mask), its input row read
-//          from the neighbour table.
+//          from the neighbour table; the group starts (the group index gidx)
+//          and the segment table come out on the way.
 // Pairs of one offset therefore come out sorted by output row, and the
 // result does not depend on scheduling.
 //
-// A map of a coordinate set onto itself (the stride-1 layers of Sec. 3.1:
-// the output coordinates are the rows the table was built from, in the same
-// order) over a region closed under negation, listed so that
-// o_{K-1-k} = -o_k with the origin in the middle, is symmetric: (i, j) is a
-// pair at offset k exactly when (j, i) is one at offset K-1-k, and the middle
-// offset pairs every row with itself.  Whenever the region is listed so and
-// the output has as many rows as the table, the count pass probes only the
-// offsets up to the middle one: each hit also writes its mirrored entry of
-// the neighbour table (set to -1 beforehand), and a second pass counts the
-// mirrored offsets' pairs per group from the table.  The middle offset
-// checks the premise: output row j must find table row j.  If one row does
-// not (other coordinates, another order, rows rewritten since the build),
-// the second pass probes the mirrored offsets itself instead, overwriting
-// their entries, so the result equals the full probe in every case.
+// A grid table (see GridWord) answers a probe with an 8-byte word that stays in
+// L2 and, for a hit, a row number; a hashed table with a slot, a random
+// 128-byte line.
 #include <algorithm>
 #include <climits>
 #include <mutex>
@@ -40,29 +30,31 @@ constexpr int kOffArgMax = 768;   // K * D offsets passed by value in the kernel
 
 // Offsets of the region, either by value in the kernel arguments (no host
 // to device copy, so the map can be enqueued asynchronously) or in device
-// memory (large regions, synchronous mode only).
+// memory (large regions, synchronous mode only).  Arguments are read where
+// they lie, as the kernel's first one: indexed through the parameter itself,
+// the compiler may copy all 3 KB of them to every lane's private memory first
+// (count pass of 300,000 rows: 800 us instead of 20).
+typedef const int32_t __attribute__((address_space(4))) KernargI32;
 struct OffsArg {
     int32_t v[kOffArgMax];
-    __device__ __forceinline__ const int32_t* at(int64_t i) const { return v + i; }
+    static __device__ __forceinline__ KernargI32* at(const OffsArg&, int64_t i) {
+        return (KernargI32*)__builtin_amdgcn_kernarg_segment_ptr() + i;
+    }
 };
 struct OffsPtr {
     const int32_t* p;
-    __device__ __forceinline__ const int32_t* at(int64_t i) const { return p + i; }
+    static __device__ __forceinline__ const int32_t* at(const OffsPtr& o, int64_t i) { return o.p + i; }
 };
 
 __device__ __forceinline__ bool header_ok(const TableHeader* h, int ncol) {
-    return h->magic == kTableMagic && h->ncol == ncol && h->status == 0;
+    return (h->magic == kTableMagic || h->magic == kGridMagic) && h->ncol == ncol && h->status == 0;
 }
 
-// Probes issued together per lane in the count pass: 4 (186 VGPRs at 16 halve
-// the resident waves; 8 and 16 measured slower on a 300k-row map), or 16
-// when every row's wave is resident at once even at that size (a 120k-row
-// map: 53 -> 45 us).  Wide keys take one at a time, so that their path needs
-// no more registers than the others.
-constexpr int kBatch = 4;
-constexpr int kBatchSmall = 16;
-template <typename KeyT, int NB>
-constexpr int batch_of() { return sizeof(KeyT) > 8 ? 1 : NB; }
+// Offsets probed together per lane on a hashed table.  Wide keys take one at a
+// time, so that their path needs no more registers than the others.
+constexpr int kBatch = 5;
+template <typename KeyT>
+constexpr int batch_of() { return sizeof(KeyT) > 8 ? 1 : kBatch; }
 
 // Key arithmetic in KeyT (uint32_t when the table's keys fit in 32 bits, the
 // usual case, uint64_t up to 62 bits, else the 128-bit wide key).  The packed
@@ -88,20 +80,18 @@ struct KeyOps<u128> {
     static __device__ __forceinline__ bool eq(const Slot& e, u128 k) { return e.key == wide_lo(k) && e.hi == wide_hi(k); }
 };
 
-// Count pass.  Each lane owns one output row.  Offsets are probed NB at a
-// time; every load is issued unconditionally (a lane whose query is out of
-// the box reads slot 0 and ignores it) so the NB loads are in flight
-// together, and collision chains are followed in rounds.  A probe reads the
-// whole 16-byte slot, so a hit also yields the input row, which goes to
+// Count pass on a hashed table.  Each lane owns one output row.  Offsets are
+// probed NB at a time; every load is issued unconditionally (a lane whose
+// query is out of the box reads slot 0 and ignores it) so the NB loads are in
+// flight together, and collision chains are followed in rounds.  A probe reads
+// the whole 16-byte slot, so a hit also yields the input row, which goes to
 // nbr[k * n_out + j] (-1 for a miss); hits are counted per 64-row group with
 // a wave ballot.
-template <typename KeyT, int NBT, typename Offs>
+template <typename KeyT, typename Offs>
 __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __restrict__ slots,
                                            const int32_t* __restrict__ out_coords, int64_t n_out, int ncol,
-                                           const Offs& offs, int K, int k_begin, int k_end, int mirror_end,
-                                           int mid, int64_t G, int32_t* __restrict__ cnt,
-                                           int32_t* __restrict__ nbr, bool ok, int64_t j,
-                                           int32_t* __restrict__ not_self) {
+                                           const Offs& offs, int k_begin, int k_end, int64_t G,
+                                           int32_t* __restrict__ cnt, int32_t* __restrict__ nbr, bool ok, int64_t j) {
     const bool valid = ok && j < n_out;
     const int D = ncol - 1;
     const unsigned long long mask = ok ? (unsigned long long)h->capacity - 1 : 0;
@@ -135,7 +125,7 @@ __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __r
     in_b = in_b && (uint32_t)rel[0] <= (uint32_t)span[0];
     const int64_t g = j >> 6;
     const bool writer = __lane_id() == 0 && g < G;
-    constexpr int NB = batch_of<KeyT, NBT>();
+    constexpr int NB = batch_of<KeyT>();
     for (int k0 = k_begin; k0 < k_end; k0 += NB) {
         KeyT key[NB];
         unsigned long long pos[NB];
@@ -144,7 +134,7 @@ __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __r
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int k = min(k0 + b, k_end - 1);
-            const int32_t* o = offs.at((int64_t)k * D);
+            const auto* o = Offs::at(offs, (int64_t)k * D);
             bool in = in_b && k0 + b < k_end;
             KeyT delta = 0;
 #pragma unroll
@@ -155,12 +145,12 @@ __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __r
                 }
             }
             const KeyT kk = base + delta;
-            KeyT local = 0;
+            uint32_t local = 0;
 #pragma unroll
             for (int i = 0; i < 3; ++i)
-                if (i < nblk) local |= ((kk >> bsh[i]) & 1) << i;
-            const unsigned long long hs =
-                (((unsigned long long)KeyOps<KeyT>::hash(kk & clear) << nblk) | (unsigned long long)local) & mask;
+                if (i < nblk) local |= (uint32_t)((kk >> bsh[i]) & 1) << i;
+            const uint32_t hash = KeyOps<KeyT>::hash(kk & clear);
+            const unsigned long long hs = (((unsigned long long)hash << nblk) | local) & mask;
             key[b] = kk;
             pos[b] = in ? hs : 0;
             pend[b] = in;
@@ -201,137 +191,321 @@ __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __r
                 const unsigned long long m = __ballot(hit[b]);
                 if (writer) cnt[(int64_t)k * G + g] = __popcll(m);
                 if (j < n_out) nbr[(int64_t)k * n_out + j] = hit[b] ? row[b] : -1;
-                // the mirrored pair (j, row) at offset K-1-k
-                if (k < mirror_end && hit[b] && row[b] >= 0 && row[b] < n_out)
-                    nbr[(int64_t)(K - 1 - k) * n_out + row[b]] = (int32_t)j;
-                // the middle offset of a self map pairs every row with itself
-                if (k == mid) {
-                    const unsigned long long bad = __ballot(j < n_out && !(hit[b] && row[b] == j));
-                    if (bad && __lane_id() == 0) atomicOr(not_self, 1);
-                }
             }
         }
     }
 }
 
-// Whether a map onto out_coords over a symmetric listing (sym) may be a map
-// of the table's coordinate set onto itself: the table is valid and has as
-// many rows as the output.  The count pass checks the rest (row j finds row j).
-__device__ __forceinline__ bool self_candidate(const TableHeader* h, int ncol, int64_t n_out, int sym) {
-    return sym && header_ok(h, ncol) && h->n == n_out;
+// Count pass on a grid table: a lane per output row, kGridBatch offsets'
+// words and then row numbers in flight together (a lane whose query lies
+// outside the box, or on no cell of its step, reads word 0 and ignores it).
+// Bound: the neighbour table written (4 K bytes per row) and the probes'
+// address arithmetic.
+//
+// A block takes at most kGridBatch offsets (the grid's second dimension has
+// the rest), so a lane's loads are one chain of header, row, word and row
+// number, whatever K.
+constexpr int kGridBatch = 9;
+
+template <int NC, typename Offs>
+__device__ __forceinline__ void count_rows_grid(const void* table, const int32_t* __restrict__ out_coords, bool vec,
+                                                int64_t n_out, int ncol, const Offs& offs, int k0, int k1, int64_t G,
+                                                int32_t* __restrict__ cnt, int32_t* __restrict__ nbr, int64_t j) {
+    const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
+    const GridWord* __restrict__ words = grid_words(table);
+    const int32_t* __restrict__ rowof =
+        reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + (size_t)h->rowof16 * 16);
+    const int D = ncol - 1;
+    const bool valid = j < n_out;
+    const int64_t jj = valid ? j : 0;
+    int32_t x[NC], rel[NC];
+    if (NC == 4 && vec) {
+        const int4 q = reinterpret_cast<const int4*>(out_coords)[jj];
+        x[0] = q.x;
+        x[1 % NC] = q.y;
+        x[2 % NC] = q.z;
+        x[3 % NC] = q.w;
+    } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) x[c] = c < ncol ? out_coords[jj * ncol + c] : 0;
+    }
+    uint32_t span[NC], low[NC], mul[NC];
+    int step[NC];
+    bool in_b = valid;
+    uint32_t base = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        rel[c] = 0;
+        span[c] = low[c] = mul[c] = 0;
+        step[c] = 0;
+        if (c >= ncol) continue;
+        span[c] = (uint32_t)(h->hi[c] - h->lo[c]);   // below 2^30
+        step[c] = h->step[c];
+        low[c] = (1u << step[c]) - 1u;
+        mul[c] = h->cstride[c];
+        // a row this far outside the box reaches it with no offset (|offset| <= 2^30); nearer ones plus an
+        // offset stay within 32 bits, negative sums being above every span as unsigned numbers
+        const int64_t d = (int64_t)x[c] - h->lo[c];
+        const int64_t reach = c == 0 ? 0 : (int64_t)1 << 30;
+        in_b = in_b && d >= -reach && d <= (int64_t)span[c] + reach;
+        rel[c] = (int32_t)d;
+        if (c == 0) {
+            in_b = in_b && ((uint32_t)rel[c] & low[c]) == 0;
+            base = ((uint32_t)rel[c] >> step[c]) * mul[c];
+        }
+    }
+    bool stepped = false;   // uniform
+    uint32_t all = base;
+#pragma unroll
+    for (int c = 1; c < NC; ++c) {
+        stepped = stepped || step[c] != 0;
+        all += (uint32_t)rel[c] * mul[c];
+    }
+    const int64_t g = j >> 6;
+    const bool writer = (threadIdx.x & 63) == 0 && g < G;
+    GridWord w[kGridBatch];
+    uint32_t cell[kGridBatch];
+    bool hit[kGridBatch];
+    int32_t row[kGridBatch];
+#pragma unroll
+    for (int b = 0; b < kGridBatch; ++b) {
+        const auto* o = Offs::at(offs, (int64_t)min(k0 + b, k1 - 1) * D);
+        bool in = in_b && k0 + b < k1;
+        uint32_t at;
+        if (!stepped) {   // the cell is linear in the coordinate: the offset's part is a scalar
+            uint32_t delta = 0;
+#pragma unroll
+            for (int c = 1; c < NC; ++c) {
+                if (c >= ncol) continue;
+                in = in && (uint32_t)rel[c] + (uint32_t)o[c - 1] <= span[c];
+                delta += (uint32_t)o[c - 1] * mul[c];
+            }
+            at = all + delta;
+        } else {
+            at = base;
+#pragma unroll
+            for (int c = 1; c < NC; ++c) {
+                if (c >= ncol) continue;
+                const uint32_t v = (uint32_t)rel[c] + (uint32_t)o[c - 1];
+                in = in && v <= span[c] && (v & low[c]) == 0;
+                at += (v >> step[c]) * mul[c];
+            }
+        }
+        cell[b] = in ? at : 0u;
+        hit[b] = in;
+        w[b] = words[cell[b] >> 5];
+    }
+#pragma unroll
+    for (int b = 0; b < kGridBatch; ++b) {
+        hit[b] = hit[b] && ((w[b].bits >> (cell[b] & 31)) & 1u);
+        row[b] = rowof[hit[b] ? grid_place(w[b], cell[b]) : 0u];
+    }
+#pragma unroll
+    for (int b = 0; b < kGridBatch; ++b) {
+        if (k0 + b >= k1) break;
+        const unsigned long long m = __ballot(hit[b]);
+        if (writer) cnt[(int64_t)(k0 + b) * G + g] = __popcll(m);
+        if (valid) nbr[(int64_t)(k0 + b) * n_out + j] = hit[b] ? row[b] : -1;
+    }
 }
 
-template <typename Offs, int NB>
-__global__ void __launch_bounds__(kThreads) k_kmap_count(const void* table, const int32_t* __restrict__ out_coords,
-                                                         int64_t n_out, int ncol, Offs offs, int K, int sym, int64_t G,
+template <typename Offs>
+__global__ void __launch_bounds__(kThreads) k_kmap_count(Offs offs, const void* table,
+                                                         const int32_t* __restrict__ out_coords, bool vec,
+                                                         int64_t n_out, int ncol, int K, int64_t G,
                                                          int32_t* __restrict__ cnt, int32_t* __restrict__ nbr,
-                                                         int64_t* err, int32_t* not_self) {
+                                                         int64_t* err) {
     const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
     const Slot* __restrict__ slots = table_slots(table);
     const bool ok = header_ok(h, ncol);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *err = ok ? 0 : 1;
-    const bool self = self_candidate(h, ncol, n_out, sym);
-    const int k_end = self ? (K + 1) / 2 : K;        // up to and including the middle offset
-    const int mirror_end = self ? (K - 1) / 2 : 0;   // offsets whose hits are mirrored
-    const int mid = self ? (K - 1) / 2 : -1;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *err = ok ? 0 : 1;
     const int64_t j = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
-    if (h->total_bits <= 32)   // uniform: all lanes take the same path
-        count_rows<uint32_t, NB>(h, slots, out_coords, n_out, ncol, offs, K, 0, k_end, mirror_end, mid, G, cnt, nbr, ok,
-                             j, not_self);
-    else if (h->total_bits <= kNarrowKeyBits)
-        count_rows<unsigned long long, NB>(h, slots, out_coords, n_out, ncol, offs, K, 0, k_end, mirror_end, mid, G, cnt,
-                                       nbr, ok, j, not_self);
-    else
-        count_rows<u128, NB>(h, slots, out_coords, n_out, ncol, offs, K, 0, k_end, mirror_end, mid, G, cnt, nbr, ok, j,
-                         not_self);
-}
-
-// Symmetric listing: clear the self-map check, and if the map may be a self
-// map, start the mirrored offsets' rows of the neighbour table empty.
-__global__ void __launch_bounds__(kThreads) k_kmap_self_init(const void* table, int64_t n_out, int ncol, int K,
-                                                             int sym, int32_t* __restrict__ nbr,
-                                                             int32_t* __restrict__ not_self) {
-    const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *not_self = 0;
-    if (!self_candidate(h, ncol, n_out, sym)) return;
-    const int64_t first = (int64_t)((K + 1) / 2) * n_out, n = (int64_t)(K / 2) * n_out;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        nbr[first + i] = -1;
-}
-
-// Symmetric listing, second pass over the offsets after the middle one: for a
-// self map (the count pass found every row at its own index) their pair
-// counts per 64-row group come from the mirrored entries of the neighbour
-// table; otherwise every row probes them itself.
-template <typename Offs, int NB>
-__global__ void __launch_bounds__(kThreads) k_kmap_mirror_count(const void* table,
-                                                                const int32_t* __restrict__ out_coords, int64_t n_out,
-                                                                int ncol, Offs offs, int K, int sym, int64_t G,
-                                                                int32_t* __restrict__ nbr, int32_t* __restrict__ cnt,
-                                                                int32_t* not_self) {
-    const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
-    if (!self_candidate(h, ncol, n_out, sym)) return;
-    const int64_t j = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
-    if (*not_self) {
-        const Slot* __restrict__ slots = table_slots(table);
-        if (h->total_bits <= 32)
-            count_rows<uint32_t, NB>(h, slots, out_coords, n_out, ncol, offs, K, (K + 1) / 2, K, 0, -1, G, cnt, nbr, true,
-                                 j, not_self);
-        else if (h->total_bits <= kNarrowKeyBits)
-            count_rows<unsigned long long, NB>(h, slots, out_coords, n_out, ncol, offs, K, (K + 1) / 2, K, 0, -1, G, cnt,
-                                           nbr, true, j, not_self);
-        else
-            count_rows<u128, NB>(h, slots, out_coords, n_out, ncol, offs, K, (K + 1) / 2, K, 0, -1, G, cnt, nbr, true, j,
-                             not_self);
-        return;
+    const int per = (K + gridDim.y - 1) / gridDim.y, k0 = blockIdx.y * per, k1 = min(K, k0 + per);
+    // uniform: all lanes take the same path
+    if (ok && h->magic == kGridMagic) {
+        if (ncol == 4) count_rows_grid<4>(table, out_coords, vec, n_out, ncol, offs, k0, k1, G, cnt, nbr, j);
+        else if (ncol == 5) count_rows_grid<5>(table, out_coords, vec, n_out, ncol, offs, k0, k1, G, cnt, nbr, j);
+        else count_rows_grid<kMaxCols>(table, out_coords, vec, n_out, ncol, offs, k0, k1, G, cnt, nbr, j);
+    } else if (h->total_bits <= 32) {
+        count_rows<uint32_t>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
+    } else if (h->total_bits <= kNarrowKeyBits) {
+        count_rows<unsigned long long>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
+    } else {
+        count_rows<u128>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
     }
-    const int64_t g = j >> 6;
-    const bool writer = __lane_id() == 0 && g < G;
-    constexpr int B = 8;
-    for (int k0 = (K + 1) / 2; k0 < K; k0 += B) {
-        int32_t r[B];
+}
+
+// Scan pass: the inclusive scan, in place, of the group counts of one offset
+// per block (cnt[k * G + g], g < G).  The offsets' totals are the last entries,
+// so the fill pass finds every group's start from them without a scan over
+// all K * G counts: one launch instead of the two of the device-wide scan
+// (which took 10 us for 27 x 4,689 counts).  A block walks G counts in rounds
+// of kScanRound, so this is for at most kScanMaxGroups of them; its offsets'
+// totals are scanned again by every fill block, so for at most kScanMaxK.
+constexpr int kScanThreads = 1024;
+constexpr int kScanPer = 4;
+constexpr int64_t kScanRound = (int64_t)kScanThreads * kScanPer;
+constexpr int64_t kScanMaxGroups = 65536;
+constexpr int kScanMaxK = 1024;
+
+__global__ void __launch_bounds__(kScanThreads) k_kmap_scan(int32_t* __restrict__ cnt, int64_t G) {
+    __shared__ int32_t wsum[2][kScanThreads / 64];
+    cnt += (int64_t)blockIdx.x * G;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t carry = 0;
+    int buf = 0;
+    for (int64_t g0 = 0; g0 < G; g0 += kScanRound, buf ^= 1) {
+        const int64_t g = g0 + (int64_t)threadIdx.x * kScanPer;
+        int32_t v[kScanPer];
 #pragma unroll
-        for (int b = 0; b < B; ++b) r[b] = j < n_out && k0 + b < K ? nbr[(int64_t)(k0 + b) * n_out + j] : -1;
+        for (int i = 0; i < kScanPer; ++i) v[i] = g + i < G ? cnt[g + i] : 0;
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const unsigned long long m = __ballot(r[b] >= 0);
-            if (writer && k0 + b < K) cnt[(int64_t)(k0 + b) * G + g] = __popcll(m);
+        for (int i = 1; i < kScanPer; ++i) v[i] += v[i - 1];
+        int32_t inc = v[kScanPer - 1];
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
         }
+        if (lane == 63) wsum[buf][wave] = inc;
+        __syncthreads();   // one barrier a round: the other round's sums are in the other buffer
+        int32_t before = carry;
+        for (int i = 0; i < kScanThreads / 64; ++i) {
+            if (i < wave) before += wsum[buf][i];
+            carry += wsum[buf][i];
+        }
+        before += inc - v[kScanPer - 1];
+#pragma unroll
+        for (int i = 0; i < kScanPer; ++i)
+            if (g + i < G) cnt[g + i] = before + v[i];
     }
 }
 
 // Fill pass: lane j reads its row of the neighbour table offset by offset;
 // each hit goes to its group start plus its rank among the wave's hits.
+// SCAN: cnt holds the offsets' inclusive scans (k_kmap_scan); the block scans
+// the offsets' totals, and the pass writes gidx, seg and *total itself, and no
+// pair when the total exceeds cap.  Otherwise gidx is given.
+template <bool SCAN>
 __global__ void __launch_bounds__(kThreads) k_kmap_fill(int64_t n_out, int K, int64_t G,
                                                         const int32_t* __restrict__ nbr,
-                                                        const int64_t* __restrict__ gidx, int32_t* __restrict__ in_idx,
-                                                        int32_t* __restrict__ out_idx, int64_t cap) {
+                                                        const int32_t* __restrict__ cnt, int64_t* __restrict__ gidx,
+                                                        int64_t* __restrict__ seg, int64_t* __restrict__ total,
+                                                        int32_t* __restrict__ in_idx, int32_t* __restrict__ out_idx,
+                                                        int64_t cap) {
+    __shared__ int64_t kbase[SCAN ? kScanMaxK + 1 : 1];
     const int64_t j = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
     const bool valid = j < n_out;
     const int64_t g = j >> 6;
-    const unsigned long long below = lanemask_lt();
-    constexpr int B = 8;   // offsets whose table entries (and group starts) are loaded together
-    for (int k0 = 0; k0 < K; k0 += B) {
-        int32_t r[B];
-        int64_t gs[B];
+    const int lane = threadIdx.x & 63;
+    if constexpr (SCAN) {
+        if (threadIdx.x < 64) {   // exclusive scan of the offsets' totals
+            int64_t carry = 0;
+            for (int k0 = 0; k0 < K; k0 += 64) {
+                const int k = k0 + lane;
+                const int64_t c = k < K ? cnt[(int64_t)k * G + G - 1] : 0;
+                int64_t inc = c;
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            r[b] = valid && k0 + b < K ? nbr[(int64_t)(k0 + b) * n_out + j] : -1;
-            gs[b] = g < G && k0 + b < K ? gidx[(int64_t)(k0 + b) * G + g] : 0;
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int64_t u = __shfl_up(inc, d, 64);
+                    if (lane >= d) inc += u;
+                }
+                if (k < K) kbase[k] = carry + inc - c;
+                carry += __shfl(inc, 63, 64);
+            }
+            if (lane == 0) kbase[K] = carry;
         }
+        __syncthreads();
+        if (blockIdx.x == 0) {
+            for (int k = threadIdx.x; k <= K; k += kThreads) seg[k] = kbase[k];
+            if (threadIdx.x == 0) {
+                gidx[(int64_t)K * G] = kbase[K];
+                if (total) *total = kbase[K];
+            }
+        }
+        if (kbase[K] > cap) cap = 0;   // (gidx is still written)
+    }
+    const unsigned long long below = lanemask_lt();
+    constexpr int B = 9;   // offsets whose table entries are loaded together (a divisor of 27)
+    for (int kc = 0; kc < K; kc += 63) {   // 63 offsets' group starts at a time, one per lane
+        const int kl = kc + lane;
+        int64_t start = 0;
+        if (g < G && lane < 63 && kl < K) {
+            if constexpr (SCAN) {
+                start = kbase[kl] + (g > 0 ? cnt[(int64_t)kl * G + g - 1] : 0);
+                gidx[(int64_t)kl * G + g] = start;
+            } else {
+                start = gidx[(int64_t)kl * G + g];
+            }
+        }
+        const int kend = min(K, kc + 63);
+        for (int k0 = kc; k0 < kend; k0 += B) {
+            int32_t r[B];
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const bool hit = r[b] >= 0;
-            const unsigned long long m = __ballot(hit);
-            if (hit) {
-                const int64_t pos = gs[b] + __popcll(m & below);
-                if (pos < cap) {
-                    in_idx[pos] = r[b];
-                    out_idx[pos] = (int32_t)j;
+            for (int b = 0; b < B; ++b) r[b] = valid && k0 + b < kend ? nbr[(int64_t)(k0 + b) * n_out + j] : -1;
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                if (k0 + b >= kend) break;
+                const int64_t gs = __shfl(start, k0 + b - kc, 64);
+                const bool hit = r[b] >= 0;
+                const unsigned long long m = __ballot(hit);
+                if (hit) {
+                    const int64_t pos = gs + __popcll(m & below);
+                    if (pos < cap) {
+                        in_idx[pos] = r[b];
+                        out_idx[pos] = (int32_t)j;
+                    }
                 }
             }
         }
     }
+}
+
+// Group starts, segments and pairs from the dense form and the group counts.
+// res (nullable, device): res[0] gets the number of pairs.  With n_pairs (host) the
+// call waits and reads res[0..1], and sets it (ESHORT
+// when it exceeds cap_pairs, EINVAL when the count pass found no valid table).
+static int pairs_enqueue(int64_t n, int K, int64_t G, const int32_t* nbr, int32_t* cnt, int64_t* gidx, int64_t* seg,
+                         int64_t* res, void* scan_ws, int32_t* in_idx, int32_t* out_idx, int64_t cap_pairs,
+                         int64_t* n_pairs, int ncol, hipStream_t s) {
+    const unsigned nblk = (unsigned)((n + kThreads - 1) / kThreads);
+    const bool by_offset = G > 0 && G <= kScanMaxGroups && K <= kScanMaxK;
+    if (by_offset) {
+        hipLaunchKernelGGL(k_kmap_scan, dim3((unsigned)K), dim3(kScanThreads), 0, s, cnt, G);
+        GSC_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_kmap_fill<true>, dim3(nblk), dim3(kThreads), 0, s, n, K, G, nbr, cnt, gidx, seg, res,
+                           in_idx, out_idx, cap_pairs);
+        GSC_LAUNCH_CHECK();
+    } else {
+        // the scan also writes seg[k] = gidx[k * G] (a launch of its own without groups)
+        int rc = G > 0 ? scan_counts(cnt, K * G, gidx, res, scan_ws, s, seg, G)
+                       : scan_counts(cnt, 0, gidx, res, scan_ws, s);
+        if (rc) return rc;
+        if (G == 0) {
+            rc = seg_from_gidx(gidx, K, G, seg, s);
+            if (rc) return rc;
+        }
+    }
+    int64_t bound = cap_pairs;
+    if (n_pairs) {
+        int64_t hres[2];
+        GSC_HIP(hipMemcpyAsync(hres, res, sizeof(hres), hipMemcpyDeviceToHost, s));
+        GSC_HIP(hipStreamSynchronize(s));
+        // the count kernel (launched when n > 0) writes the header check
+        if (nblk > 0 && hres[1])
+            return fail(GSC_EINVAL, "kernel_map: in_table is not a valid table of %d-column rows", ncol);
+        *n_pairs = hres[0];
+        if (hres[0] > cap_pairs)
+            return fail(GSC_ESHORT, "kernel_map: %lld pairs exceed cap_pairs=%lld", (long long)hres[0],
+                        (long long)cap_pairs);
+        bound = hres[0];
+    }
+    if (!by_offset && nblk > 0 && bound > 0) {
+        hipLaunchKernelGGL(k_kmap_fill<false>, dim3(nblk), dim3(kThreads), 0, s, n, K, G, nbr, nullptr, gidx, nullptr,
+                           nullptr, in_idx, out_idx, cap_pairs);
+        GSC_LAUNCH_CHECK();
+    }
+    return GSC_OK;
 }
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -385,75 +559,27 @@ __global__ void __launch_bounds__(kThreads) k_nbr_count(const int32_t* __restric
 
 template <typename Offs>
 static int kmap_enqueue(const void* in_table, const int32_t* out_coords, int64_t n_out, int ncol, Offs offs, int K,
-                        int sym, int64_t G, int32_t* in_idx, int32_t* out_idx, int64_t cap_pairs, int64_t* seg,
-                        int64_t* gidx, int64_t* n_pairs, int64_t* res, int32_t* cnt, int32_t* nbr, void* scan_ws,
-                        hipStream_t s) {
-    int32_t* not_self = reinterpret_cast<int32_t*>(res + 2);
+                        int64_t G, int32_t* in_idx, int32_t* out_idx, int64_t cap_pairs, int64_t* seg, int64_t* gidx,
+                        int64_t* n_pairs, int64_t* res, int32_t* cnt, int32_t* nbr, void* scan_ws, hipStream_t s) {
     const unsigned nblk = (unsigned)((n_out + kThreads - 1) / kThreads);
     if (nblk > 0) {
-        if (sym && K > 1) {   // whether the map is a self map is read from the table on the device
-            const int64_t n_init = (int64_t)(K / 2) * n_out;
-            const int64_t gi = (n_init + kThreads - 1) / kThreads;
-            hipLaunchKernelGGL(k_kmap_self_init, dim3((unsigned)(gi < 4096 ? (gi > 0 ? gi : 1) : 4096)), dim3(kThreads), 0,
-                               s, in_table, n_out, ncol, K, sym, nbr, not_self);
-            GSC_LAUNCH_CHECK();
-        }
-        // the wide batch while every row's wave fits at once (two waves per SIMD)
-        const bool small = n_out <= (int64_t)device_cus() * 4 * 2 * 64;
-        if (small)
-            hipLaunchKernelGGL((k_kmap_count<Offs, kBatchSmall>), dim3(nblk), dim3(kThreads), 0, s, in_table,
-                               out_coords, n_out, ncol, offs, K, sym, G, cnt, nbr, res + 1, not_self);
-        else
-            hipLaunchKernelGGL((k_kmap_count<Offs, kBatch>), dim3(nblk), dim3(kThreads), 0, s, in_table, out_coords,
-                               n_out, ncol, offs, K, sym, G, cnt, nbr, res + 1, not_self);
-        GSC_LAUNCH_CHECK();
-        if (sym && K > 1) {
-            if (small)
-                hipLaunchKernelGGL((k_kmap_mirror_count<Offs, kBatchSmall>), dim3(nblk), dim3(kThreads), 0, s,
-                                   in_table, out_coords, n_out, ncol, offs, K, sym, G, nbr, cnt, not_self);
-            else
-                hipLaunchKernelGGL((k_kmap_mirror_count<Offs, kBatch>), dim3(nblk), dim3(kThreads), 0, s, in_table,
-                                   out_coords, n_out, ncol, offs, K, sym, G, nbr, cnt, not_self);
-            GSC_LAUNCH_CHECK();
-        }
-    }
-    // the scan also writes seg[k] = gidx[k * G] (a launch of its own without groups)
-    int rc = G > 0 ? scan_counts(cnt, K * G, gidx, res, scan_ws, s, seg, G)
-                   : scan_counts(cnt, 0, gidx, res, scan_ws, s);
-    if (rc) return rc;
-    if (G == 0) {
-        rc = seg_from_gidx(gidx, K, G, seg, s);
-        if (rc) return rc;
-    }
-    int64_t bound = cap_pairs;
-    if (n_pairs) {
-        int64_t hres[2];
-        GSC_HIP(hipMemcpyAsync(hres, res, sizeof(hres), hipMemcpyDeviceToHost, s));
-        GSC_HIP(hipStreamSynchronize(s));
-        // the count kernel (launched when n_out > 0) writes the header check
-        if (nblk > 0 && hres[1])
-            return fail(GSC_EINVAL, "kernel_map: in_table is not a valid table of %d-column rows", ncol);
-        *n_pairs = hres[0];
-        if (hres[0] > cap_pairs)
-            return fail(GSC_ESHORT, "kernel_map: %lld pairs exceed cap_pairs=%lld", (long long)hres[0],
-                        (long long)cap_pairs);
-        bound = hres[0];
-    }
-    if (nblk > 0 && bound > 0) {
-        hipLaunchKernelGGL(k_kmap_fill, dim3(nblk), dim3(kThreads), 0, s, n_out, K, G, nbr, gidx, in_idx, out_idx,
-                           cap_pairs);
+        const bool vec = ncol == 4 && ((uintptr_t)out_coords & 15) == 0;   // rows as 16-byte words
+        // a multiple of the XCDs, so that the blocks of one row range and all offsets share an L2
+        const unsigned gx = (nblk + kNumXcd - 1) / kNumXcd * kNumXcd;
+        const unsigned gy = (unsigned)((K + kGridBatch - 1) / kGridBatch);
+        hipLaunchKernelGGL(k_kmap_count<Offs>, dim3(gx, gy), dim3(kThreads), 0, s, offs, in_table, out_coords, vec,
+                           n_out, ncol, K, G, cnt, nbr, res + 1);
         GSC_LAUNCH_CHECK();
     }
-    return GSC_OK;
+    return pairs_enqueue(n_out, K, G, nbr, cnt, gidx, seg, res, scan_ws, in_idx, out_idx, cap_pairs, n_pairs, ncol, s);
 }
 
 // Host-side checks and the offsets scaled by the tensor stride (by value in
-// `arg` when K * D <= kOffArgMax, always in `offs`); sym = the listing is
-// symmetric (K odd, o_{K-1-k} = -o_k, the origin in the middle).
+// `arg` when K * D <= kOffArgMax, always in `offs`).
 static int kmap_prepare(const void* in_table, const int32_t* out_coords, int64_t n_out, int32_t D,
                         const int32_t* offsets, int32_t K, const int32_t* tensor_stride, int32_t* in_idx,
                         int32_t* out_idx, int64_t cap_pairs, int64_t* seg, int64_t* gidx, int64_t* n_pairs,
-                        OffsArg& arg, std::vector<int32_t>& offs, int& sym) {
+                        OffsArg& arg, std::vector<int32_t>& offs) {
     if (D < 1 || D + 1 > kMaxCols) return fail(GSC_EINVAL, "kernel_map: D=%d outside [1,%d]", D, kMaxCols - 1);
     if (K < 1) return fail(GSC_EINVAL, "kernel_map: K=%d must be >= 1", K);
     if (n_out < 0 || n_out > INT32_MAX) return fail(GSC_EINVAL, "kernel_map: n_out=%lld invalid", (long long)n_out);
@@ -470,12 +596,6 @@ static int kmap_prepare(const void* in_table, const int32_t* out_coords, int64_t
             return fail(GSC_EINVAL, "kernel_map: asynchronous mode needs K*D <= %d (got %d)", kOffArgMax, K * D);
     }
     offs.assign((size_t)K * D, 0);
-    sym = K % 2 == 1 ? 1 : 0;
-    for (int k = 0; k < K && sym; ++k)
-        for (int d = 0; d < D; ++d) {
-            const int32_t a = offsets[(size_t)k * D + d], b = offsets[(size_t)(K - 1 - k) * D + d];
-            if ((int64_t)a != -(int64_t)b) sym = 0;
-        }
     for (int k = 0; k < K; ++k)
         for (int d = 0; d < D; ++d) {
             const int64_t ts = tensor_stride ? tensor_stride[d] : 1;
@@ -528,7 +648,7 @@ size_t gsc_kmap_ws_bytes(int64_t n_out, int32_t K, int32_t D) {
     if (n_out < 0 || K < 1 || D < 1) return 0;
     const int64_t G = gsc_kmap_groups(n_out);
     size_t b = align256((size_t)K * D * sizeof(int32_t));      // offsets (scaled)
-    b += align256(3 * sizeof(int64_t));                         // total, error flag, self-map check
+    b += align256(3 * sizeof(int64_t));                         // total, error flag
     b += align256((size_t)K * G * sizeof(int32_t));             // counts
     b += align256((size_t)K * n_out * sizeof(int32_t));         // neighbour table
     b += scan_ws_bytes(K * G);
@@ -545,9 +665,8 @@ int gsc_kernel_map(const void* in_table, const int32_t* out_coords, int64_t n_ou
         return fail(GSC_ESHORT, "kernel_map: ws needs %zu bytes, got %zu", gsc_kmap_ws_bytes(n_out, K, D), ws_bytes);
     OffsArg arg;
     std::vector<int32_t> offs;
-    int sym = 0;
     int rc = kmap_prepare(in_table, out_coords, n_out, D, offsets, K, tensor_stride, in_idx, out_idx, cap_pairs, seg,
-                          gidx, n_pairs, arg, offs, sym);
+                          gidx, n_pairs, arg, offs);
     if (rc) return rc;
     const bool by_value = (int64_t)K * D <= kOffArgMax;
 
@@ -557,7 +676,7 @@ int gsc_kernel_map(const void* in_table, const int32_t* out_coords, int64_t n_ou
     char* w = reinterpret_cast<char*>(ws);
     int32_t* d_offs = reinterpret_cast<int32_t*>(w);
     w += align256((size_t)K * D * sizeof(int32_t));
-    int64_t* res = reinterpret_cast<int64_t*>(w);   // res[0] = total, res[1] = header error, res[2] = self check
+    int64_t* res = reinterpret_cast<int64_t*>(w);   // res[0] = total, res[1] = header error
     w += align256(3 * sizeof(int64_t));
     int32_t* cnt = reinterpret_cast<int32_t*>(w);
     w += align256((size_t)K * G * sizeof(int32_t));
@@ -565,11 +684,11 @@ int gsc_kernel_map(const void* in_table, const int32_t* out_coords, int64_t n_ou
     w += align256((size_t)K * n_out * sizeof(int32_t));
     void* scan_ws = w;
     if (by_value)
-        return kmap_enqueue(in_table, out_coords, n_out, ncol, arg, K, sym, G, in_idx, out_idx, cap_pairs, seg, gidx,
+        return kmap_enqueue(in_table, out_coords, n_out, ncol, arg, K, G, in_idx, out_idx, cap_pairs, seg, gidx,
                             n_pairs, res, cnt, nbr, scan_ws, s);
     // synchronous mode: the copy below completes before this call returns
     GSC_HIP(hipMemcpyAsync(d_offs, offs.data(), offs.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    return kmap_enqueue(in_table, out_coords, n_out, ncol, OffsPtr{d_offs}, K, sym, G, in_idx, out_idx, cap_pairs,
+    return kmap_enqueue(in_table, out_coords, n_out, ncol, OffsPtr{d_offs}, K, G, in_idx, out_idx, cap_pairs,
                         seg, gidx, n_pairs, res, cnt, nbr, scan_ws, s);
 }
 
@@ -592,9 +711,8 @@ int gsc_kernel_map_noalloc(const void* in_table, const int32_t* out_coords, int6
                     (long long)n_out, K);
     OffsArg arg;
     std::vector<int32_t> offs;
-    int sym = 0;
     int rc = kmap_prepare(in_table, out_coords, n_out, D, offsets, K, tensor_stride, in_idx, out_idx, cap_pairs, seg,
-                          gidx, nullptr, arg, offs, sym);
+                          gidx, nullptr, arg, offs);
     if (rc) return rc;
     char* w = nullptr;
     rc = noalloc_scratch(&w);
@@ -605,7 +723,7 @@ int gsc_kernel_map_noalloc(const void* in_table, const int32_t* out_coords, int6
     w += align256(3 * sizeof(int64_t));
     int32_t* cnt = reinterpret_cast<int32_t*>(w);
     w += align256((size_t)K * G * sizeof(int32_t));
-    return kmap_enqueue(in_table, out_coords, n_out, D + 1, arg, K, sym, G, in_idx, out_idx, cap_pairs, seg, gidx,
+    return kmap_enqueue(in_table, out_coords, n_out, D + 1, arg, K, G, in_idx, out_idx, cap_pairs, seg, gidx,
                         nullptr, res, cnt, nbr, w, s);
 }
 
@@ -652,19 +770,8 @@ int gsc_kernel_map_transpose(const int32_t* in_idx, const int32_t* out_idx, cons
         hipLaunchKernelGGL(k_nbr_count, dim3(nblk), dim3(kThreads), 0, s, t_nbr, n_rev, K, G, cnt);
         GSC_LAUNCH_CHECK();
     }
-    int rc = G > 0 ? scan_counts(cnt, K * G, t_gidx, nullptr, w, s, t_seg, G)
-                   : scan_counts(cnt, 0, t_gidx, nullptr, w, s);
-    if (rc) return rc;
-    if (G == 0) {
-        rc = seg_from_gidx(t_gidx, K, G, t_seg, s);
-        if (rc) return rc;
-    }
-    if (nblk > 0 && cap_pairs > 0) {
-        hipLaunchKernelGGL(k_kmap_fill, dim3(nblk), dim3(kThreads), 0, s, n_rev, K, G, t_nbr, t_gidx, t_in_idx,
-                           t_out_idx, cap_pairs);
-        GSC_LAUNCH_CHECK();
-    }
-    return GSC_OK;
+    return pairs_enqueue(n_rev, K, G, t_nbr, cnt, t_gidx, t_seg, nullptr, w, t_in_idx, t_out_idx, cap_pairs, nullptr,
+                         0, s);
 }
 
 int gsc_kernel_map_transpose_status(const void* ws, void* stream) {

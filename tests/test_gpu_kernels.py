@@ -51,3 +51,176 @@ def test_affine_act_bwd_shapes(dtype, n, c, shift):
         assert torch.isfinite(ds[1]).item() != counts
     again = gsc.gsc_affine_act_bwd(Y, dY, scale, sh, relu=True)
     assert torch.equal(again[1].nan_to_num(7.0), ds.nan_to_num(7.0)) and torch.equal(again[2], dt)
+
+
+# --------------------------------------------------------------------------- #
+# the two forms of a coordinate table: grid and hashed slots
+# --------------------------------------------------------------------------- #
+def _pairs(src, dst, offs):
+    """(input row, output row) per offset from a dict of rows."""
+    at = {tuple(r): i for i, r in enumerate(src.tolist())}
+    out = []
+    for o in np.asarray(offs).tolist():
+        hit = [(at.get((r[0],) + tuple(a + b for a, b in zip(r[1:], o))), j) for j, r in enumerate(dst.tolist())]
+        out.append([(i, j) for i, j in hit if i is not None])
+    return out
+
+
+def _rows(seed, n, D, span, step=1, lo=-7, batch=2):
+    rng = np.random.default_rng(seed)
+    r = np.concatenate([rng.integers(0, batch, (4 * n, 1)), lo + step * rng.integers(0, span, (4 * n, D))], 1)
+    r = np.unique(r, axis=0)
+    return np.ascontiguousarray(rng.permutation(r)[:n].astype(np.int32))
+
+
+GRID_ROWS = {
+    "one_row": np.array([[3, -5, 7, 11]], np.int32),
+    "line_1d": _rows(1, 130, 1, 400),
+    "plane_2d": _rows(2, 257, 2, 40),
+    "sparse_3d": _rows(3, 1025, 3, 40),
+    "step2_3d": _rows(4, 700, 3, 20, step=2, lo=-8),
+    "step4_wide_3d": _rows(5, 333, 3, 30, step=4, lo=1 << 28),
+    "video_4d": _rows(6, 500, 4, 9),
+    "sorted_run": np.array([[0, 0, y, z] for y in range(3) for z in range(70)], np.int32),
+    "low_end": np.array([[0, -2**31, 0, 0], [0, -2**31 + 1, 0, 1], [1, -2**31, 1, 0]], np.int32),
+    "split_box": np.array([[0, -2**29, 0, 0], [0, 2**29, 0, 0], [0, 2**29, 0, 1]], np.int32),   # hashed: too wide
+    "five_5d": _rows(7, 200, 5, 4),
+    "seven_7d": _rows(8, 300, 7, 3),
+    # past the rows that one block builds a table of
+    "block_3d": _rows(9, 3072, 3, 40),
+    "past_block_3d": _rows(10, 3073, 3, 40),
+    "big_line_1d": _rows(11, 5000, 1, 9000),
+    "big_step2_3d": _rows(12, 4100, 3, 30, step=2, lo=-8),
+    "big_video_4d": _rows(13, 3500, 4, 10),
+    "big_wide_3d": _rows(14, 4000, 3, 900, step=4, lo=1 << 28),   # hashed: too many cells
+    "big_seven_7d": _rows(15, 3300, 7, 4),
+}
+
+
+@pytest.mark.parametrize("form", ["any", "hash"])
+@pytest.mark.parametrize("name", sorted(GRID_ROWS))
+def test_table_forms(name, form, monkeypatch):
+    """Kernel maps onto the rows themselves (cube 3, and cube 3 at twice the
+    step), onto other rows (some far outside the box) and strided rows, from
+    the form that the box gives and from hashed slots, against a dict."""
+    from paper_1904_08755_amd import gsc, regions
+    if form == "hash":
+        monkeypatch.setenv("GSC_TABLE_CAP_LIMIT", str(1 << 40))
+    host = GRID_ROWS[name]
+    D = host.shape[1] - 1
+    c = torch.from_numpy(host).to(DEV)
+    table = gsc.gsc_coords_build(c)
+    offs = regions.hypercube(3, D) if D <= 4 else regions.hypercross(3, D)
+    step = 4 if "step4" in name else (2 if "step2" in name else 1)
+    rng = np.random.default_rng(11)
+    other = host[rng.integers(0, len(host), 90)].astype(np.int64)
+    other[:, 1:] += rng.integers(-3, 4, other[:, 1:].shape)
+    far = np.array([[0] + [2**31 - 1] * D, [0] + [-2**31] * D, [-2**31] + [0] * D, [2**31 - 1] + [0] * D])
+    other = np.concatenate([other.clip(-2**31, 2**31 - 1), far]).astype(np.int32)
+    for dst, ts in ((host, 1), (host, step), (host[::-1].copy(), step), (other, 1)):
+        km = gsc.gsc_kernel_map(table, torch.from_numpy(dst).to(DEV), offs, tensor_stride=ts, dense=True)
+        seg = km.seg.cpu().numpy()
+        got_i, got_o, nbr = km.in_idx.cpu().numpy(), km.out_idx.cpu().numpy(), km.nbr.cpu().numpy()
+        gidx = km.gidx.cpu().numpy()
+        G = gsc.gsc_kmap_groups(len(dst))
+        for k, pairs in enumerate(_pairs(host.astype(np.int64), dst.astype(np.int64), offs.astype(np.int64) * ts)):
+            i, o = got_i[seg[k]:seg[k + 1]], got_o[seg[k]:seg[k + 1]]
+            assert list(zip(i.tolist(), o.tolist())) == pairs, (name, k)
+            dense = np.full(len(dst), -1)
+            dense[o] = i
+            assert (nbr[k] == dense).all()
+            assert (gidx[k * G:(k + 1) * G] == seg[k] + np.searchsorted(o, 64 * np.arange(G))).all()
+        assert gidx[-1] == seg[-1] == km.n_pairs
+    if name in ("low_end", "split_box"):   # a strided value may leave int32 there
+        return
+    for s in (2, 3):
+        out, out_table = gsc.gsc_coords_stride(c, s)
+        want = host.astype(np.int64).copy()
+        want[:, 1:] = want[:, 1:] // s * s
+        seen = list(dict.fromkeys(tuple(r) for r in want.tolist()))
+        assert [tuple(r) for r in out.cpu().tolist()] == seen
+        up = gsc.gsc_kernel_map(out_table, out, np.zeros((1, D), np.int32))
+        assert up.in_idx.cpu().tolist() == list(range(len(seen)))
+
+
+@pytest.mark.parametrize("form", ["any", "hash"])
+def test_table_forms_duplicates(form, monkeypatch):
+    from paper_1904_08755_amd import gsc
+    if form == "hash":
+        monkeypatch.setenv("GSC_TABLE_CAP_LIMIT", str(1 << 40))
+    c = torch.from_numpy(np.concatenate([GRID_ROWS["sparse_3d"], GRID_ROWS["sparse_3d"][500:501]])).to(DEV)
+    with pytest.raises(gsc.GscError) as e:
+        gsc.gsc_coords_build(c)
+    assert e.value.code == gsc.GSC_EDUP
+
+
+def test_grid_limit_of_cells():
+    """Boxes on both sides of the most cells a grid may have (64 KiB of words
+    for few rows): the same map."""
+    from paper_1904_08755_amd import gsc, regions
+    for n in (1200, 6000):
+        for z in (170, 174, 178, 300):   # 1200 rows: room for 262,144 cells; 6000: 192 cells a row
+            side = 39 if n == 1200 else 81
+            rng = np.random.default_rng(z)
+            flat = np.unique(np.concatenate([rng.choice(side * side * z, n), [0, side * side * z - 1]]))
+            host = np.stack([0 * flat, flat // (side * z), flat // z % side, flat % z], 1).astype(np.int32)
+            c = torch.from_numpy(host).to(DEV)
+            km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, regions.hypercube(3, 3))
+            seg, i, o = km.seg.cpu().numpy(), km.in_idx.cpu().numpy(), km.out_idx.cpu().numpy()
+            for k, pairs in enumerate(_pairs(host, host, regions.hypercube(3, 3))):
+                assert list(zip(i[seg[k]:seg[k + 1]].tolist(), o[seg[k]:seg[k + 1]].tolist())) == pairs
+
+
+@pytest.mark.parametrize("n,K", [(300, 2187), (300, 1024), (64 * 65536, 2), (64 * 65536 + 1, 2)])
+def test_kernel_map_scan_limits(n, K):
+    """Offsets and groups on both sides of the limits of the per-offset scan:
+    rows on a line, offsets along it, so offset s pairs row j with j + s."""
+    from paper_1904_08755_amd import gsc
+    x = torch.arange(n, dtype=torch.int32, device=DEV)
+    c = torch.stack([torch.zeros_like(x), x], 1).contiguous()
+    o = np.arange(K)[:, None].astype(np.int32) * (1 if K > 2 else 70001)
+    km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, o)
+    seg = np.concatenate([[0], np.cumsum(np.maximum(n - o[:, 0].astype(np.int64), 0))])
+    assert (km.seg.cpu().numpy() == seg).all() and km.n_pairs == seg[-1]
+    want_o = torch.cat([x[:max(n - int(s), 0)] for s in o[:, 0]])
+    want_i = torch.cat([x[int(s):] for s in o[:, 0]])
+    assert torch.equal(km.out_idx, want_o) and torch.equal(km.in_idx, want_i)
+    G = gsc.gsc_kmap_groups(n)
+    k = K - 1
+    assert km.gidx[k * G].item() == seg[k] and km.gidx[-1].item() == seg[-1]
+    assert km.gidx[(k - 1) * G + G // 2].item() == seg[k - 1] + min(64 * (G // 2), seg[k] - seg[k - 1])
+    if n > 1000:
+        with pytest.raises(gsc.GscError) as e:
+            gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, o, cap_pairs=int(seg[-1]) - 1)
+        assert e.value.code == gsc.GSC_ESHORT
+
+
+@pytest.mark.parametrize("form", ["any", "hash"])
+@pytest.mark.parametrize("n", [1, 200, 3072, 3073, 9000])
+def test_quantize_sizes(n, form, monkeypatch):
+    """Voxels, first points, labels and the inverse map by numpy, on both sides
+    of the points that one block takes; unsorted points."""
+    from paper_1904_08755_amd import gsc
+    if form == "hash":
+        monkeypatch.setenv("GSC_TABLE_CAP_LIMIT", str(1 << 40))
+    rng = np.random.default_rng(n)
+    pts = (rng.integers(-40, 41, (n, 3)) * 0.125 + 0.0625).astype(np.float32)   # exact quotients at 0.25
+    batch = rng.integers(0, 3, n).astype(np.int32)
+    labels = rng.integers(0, 2, n).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).to(DEV)
+    q = gsc.gsc_quantize(dev(pts), 0.25, dev(batch), dev(labels), ignore_label=-7)
+    rows = np.concatenate([batch[:, None], np.floor(pts / np.float32(0.25)).astype(np.int32)], 1)
+    first, inverse = {}, []
+    for i, r in enumerate(map(tuple, rows.tolist())):
+        inverse.append(first.setdefault(r, (len(first), i))[0])
+    rep = [i for _, i in first.values()]
+    same = [set() for _ in first]
+    for i, v in enumerate(inverse):
+        same[v].add(int(labels[i]))
+    assert q.coords.cpu().tolist() == [list(r) for r in first]
+    assert q.rep.cpu().tolist() == rep and q.inverse.cpu().tolist() == inverse
+    assert q.labels.cpu().tolist() == [s.pop() if len(s) == 1 else -7 for s in same]
+    km = gsc.gsc_kernel_map(q.table, q.coords, np.zeros((1, 3), np.int32))
+    assert km.in_idx.cpu().tolist() == list(range(len(first)))
+    q2 = gsc.gsc_quantize(dev(pts), 0.25, dev(batch))
+    assert torch.equal(q2.coords, q.coords) and torch.equal(q2.inverse, q.inverse) and q2.labels is None
