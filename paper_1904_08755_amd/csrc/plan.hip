@@ -26,13 +26,16 @@
 //                16b + r at offset k, or -1 if there is none.
 // Input: the map's dense form nbr[k][j] (input row or -1), which the kernel
 // map writes as it probes.  Steps:
-//   masks:  every row's mask from its column of nbr;
+//   masks:  every row's mask from its column of nbr, its sort key, and the
+//           digit counts of every kMaskRows rows;
+//   counts: the digit counts' totals, and their prefixes over the row groups
+//           (where the first pass's tiles place their keys);
 //   sort:   stable LSD radix sort of (key, row) by key = (min(popcount of
 //           the mask, cap) << K) | mask, 10-bit digits, one kernel per digit
 //           (cap: plan_key_cap);
-//   count:  block unions and item counts; a scan gives ibase;
-//   fill:   one lane per position writes its entry of each of its block's
-//           items.
+//   count:  block unions and item counts, scanned within kBlkTile blocks;
+//   fill:   the item bases, and one lane per position writes its entry of each
+//           of its block's items.
 // Everything is deterministic and runs without a host round trip.
 #include <algorithm>
 #include <climits>
@@ -46,8 +49,17 @@ constexpr int kPlanThreads = 256;
 constexpr int kRsBits = 10;                       // radix digit width
 constexpr int kRsBins = 1 << kRsBits;
 constexpr int kRsThreads = 1024;                  // radix sort block
-constexpr int kRsPer = 2;                         // keys per thread and block (2048-key tiles: more tiles in flight)
-constexpr int kRsTile = kRsThreads * kRsPer;      // keys per block
+// Keys per thread: 2 in the first pass, whose tiles do not wait for each other
+// (300,000 keys: 7.4 us against 9.1 with 4), and in later passes 4 from
+// kRsWideKeys keys on, where the look-back over half as many tiles outweighs a
+// tile's longer work (300,000 keys: 16.7 us against 18.2; 40,000 keys: 11.6
+// against 10.4).
+constexpr int kRsPer = 2, kRsPerWide = 4;
+constexpr int64_t kRsWideKeys = 100000;
+constexpr int kRsTile = kRsThreads * kRsPer;      // keys per block of the first pass
+constexpr int kRsMaxPasses = 4;                   // keys of up to 40 bits
+constexpr int kMaskRows = 1024;                   // rows (and threads) of a block of the mask kernel
+static_assert(kRsTile % kMaskRows == 0, "a sort tile is a whole number of counted row groups");
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -70,162 +82,206 @@ __host__ __device__ inline uint32_t range_kmask(int kr) { return kr >= 32 ? ~0u 
 // ---------------------------------------------------------------------------
 // masks from the dense map
 // ---------------------------------------------------------------------------
-// Range r = blockIdx.y of the plan: keys[r * n + j] for its offsets.  (Also
-// clears the sort's counters and first look-back entries, zero[0, nzero),
-// which the histogram kernel after it starts to fill.)
-__global__ void __launch_bounds__(kPlanThreads) k_plan_masks(const int32_t* __restrict__ nbr, int64_t n, int Kall,
-                                                             int S, uint32_t* __restrict__ keys,
-                                                             uint32_t* __restrict__ zero, int64_t nzero,
-                                                             uint32_t* __restrict__ lb_status) {
+// Range r = blockIdx.y of the plan: keys[r * n + j] for its offsets, and how
+// many of the block's keys have each digit of each pass: cnt[((r * passes + p)
+// * nm + block) * kRsBins + digit].  (Also clears the sort's tickets and
+// look-back entries, zero[0, nzero).)  Bound: nbr read once; B loads in flight
+// per lane.
+__global__ void __launch_bounds__(kMaskRows) k_plan_masks(const int32_t* __restrict__ nbr, int64_t n, int Kall, int S,
+                                                          int passes, uint32_t* __restrict__ keys,
+                                                          uint16_t* __restrict__ cnt, uint32_t* __restrict__ zero,
+                                                          int64_t nzero, uint32_t* __restrict__ lb_status) {
+    __shared__ uint32_t hist[kRsMaxPasses * kRsBins];
+    const int t = threadIdx.x;
     const int64_t lin = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;   // block number over all ranges
-    if (lb_status && lin == 0 && threadIdx.x == 0) *lb_status = 0u;     // the plan call's first kernel
-    for (int64_t i = lin * kPlanThreads + threadIdx.x; i < nzero; i += (int64_t)gridDim.x * gridDim.y * kPlanThreads)
-        zero[i] = 0;
+    if (lb_status && lin == 0 && t == 0) *lb_status = 0u;               // the plan call's first kernel
+    for (int64_t i = lin * kMaskRows + t; i < nzero; i += (int64_t)gridDim.x * gridDim.y * kMaskRows) zero[i] = 0;
+    for (int i = t; i < passes * kRsBins; i += kMaskRows) hist[i] = 0;
     const int rg = blockIdx.y;
     const int K = range_len(rg, S, Kall);
     const uint32_t cap = plan_key_cap(K);
     nbr += (int64_t)range_k0(rg, S) * n;
     keys += (int64_t)rg * n;
-    const int64_t j = (int64_t)blockIdx.x * kPlanThreads + threadIdx.x;
-    if (j >= n) return;
+    const int64_t j = (int64_t)blockIdx.x * kMaskRows + t;
+    const bool valid = j < n;
+    const int64_t jj = valid ? j : n - 1;
     uint32_t m = 0;
-    constexpr int B = 8;   // table entries loaded together
+    constexpr int B = 9;   // table entries loaded together (a divisor of 27)
     for (int k0 = 0; k0 < K; k0 += B) {
         int32_t r[B];
 #pragma unroll
-        for (int b = 0; b < B; ++b) r[b] = k0 + b < K ? nbr[(int64_t)(k0 + b) * n + j] : -1;
+        for (int b = 0; b < B; ++b) r[b] = nbr[(int64_t)min(k0 + b, K - 1) * n + jj];
 #pragma unroll
-        for (int b = 0; b < B; ++b) m |= (uint32_t)(r[b] >= 0) << ((k0 + b) & 31);
+        for (int b = 0; b < B; ++b) m |= (uint32_t)(k0 + b < K && r[b] >= 0) << ((k0 + b) & 31);
     }
     const uint32_t c = min((uint32_t)__popc(m), cap);
-    keys[j] = cap ? m | (c << K) : m;   // cap > 0 only where K + its bits <= 32
+    const uint32_t key = cap ? m | (c << K) : m;   // cap > 0 only where K + its bits <= 32
+    if (valid) keys[j] = key;
+    __syncthreads();   // hist is clear
+    if (valid)
+        for (int p = 0; p < passes; ++p) atomicAdd(&hist[p * kRsBins + ((key >> (p * kRsBits)) & (kRsBins - 1))], 1u);
+    __syncthreads();
+    const int64_t nm = gridDim.x;
+    for (int i = t; i < passes * kRsBins; i += kMaskRows)
+        cnt[(((int64_t)rg * passes + i / kRsBins) * nm + blockIdx.x) * kRsBins + i % kRsBins] = (uint16_t)hist[i];
 }
 
 // ---------------------------------------------------------------------------
 // stable LSD radix sort of (key, value) by key, one kernel per pass
 // ---------------------------------------------------------------------------
-// The digit counts of every pass over all keys come first (one histogram
-// kernel); each tile of a pass scans its pass's counts to know where each
-// digit's range starts.  A pass kernel
-// takes tiles of kRsTile keys in ticket order (an atomic counter, so every
-// tile a block waits for is already running), publishes its tile's count of
-// each digit and looks back over the earlier tiles' published counts to find
-// how many keys with that digit precede the tile (the decoupled look-back
-// of Merrill and Garland's single-pass prefix scan: a tile's entry holds
-// either its own count or, once known, its inclusive prefix).  The keys are then placed stably: in rounds of kRsThreads keys in
-// index order, lanes with equal digits found with kRsBits ballots.
-constexpr int kRsMaxPasses = 4;                   // keys of up to 40 bits
+// Block (x, y) = (64 digits, range and pass): the digits' totals over the nm
+// row groups into ghist, and for the first pass, whose keys lie in row order,
+// the exclusive prefix over the groups before each sort tile into pre[(r * nrs
+// + tile) * kRsBins + digit].  16 lanes per digit take a sixteenth of the
+// tiles each.
+constexpr int kCntLanes = 16;
+constexpr int kSub = kRsTile / kMaskRows;   // row groups of a tile
+
+__global__ void __launch_bounds__(64 * kCntLanes) k_rs_counts(const uint16_t* __restrict__ cnt, int64_t nm, int64_t nrs,
+                                                              int passes, uint32_t* __restrict__ ghist,
+                                                              uint32_t* __restrict__ pre) {
+    __shared__ uint32_t part[kCntLanes][64];
+    const int d = blockIdx.x * 64 + (threadIdx.x & 63), lane = threadIdx.x >> 6;
+    const int rg = blockIdx.y / passes, p = blockIdx.y % passes;
+    cnt += (int64_t)blockIdx.y * nm * kRsBins;
+    const int64_t t0 = nrs * lane / kCntLanes, t1 = nrs * (lane + 1) / kCntLanes;
+    uint32_t sum = 0;
+    for (int64_t g = t0 * kSub; g < t1 * kSub; g += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = g + i < t1 * kSub && g + i < nm ? cnt[(g + i) * kRsBins + d] : 0u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum += v[i];
+    }
+    part[lane][threadIdx.x & 63] = sum;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (int i = 0; i < kCntLanes; ++i) {
+        const uint32_t v = part[i][threadIdx.x & 63];
+        if (i < lane) before += v;
+        all += v;
+    }
+    if (lane == 0) ghist[((int64_t)rg * kRsMaxPasses + p) * kRsBins + d] = all;
+    if (p != 0) return;
+    for (int64_t t = t0; t < t1; ++t) {
+        pre[((int64_t)rg * nrs + t) * kRsBins + d] = before;
+#pragma unroll
+        for (int i = 0; i < kSub; ++i) before += t * kSub + i < nm ? cnt[(t * kSub + i) * kRsBins + d] : 0u;
+    }
+}
+
+// A pass takes the keys in tiles of PER per thread.  A wave ranks its own contiguous
+// keys of the tile with a counter per digit of its own (lanes with equal
+// digits found with kRsBits ballots, rounds of 64 keys in index order), so
+// ranking needs no barrier; then the waves' counts are scanned per digit, and
+// a key's place is its digit's start in the pass's output + the keys of that
+// digit in earlier tiles + in earlier waves + its rank.
+//
+// The keys of earlier tiles: known beforehand in the first pass (FIRST:
+// k_rs_counts).  Later passes take tiles in ticket order (an atomic counter, so
+// every tile a block waits for is already running), publish the tile's count
+// of each digit and look back over the earlier tiles' published counts (the
+// decoupled look-back of Merrill and Garland's single-pass prefix scan: a
+// tile's entry holds either its own count or, once known, its inclusive
+// prefix).
+//
+// Bound: latency.  With ranks from block-wide rounds (five barriers and up to
+// 15 counters read per key and round) and the look-back in every pass, 300,000
+// keys took 20.7 us a pass and 40,000 keys 13.3 us.
 constexpr uint32_t kStAgg = 1u << 30;             // entry holds the tile's own count
 constexpr uint32_t kStIncl = 1u << 31;            // entry holds the inclusive prefix
 constexpr uint32_t kStCount = kStAgg - 1;
 constexpr int64_t kRsMaxKeys = kStCount;          // counts must fit below the flag bits
 constexpr int kSpinMax = 1 << 22;                 // bound on polls of one entry (not reached in practice)
 
-// Range r = blockIdx.y: its keys at keys + r * n, its counts at
-// ghist + r * kRsMaxPasses * kRsBins.
-__global__ void __launch_bounds__(kRsThreads) k_rs_ghist(const uint32_t* __restrict__ keys, int64_t n, int passes,
-                                                         uint32_t* __restrict__ ghist) {
-    __shared__ int32_t h[kRsMaxPasses][kRsBins];
-    keys += (int64_t)blockIdx.y * n;
-    ghist += (int64_t)blockIdx.y * kRsMaxPasses * kRsBins;
-    for (int i = threadIdx.x; i < kRsMaxPasses * kRsBins; i += kRsThreads) (&h[0][0])[i] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    uint32_t key[kRsPer];
-#pragma unroll
-    for (int i = 0; i < kRsPer; ++i) {
-        const int64_t idx = base + (int64_t)i * kRsThreads + threadIdx.x;
-        key[i] = idx < n ? keys[idx] : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < kRsPer; ++i) {
-        if (base + (int64_t)i * kRsThreads + threadIdx.x < n)
-            for (int p = 0; p < passes; ++p) atomicAdd(&h[p][(key[i] >> (p * kRsBits)) & (kRsBins - 1)], 1);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < passes * kRsBins; i += kRsThreads) {
-        const int32_t c = (&h[0][0])[i];
-        if (c) atomicAdd(&ghist[i], (uint32_t)c);
-    }
-}
-
 // Tiles of all ranges share the ticket: ticket T is tile T % nrs of range
 // T / nrs, which looks back over its own range's tiles only (all of them
 // took smaller tickets).  Range r's keys and values are at r * n, its look-
-// back entries at r * nrs * kRsBins, its digit counts at r * kRsMaxPasses *
-// kRsBins (ghist points at the pass's row of range 0).
+// back entries (or prefixes) at r * nrs * kRsBins, its digit counts at r *
+// kRsMaxPasses * kRsBins (ghist points at the pass's row of range 0).
+template <bool FIRST, int PER>
 __global__ void __launch_bounds__(kRsThreads) k_rs_pass(const uint32_t* __restrict__ kin,
                                                         const int32_t* __restrict__ vin, int64_t n, int64_t nrs,
-                                                        int R, int shift, const uint32_t* __restrict__ ghist,
-                                                        uint32_t* __restrict__ status,
-                                                        uint32_t* __restrict__ status_next,
-                                                        uint32_t* __restrict__ ticket, uint32_t* __restrict__ kout,
-                                                        int32_t* __restrict__ vout, int spin_max,
-                                                        uint32_t* __restrict__ lb_status) {
+                                                        int shift, const uint32_t* __restrict__ ghist,
+                                                        uint32_t* __restrict__ status, uint32_t* __restrict__ ticket,
+                                                        uint32_t* __restrict__ kout, int32_t* __restrict__ vout,
+                                                        int spin_max, uint32_t* __restrict__ lb_status) {
     constexpr int W = kRsThreads / 64;
-    static_assert(kRsThreads == kRsBins, "one thread per digit in the look-back");
-    __shared__ int64_t start[kRsBins];
-    __shared__ int32_t hist[kRsBins];
-    __shared__ int32_t wcnt[W][kRsBins];
-    __shared__ int64_t tile_sh;
-    __shared__ int64_t wsum[W];
+    static_assert(kRsThreads == kRsBins, "one thread per digit");
+    __shared__ uint32_t start[kRsBins];
+    __shared__ uint16_t wcnt[W][kRsBins];
+    __shared__ uint32_t tile_sh;
+    __shared__ uint32_t wsum[W];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if (tid == 0) tile_sh = atomicAdd(ticket, 1u);
-    hist[tid] = 0;
-    for (int i = tid; i < W * kRsBins; i += kRsThreads) (&wcnt[0][0])[i] = 0;
-    // the pass's digit counts: range 0's load while the ticket is out (a
-    // single-range plan waits for nothing more); a tile of another range
-    // loads its own once the ticket has told it its range
-    int64_t dc = ghist[tid];
-    int64_t rg = 0;   // the tile's range
-    if (R > 1) {      // uniform
-        __syncthreads();
-        rg = (int64_t)tile_sh / nrs;
-        if (rg != 0) dc = ghist[rg * kRsMaxPasses * kRsBins + tid];
-    }
+    if (!FIRST && tid == 0) tile_sh = atomicAdd(ticket, 1u);
+    for (int i = tid; i < W * kRsBins / 2; i += kRsThreads) reinterpret_cast<uint32_t*>(&wcnt[0][0])[i] = 0;
+    __syncthreads();
+    const int64_t T = FIRST ? (int64_t)blockIdx.x : (int64_t)tile_sh;
+    const int64_t rg = T / nrs, t = T - rg * nrs;
     kin += rg * n;
     vout += rg * n;
     kout += rg * n;
-    if (vin) vin += rg * n;
+    if (!FIRST) vin += rg * n;
     status += rg * nrs * kRsBins;
-    status_next += rg * nrs * kRsBins;
-    // where digit tid's keys start in this pass's output (the keys of smaller
-    // digits): every tile scans the pass's digit counts itself
-    int64_t dinc = dc;
+    const uint32_t dc = ghist[rg * kRsMaxPasses * kRsBins + tid];
+    const int64_t base = t * (kRsThreads * PER) + wave * (64 * PER) + lane;
+    uint32_t key[PER];
+    int32_t val[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int64_t idx = base + r * 64;
+        const int64_t ii = idx < n ? idx : 0;
+        key[r] = kin[ii];
+        val[r] = FIRST ? (int32_t)idx : vin[ii];
+    }
+    const uint32_t prefix = FIRST ? status[t * kRsBins + tid] : 0u;
+    // ranks within the wave
+    const unsigned long long below = lanemask_lt();
+    uint32_t rank[PER];
+    uint16_t* mine = wcnt[wave];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const bool valid = base + r * 64 < n;
+        const int d = (int)((key[r] >> shift) & (kRsBins - 1));
+        unsigned long long peers = __ballot(valid);
+#pragma unroll
+        for (int b = 0; b < kRsBits; ++b) {
+            const bool bit = (d >> b) & 1;
+            const unsigned long long m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t seen = mine[d];
+        wave_lds_sync();   // every lane has read its digit's counter
+        rank[r] = seen + (uint32_t)__popcll(peers & below);
+        if (valid && (peers & below) == 0) mine[d] = (uint16_t)(seen + __popcll(peers));
+        wave_lds_sync();
+    }
+    // where digit tid's keys start in this pass's output (the keys of smaller digits)
+    uint32_t dinc = dc;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const int64_t u = __shfl_up(dinc, o, 64);
+        const uint32_t u = __shfl_up(dinc, o, 64);
         if (lane >= o) dinc += u;
     }
     if (lane == 63) wsum[wave] = dinc;
-    __syncthreads();
-    int64_t dbase = dinc - dc;
+    __syncthreads();   // the waves' counts are complete
+    uint32_t dbase = dinc - dc;
     for (int i = 0; i < wave; ++i) dbase += wsum[i];
-    const int64_t t = tile_sh - rg * nrs;   // (visible: a barrier has passed since thread 0 set it)
-    const int64_t base = t * kRsTile;
-    status_next[t * kRsBins + tid] = 0;   // the next pass's entry of this tile (that array is idle now)
-    uint32_t key[kRsPer];
-    int32_t val[kRsPer];
+    uint32_t c = 0;   // digit tid: the waves' counts become exclusive prefixes, the tile's count their sum
 #pragma unroll
-    for (int r = 0; r < kRsPer; ++r) {
-        const int64_t idx = base + (int64_t)r * kRsThreads + tid;
-        const bool valid = idx < n;
-        key[r] = valid ? kin[idx] : 0u;
-        val[r] = valid ? (vin ? vin[idx] : (int32_t)idx) : 0;
+    for (int w = 0; w < W; ++w) {
+        const uint32_t v = wcnt[w][tid];
+        wcnt[w][tid] = (uint16_t)c;
+        c += v;
     }
-#pragma unroll
-    for (int r = 0; r < kRsPer; ++r)
-        if (base + (int64_t)r * kRsThreads + tid < n) atomicAdd(&hist[(key[r] >> shift) & (kRsBins - 1)], 1);
-    __syncthreads();
-    {   // publish this tile's count of digit tid, then look back for the keys before the tile
+    uint32_t before = prefix;
+    if (!FIRST) {   // publish the tile's count of digit tid, then look back for the keys before the tile
         // (the entries are the only data exchanged, so relaxed atomics at
         // agent scope suffice: they go to L2 and every poll sees the latest)
-        const uint32_t c = (uint32_t)hist[tid];
-        uint32_t* mine = status + t * kRsBins + tid;
-        uint32_t before = 0;
-        __hip_atomic_store(mine, (t == 0 ? kStIncl : kStAgg) | c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t* entry = status + t * kRsBins + tid;
+        __hip_atomic_store(entry, (t == 0 ? kStIncl : kStAgg) | c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (t > 0) {
-            constexpr int LW = 4;   // predecessors' entries loaded together (wider batches read more entries past the first inclusive one, and measured slower)
+            constexpr int LW = 4;   // predecessors' entries loaded together
             bool done = false;
             for (int64_t j0 = t - 1; !done && j0 >= 0; j0 -= LW) {
                 uint32_t v[LW];
@@ -252,50 +308,20 @@ __global__ void __launch_bounds__(kRsThreads) k_rs_pass(const uint32_t* __restri
                     done = (x & kStIncl) != 0;
                 }
             }
-            __hip_atomic_store(mine, kStIncl | (before + c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(entry, kStIncl | ((before + c) & kStCount), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        start[tid] = dbase + before;
     }
-    const unsigned long long below = lanemask_lt();
+    start[tid] = dbase + before;
+    __syncthreads();
 #pragma unroll
-    for (int rnd = 0; rnd < kRsPer; ++rnd) {
-        const int64_t idx = base + (int64_t)rnd * kRsThreads + tid;
-        const bool valid = idx < n;
-        const int d = (int)((key[rnd] >> shift) & (kRsBins - 1));
-        unsigned long long peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < kRsBits; ++b) {
-            const bool bit = (d >> b) & 1;
-            const unsigned long long m = __ballot(bit);
-            peers &= bit ? m : ~m;
+    for (int r = 0; r < PER; ++r) {
+        if (base + r * 64 >= n) continue;
+        const int d = (int)((key[r] >> shift) & (kRsBins - 1));
+        const uint32_t pos = start[d] + wcnt[wave][d] + rank[r];
+        if (pos < n) {   // always true for consistent counts; keeps a bad input from writing outside
+            kout[pos] = key[r];
+            vout[pos] = val[r];
         }
-        const int rank = __popcll(peers & below);
-        __syncthreads();   // wcnt is clear, start holds this round's bases
-        if (valid && rank == 0) wcnt[wave][d] = __popcll(peers);
-        __syncthreads();
-        int64_t pos = 0;
-        if (valid) {
-            pos = start[d] + rank;
-            for (int w = 0; w < wave; ++w) pos += wcnt[w][d];
-        }
-        __syncthreads();   // every lane has read start and wcnt
-        if (valid) {
-            if (pos >= 0 && pos < n) {   // always true for consistent counts; keeps a bad input from writing outside
-                kout[pos] = key[rnd];
-                vout[pos] = val[rnd];
-            }
-            if (rank == 0) {   // the lowest wave holding digit d advances start[d] by the round's count
-                int32_t c = 0;
-                bool first = true;
-                for (int w = 0; w < W; ++w) {
-                    c += wcnt[w][d];
-                    if (w < wave) first = first && wcnt[w][d] == 0;
-                }
-                if (first) start[d] += c;
-            }
-        }
-        __syncthreads();   // start updated by the first holders of each digit
-        if (valid && rank == 0) wcnt[wave][d] = 0;
     }
 }
 
@@ -309,40 +335,73 @@ __device__ __forceinline__ uint32_t block_or16(uint32_t v) {
     return v;
 }
 
-// Range r = blockIdx.y (its keys at r * n, its blocks at r * nb).  (The
-// sorted keys are masked to the range's offsets and the rows clamped to
-// [0, n): after a look-back that gave up they need not be what the sort
-// meant, and the plan must still stay inside its arrays.)
-__global__ void __launch_bounds__(kPlanThreads) k_blk_count(const uint32_t* __restrict__ keys, int Kall, int S,
-                                                            int64_t n, int64_t nb, uint32_t* __restrict__ bmask,
-                                                            int32_t* __restrict__ cnt) {
+// A thread per block: its union mask and item count, and the exclusive scan of
+// the counts within the kBlkTile blocks of a workgroup (lpre; the sum to
+// part).  Range r = blockIdx.y (its keys at r * n, its blocks at r * nb, its
+// sums at r * gridDim.x).  (The sorted keys are masked to the range's offsets
+// and the rows clamped to [0, n): after a look-back that gave up they need not
+// be what the sort meant, and the plan must still stay inside its arrays.)
+constexpr int kBlkTile = 256;
+
+__global__ void __launch_bounds__(kBlkTile) k_blk_count(const uint32_t* __restrict__ keys, int Kall, int S, int64_t n,
+                                                        int64_t nb, uint32_t* __restrict__ bmask,
+                                                        int32_t* __restrict__ lpre, int32_t* __restrict__ part) {
+    __shared__ int32_t wsum[kBlkTile / 64];
     const int rg = blockIdx.y;
     const uint32_t kmask = range_kmask(range_len(rg, S, Kall));
     keys += (int64_t)rg * n;
-    bmask += (int64_t)rg * nb;
-    cnt += (int64_t)rg * nb;
-    const int64_t i = (int64_t)blockIdx.x * kPlanThreads + threadIdx.x;
-    const uint32_t u = block_or16(i < n ? keys[i] & kmask : 0u);
-    const int64_t b = i >> 4;
-    if ((threadIdx.x & 15) == 0 && b < nb) {
-        bmask[b] = u;
-        cnt[b] = __popc(u);
+    const int64_t b = (int64_t)blockIdx.x * kBlkTile + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t u = 0;
+    if (b < nb) {
+        uint32_t v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = keys[min(16 * b + i, n - 1)];   // (the last key again past the end)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) u |= v[i];
+        u &= kmask;
+        bmask[(int64_t)rg * nb + b] = u;
     }
+    const int32_t c = __popc(u);
+    int32_t inc = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t x = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += x;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    int32_t before = inc - c, all = 0;
+    for (int i = 0; i < kBlkTile / 64; ++i) {
+        if (i < wave) before += wsum[i];
+        all += wsum[i];
+    }
+    if (b < nb) lpre[(int64_t)rg * nb + b] = before;
+    if (threadIdx.x == 0) part[(int64_t)rg * gridDim.x + blockIdx.x] = all;
 }
 
 // Range r = blockIdx.y: keys and perm at r * n, the range's offsets' dense
 // rows from nbr + k0 * n, ibase at r * (nb + 1), items from items + 16 k0 nb.
+// A workgroup's blocks lie in one tile of k_blk_count's, so it adds up the
+// `parts` sums of the tiles before that one (a load per lane for 65,536
+// blocks) instead of waiting for a scan of all counts (two launches, 10 us).
 __global__ void __launch_bounds__(kPlanThreads) k_blk_fill(const uint32_t* __restrict__ keys, int Kall, int S,
                                                            const int32_t* __restrict__ perm,
                                                            const int32_t* __restrict__ nbr,
-                                                           const int64_t* __restrict__ ibase, int64_t n, int64_t nb,
+                                                           const int32_t* __restrict__ lpre,
+                                                           const int32_t* __restrict__ part, int64_t parts,
+                                                           int64_t* __restrict__ ibase, int64_t n, int64_t nb,
                                                            int32_t* __restrict__ items) {
+    static_assert(kBlkTile * 16 % kPlanThreads == 0, "a workgroup's blocks lie in one counted tile");
+    __shared__ int64_t wsum[kPlanThreads / 64];
     const int rg = blockIdx.y;
     const int k0 = range_k0(rg, S);
     const uint32_t kmask = range_kmask(range_len(rg, S, Kall));
     keys += (int64_t)rg * n;
     perm += (int64_t)rg * n;
     nbr += (int64_t)k0 * n;
+    lpre += (int64_t)rg * nb;
+    part += (int64_t)rg * parts;
     ibase += (int64_t)rg * (nb + 1);
     items += (int64_t)k0 * nb * 16;
     const int64_t i = (int64_t)blockIdx.x * kPlanThreads + threadIdx.x;
@@ -350,11 +409,24 @@ __global__ void __launch_bounds__(kPlanThreads) k_blk_fill(const uint32_t* __res
     const int r = threadIdx.x & 15;
     const bool valid = i < n;
     const uint32_t key = valid ? keys[i] & kmask : 0u;
+    const int32_t pr = valid ? perm[i] : 0;
+    const int32_t lp = b < nb ? lpre[b] : 0;
+    const int64_t tile = (int64_t)blockIdx.x * kPlanThreads / (16 * kBlkTile);
+    int64_t sum = 0;
+    for (int64_t x = threadIdx.x; x < tile; x += kPlanThreads) sum += part[x];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    int64_t base = lp;
+    for (int w = 0; w < kPlanThreads / 64; ++w) base += wsum[w];
     const uint32_t u = block_or16(key);
     if (b >= nb) return;   // whole blocks of 16 lanes leave together
-    const int32_t pr = valid ? perm[i] : 0;
+    if (r == 0) {
+        ibase[b] = base;
+        if (b == nb - 1) ibase[nb] = base + __popc(u);
+    }
     const int64_t row = pr >= 0 && pr < n ? pr : 0;
-    const int64_t base = ibase[b];
     uint32_t m = u;
     // four of the block's offsets per round, their table entries loaded together
     for (int j = 0; m != 0; j += 4) {
@@ -382,24 +454,35 @@ __global__ void k_plan_empty(int64_t* ibase, int R, uint32_t* lb_status) {
     }
 }
 
-// The workspace of a plan over n rows in R ranges: keys and values twice,
-// the zeroed counters (digit counts per range and pass, tickets, the first
-// pass's look-back entries), the second look-back array, block item counts,
-// the scan's scratch.
+static int plan_passes(int S) {
+    // as many passes as for the widest range's mask alone (the popcount field fills spare bits)
+    return (S + plan_key_pbits(S) + kRsBits - 1) / kRsBits;
+}
+
+// The workspace of a plan over n rows in R ranges of S offsets: keys and
+// values twice, the digit counts of the row groups, their totals and the first
+// pass's prefixes, the zeroed words (tickets, later passes' look-back entries),
+// the blocks' item counts scanned within tiles and the tiles' sums.
 struct PlanWs {
     uint32_t *ka, *kb;
     int32_t *va, *vb;
-    uint32_t *ghist, *ticket, *st0, *st1;
-    int64_t nzero;
-    int32_t* cnt;
-    void* scan_ws;
+    uint16_t* mcnt;
+    uint32_t *ghist, *pre, *ticket, *st;
+    int64_t nzero, nm, nrs, nrs_later, parts;   // row groups, tiles of the first and the later passes, block tiles
+    bool wide;                                  // later passes: kRsPerWide keys per thread
+    int32_t *lpre, *part;
     size_t bytes;   // up to here
 };
 
-static PlanWs plan_ws_layout(void* ws, int64_t n, int R) {
+static PlanWs plan_ws_layout(void* ws, int64_t n, int R, int passes) {
     const int64_t nb = (n + 15) / 16;
-    const int64_t nrs = (n + kRsTile - 1) / kRsTile;
     PlanWs L{};
+    L.nm = (n + kMaskRows - 1) / kMaskRows;
+    L.nrs = (n + kRsTile - 1) / kRsTile;
+    L.wide = n >= kRsWideKeys;
+    const int64_t later = L.wide ? kRsThreads * kRsPerWide : kRsTile;
+    L.nrs_later = (n + later - 1) / later;
+    L.parts = (nb + kBlkTile - 1) / kBlkTile;
     char* base = reinterpret_cast<char*>(ws);
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -411,65 +494,64 @@ static PlanWs plan_ws_layout(void* ws, int64_t n, int R) {
     L.kb = reinterpret_cast<uint32_t*>(take((size_t)R * n * sizeof(uint32_t)));
     L.va = reinterpret_cast<int32_t*>(take((size_t)R * n * sizeof(int32_t)));
     L.vb = reinterpret_cast<int32_t*>(take((size_t)R * n * sizeof(int32_t)));
-    L.nzero = (int64_t)R * kRsMaxPasses * kRsBins + kRsMaxPasses + (int64_t)R * nrs * kRsBins;
-    L.ghist = reinterpret_cast<uint32_t*>(take((size_t)L.nzero * sizeof(uint32_t)));
-    L.ticket = L.ghist ? L.ghist + (int64_t)R * kRsMaxPasses * kRsBins : nullptr;
-    L.st0 = L.ticket ? L.ticket + kRsMaxPasses : nullptr;
-    L.st1 = reinterpret_cast<uint32_t*>(take((size_t)R * nrs * kRsBins * sizeof(uint32_t)));
-    L.cnt = reinterpret_cast<int32_t*>(take((size_t)R * nb * sizeof(int32_t)));
-    L.scan_ws = take(scan_ws_bytes(nb));
+    L.mcnt = reinterpret_cast<uint16_t*>(take((size_t)R * passes * L.nm * kRsBins * sizeof(uint16_t)));
+    L.ghist = reinterpret_cast<uint32_t*>(take((size_t)R * kRsMaxPasses * kRsBins * sizeof(uint32_t)));
+    L.pre = reinterpret_cast<uint32_t*>(take((size_t)R * L.nrs * kRsBins * sizeof(uint32_t)));
+    L.nzero = kRsMaxPasses + (int64_t)(passes - 1) * R * L.nrs_later * kRsBins;
+    L.ticket = reinterpret_cast<uint32_t*>(take((size_t)L.nzero * sizeof(uint32_t)));
+    L.st = L.ticket ? L.ticket + kRsMaxPasses : nullptr;
+    L.lpre = reinterpret_cast<int32_t*>(take((size_t)R * nb * sizeof(int32_t)));
+    L.part = reinterpret_cast<int32_t*>(take((size_t)R * L.parts * sizeof(int32_t)));
     L.bytes = o;
     return L;
 }
 
 // All ranges of a plan (R ranges of S offsets, the last one K - (R-1) S)
 // go through one launch per step: the kernels take the range from the
-// grid's second dimension (the radix passes from the tile's ticket), so a
-// map with more than 32 offsets costs the launches of one plan.  The item
-// counts are scanned per range (ibase restarts at 0 in every range).
+// grid's second dimension (the radix passes from the tile's number), so a
+// map with more than 32 offsets costs the launches of one plan.
 // lb_status: the plan call's look-back status word, cleared by the first
 // kernel and set by a pass that gave up.
 static int plan_enqueue(const int32_t* nbr, int64_t n, int K, int R, int S, int32_t* perm, uint32_t* bmask,
                         int64_t* ibase, int32_t* items, void* ws, uint32_t* lb_status, int spin_max, hipStream_t s) {
     const int64_t nb = (n + 15) / 16;
-    const int64_t nrs = (n + kRsTile - 1) / kRsTile;
-    // as many passes as for the widest range's mask alone (the popcount field fills spare bits)
-    const int passes = (S + plan_key_pbits(S) + kRsBits - 1) / kRsBits;
-    const PlanWs L = plan_ws_layout(ws, n, R);
+    const int passes = plan_passes(S);
+    const PlanWs L = plan_ws_layout(ws, n, R, passes);
     if (n == 0) {
         hipLaunchKernelGGL(k_plan_empty, dim3(1), dim3(64), 0, s, ibase, R, lb_status);
         GSC_LAUNCH_CHECK();
         return GSC_OK;
     }
-    const unsigned pblocks = (unsigned)((n + kPlanThreads - 1) / kPlanThreads);
-    hipLaunchKernelGGL(k_plan_masks, dim3(pblocks, (unsigned)R), dim3(kPlanThreads), 0, s, nbr, n, K, S, L.ka, L.ghist,
-                       L.nzero, lb_status);
+    hipLaunchKernelGGL(k_plan_masks, dim3((unsigned)L.nm, (unsigned)R), dim3(kMaskRows), 0, s, nbr, n, K, S, passes,
+                       L.ka, L.mcnt, L.ticket, L.nzero, lb_status);
     GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_rs_ghist, dim3((unsigned)nrs, (unsigned)R), dim3(kRsThreads), 0, s, L.ka, n, passes, L.ghist);
+    hipLaunchKernelGGL(k_rs_counts, dim3(kRsBins / 64, (unsigned)(R * passes)), dim3(64 * kCntLanes), 0, s, L.mcnt, L.nm,
+                       L.nrs, passes, L.ghist, L.pre);
     GSC_LAUNCH_CHECK();
     const uint32_t* kin = L.ka;
     const int32_t* vin = nullptr;
     for (int p = 0; p < passes; ++p) {
         uint32_t* kout = (p & 1) ? L.ka : L.kb;
         int32_t* vout = (p == passes - 1) ? perm : ((p & 1) ? L.va : L.vb);
-        uint32_t* st = (p & 1) ? L.st1 : L.st0;
-        uint32_t* st_next = (p & 1) ? L.st0 : L.st1;
-        hipLaunchKernelGGL(k_rs_pass, dim3((unsigned)(nrs * R)), dim3(kRsThreads), 0, s, kin, vin, n, nrs, R,
-                           p * kRsBits, L.ghist + (int64_t)p * kRsBins, st, st_next, L.ticket + p, kout, vout,
-                           spin_max, lb_status);
+        const uint32_t* gh = L.ghist + (int64_t)p * kRsBins;
+        if (p == 0) {
+            hipLaunchKernelGGL((k_rs_pass<true, kRsPer>), dim3((unsigned)(L.nrs * R)), dim3(kRsThreads), 0, s, kin, vin, n,
+                               L.nrs, 0, gh, L.pre, (uint32_t*)nullptr, kout, vout, spin_max, lb_status);
+        } else {
+            auto* kern = L.wide ? k_rs_pass<false, kRsPerWide> : k_rs_pass<false, kRsPer>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)(L.nrs_later * R)), dim3(kRsThreads), 0, s, kin, vin, n, L.nrs_later,
+                               p * kRsBits, gh, L.st + (int64_t)(p - 1) * R * L.nrs_later * kRsBins, L.ticket + p, kout,
+                               vout, spin_max, lb_status);
+        }
         GSC_LAUNCH_CHECK();
         kin = kout;
         vin = vout;
     }
-    hipLaunchKernelGGL(k_blk_count, dim3(pblocks, (unsigned)R), dim3(kPlanThreads), 0, s, kin, K, S, n, nb, bmask,
-                       L.cnt);
+    hipLaunchKernelGGL(k_blk_count, dim3((unsigned)L.parts, (unsigned)R), dim3(kBlkTile), 0, s, kin, K, S, n, nb, bmask,
+                       L.lpre, L.part);
     GSC_LAUNCH_CHECK();
-    for (int r = 0; r < R; ++r) {
-        const int rc = scan_counts(L.cnt + (int64_t)r * nb, nb, ibase + (int64_t)r * (nb + 1), nullptr, L.scan_ws, s);
-        if (rc) return rc;
-    }
-    hipLaunchKernelGGL(k_blk_fill, dim3(pblocks, (unsigned)R), dim3(kPlanThreads), 0, s, kin, K, S, perm, nbr, ibase,
-                       n, nb, items);
+    hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)((n + kPlanThreads - 1) / kPlanThreads), (unsigned)R),
+                       dim3(kPlanThreads), 0, s, kin, K, S, perm, nbr, L.lpre, L.part, L.parts, ibase, n, nb, items);
     GSC_LAUNCH_CHECK();
     return GSC_OK;
 }
@@ -502,7 +584,7 @@ int32_t gsc_plan_ranges(int32_t K) { return K < 1 || K > kPlanMaxKAll ? 0 : plan
 
 size_t gsc_conv_plan_ws_bytes(int64_t n_out, int32_t K) {
     if (n_out < 0 || n_out > kRsMaxKeys || K < 1 || K > kPlanMaxKAll) return 0;
-    return plan_ws_layout(nullptr, n_out, plan_ranges(K)).bytes + 256;
+    return plan_ws_layout(nullptr, n_out, plan_ranges(K), plan_passes(plan_range_size(K))).bytes + 256;
 }
 
 int gsc_conv_plan(const int32_t* nbr, int64_t n_out, int32_t K, int32_t* perm, uint32_t* bmask, int64_t* ibase,

@@ -224,3 +224,58 @@ def test_quantize_sizes(n, form, monkeypatch):
     assert km.in_idx.cpu().tolist() == list(range(len(first)))
     q2 = gsc.gsc_quantize(dev(pts), 0.25, dev(batch))
     assert torch.equal(q2.coords, q.coords) and torch.equal(q2.inverse, q.inverse) and q2.labels is None
+
+
+# --------------------------------------------------------------------------- #
+# block plans at the edges of the sort's tiles and the counted block tiles
+# --------------------------------------------------------------------------- #
+@pytest.mark.parametrize("K", [1, 8, 10, 11, 27, 32, 81])
+@pytest.mark.parametrize("n", [1, 15, 17, 1023, 1025, 2049, 4097, 16385])
+def test_plan_sizes(n, K):
+    _plan_case(n, K)
+
+
+@pytest.mark.parametrize("n", [98305, 99999, 100000, 102401])   # the later passes' tiles grow at 100,000 rows
+def test_plan_tile_rule(n):
+    _plan_case(n, 27)
+
+
+def _plan_case(n, K):
+    """The plan of a synthetic dense form: row order, block masks, item bases and
+    items, with rows of equal keys in row order (random masks of few values)."""
+    from paper_1904_08755_amd import gsc
+    g = np.random.default_rng(n * 100 + K)
+    has = g.random((K, n)) < g.choice([0.02, 0.5, 0.9], (1, n))
+    nbr = np.where(has, g.integers(0, n, (K, n)), -1).astype(np.int32)
+    km = gsc.KernelMap(None, None, torch.zeros(K + 1, dtype=torch.int64, device=DEV), None, None, n,
+                       np.zeros((K, 3), np.int32), 0, torch.from_numpy(nbr).to(DEV))
+    bufs = gsc.PlanBuffers(n, K, DEV)
+    plan = gsc.gsc_conv_plan(km, bufs).plan
+    gsc.gsc_conv_plan_status(km, bufs)
+    R, nb = gsc.gsc_plan_ranges(K), gsc.gsc_plan_blocks(n)
+    S = -(-K // R)
+    perm, bmask = plan.perm.cpu().numpy(), plan.bmask.cpu().numpy().view(np.uint32)
+    ibase, items = plan.ibase.cpu().numpy(), plan.items.cpu().numpy()
+    for r in range(R):
+        k0, kr = r * S, min(S, K - r * S)
+        mask = (has[k0:k0 + kr].astype(np.int64) << np.arange(kr)[:, None]).sum(0)
+        pbits = min(10 * -(-kr // 10) - kr, 32 - kr, 6)
+        key = np.minimum(has[k0:k0 + kr].sum(0), 2 ** pbits - 1) << kr | mask
+        want = np.argsort(key, kind="stable")
+        assert np.array_equal(perm[r * n:(r + 1) * n], want)
+        pad = np.zeros(nb * 16, np.int64)
+        pad[:n] = mask[want]
+        union = np.bitwise_or.reduce(pad.reshape(nb, 16), 1)
+        assert np.array_equal(bmask[r * nb:(r + 1) * nb], union)
+        base = np.concatenate([[0], np.cumsum([bin(u).count("1") for u in union.tolist()])])
+        assert np.array_equal(ibase[r * (nb + 1):(r + 1) * (nb + 1)], base)
+        got = items[k0 * nb:k0 * nb + base[-1]]
+        rows = np.full(nb * 16, -1)
+        rows[:n] = want
+        at = 0
+        for b, u in enumerate(union.tolist()):
+            for k in range(kr):
+                if u >> k & 1:
+                    blk = rows[16 * b:16 * b + 16]
+                    assert np.array_equal(got[at], np.where(blk >= 0, nbr[k0 + k][blk], -1))
+                    at += 1
