@@ -138,8 +138,8 @@ k_conv_os(const TIn* __restrict__ X, int64_t n_x, const TIn* __restrict__ W, con
 }
 
 // ---------------------------------------------------------------------------
-// fp32 specialisation for reduction width CA and output width CB (multiples of
-// 16, <= 64).  Differences from the generic kernel:
+// fp32 specialisation for reduction width CA and output width CB, one of them 16
+// (the other 16, 32 or 64).  Differences from the generic kernel:
 //   * the (offset, 16-pair group) items of a tile are split into four
 //     contiguous ranges, one per wave, so a wave meets few distinct offsets and
 //     keeps the offset's B fragments (CA/4 x CB/16 floats per lane) in
@@ -359,6 +359,247 @@ k_conv_f32(const float* __restrict__ X, int64_t n_x, const float* __restrict__ W
             const int64_t row = perm ? (int64_t)perm[pos] : pos;
             Y[row * CB + cc] = acc[r * AS + cc];
         }
+    }
+}
+
+// Rows of 32 or 64 channels on both sides.  The kernel above reads an offset's
+// weights (16 KB at 64 x 64) for every 16 pairs, four times what it gathers.
+// Here a workgroup of four waves owns kWideRows output rows and a wave 16 of
+// their columns (with 32 columns, two waves share a column block and take a
+// step's halves in turn): its part of an offset's weights stays in registers
+// while the offset's pairs in the tile go by, kWidePairs a step, so the 16-pair
+// MFMA steps are fuller too (a tile has twice a group's pairs).  The rows are
+// gathered once for the four waves into LDS (double buffered, one barrier a
+// step; the rows of the next three steps are on their way in registers).  A
+// wave adds only to its own columns of the tile's sums in LDS, one offset after
+// another, and the pairs of an offset have distinct rows: no atomics, and an
+// output row's products are added in increasing offset order.
+//
+// 239,878 rows, 1.84 M pairs, 64 x 64 (138 us of MFMA time at the clock the
+// run holds): forward 358 -> 244 us, input gradient 463 -> 263 us, MFMA busy
+// 51 %; 192 or 256 rows a tile leave two or one workgroups per CU (295 us);
+// 32 x 32: 123 -> 94 and 159 -> 104 us, and no shape from 1,571 to 300,082
+// rows was faster on the kernel above.
+constexpr int kWideRows = 2 * GSC_GROUP_ROWS;   // three workgroups per CU (33 KB of sums and 16 KB of rows each)
+constexpr int kWidePairs = 32;                  // pairs of a step
+
+template <int CA, int CB, bool WT, typename Sel, bool EP>
+__global__ void __launch_bounds__(kThreads, 2)
+k_conv_f32_wide(const float* __restrict__ X, int64_t n_x, const float* __restrict__ W, const int32_t* __restrict__ gat,
+                const int32_t* __restrict__ sca, const int64_t* __restrict__ gidx, int K, int64_t G, int64_t n_y,
+                float* __restrict__ Y, Sel sel, Epilogue ep) {
+    constexpr int CW = CB / 16;                      // the waves' column blocks
+    constexpr int HW = 4 / CW;                       // waves of one column block, taking a step's 16-pair halves in turn
+    constexpr int KS = CA / 4;
+    constexpr int CH = CA / 4;                       // 16-byte chunks of a row
+    constexpr int PER = kWidePairs * CH / kThreads;  // chunks a thread gathers per step
+    __shared__ __attribute__((aligned(16))) float acc[(kWideRows + 1) * CB];   // and a row for pairs that are none
+    __shared__ __attribute__((aligned(16))) floatx4 rows[2][kWidePairs * CH];
+    __shared__ __attribute__((aligned(16))) int32_t lrow[2][kWidePairs];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int r16 = lane & 15, q = lane >> 4;
+    const int wc = wave % CW, wh = wave / CW;
+    const int64_t tile = xcd_unit(blockIdx.x, gridDim.x);
+    constexpr int TG = kWideRows / GSC_GROUP_ROWS;
+    const int64_t g0 = tile * TG, g1 = min(g0 + TG, G);
+    const int64_t row0 = tile * kWideRows;
+    for (int i = tid; i < kWideRows * CB / 4; i += kThreads) reinterpret_cast<float4*>(acc)[i] = float4{0.f, 0.f, 0.f, 0.f};
+
+    // the tile's pairs of every offset, one offset per lane (K <= 64)
+    int64_t lo = 0;
+    int np = 0;
+    if (lane < K) {
+        lo = gidx[(int64_t)lane * G + g0];
+        np = (int)(gidx[(int64_t)lane * G + g1] - lo);
+    }
+    // steps in offset order (uniform): offset k, pairs [pb, pb + kWidePairs) of it (k = -1 past the last)
+    unsigned long long left = __ballot(np > 0);
+    unsigned long long wleft = left;   // offsets whose weights have not been asked for
+    if (left) {                        // uniform
+    int fk = -1, fpb = 0, fnp = 0;     // the front of the walk
+    int64_t flo = 0;
+    const auto next_step = [&]() __attribute__((always_inline)) {
+        fpb += kWidePairs;
+        if (fpb >= fnp) {
+            fk = left ? __ffsll((long long)left) - 1 : -1;
+            left &= left - 1;
+            fpb = 0;
+            fnp = 0;
+            flo = 0;
+            if (fk >= 0) {
+                fnp = __builtin_amdgcn_readlane(np, fk);
+                const uint32_t l0 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)lo, fk);
+                const uint32_t l1 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)lo >> 32), fk);
+                flo = (int64_t)(((uint64_t)l1 << 32) | l0);
+            }
+        }
+    };
+    // Thread t gathers chunk t % CH of every RPI-th row of a step.  Steps go through D slots of registers:
+    // a step's rows are loaded D steps ahead, their indices 2 D (with the indices one step ahead of the
+    // rows, every step waited for them: 360 us); every step issues the same loads at valid addresses (pairs past an offset's last repeat it, steps past the end read pair 0).
+    constexpr int RPI = kThreads / CH;   // rows per round of the block
+    constexpr int D = 3;
+    const int mine = tid / CH;           // the thread's row of each round
+    const floatx4* Xc = reinterpret_cast<const floatx4*>(X) + tid % CH;
+    int sk[D], spb[D], snp[D];      // the steps whose rows are loaded
+    int ik[D], ipb[D], inp[D];      // those whose indices are
+    int32_t gr[D][PER], sr[D][PER];
+    floatx4 rv[D][PER];
+    int32_t lr[D][PER];
+    const auto load_idx = [&](auto P) __attribute__((always_inline)) {
+        constexpr int j = decltype(P)::value;
+        next_step();
+        ik[j] = fk;
+        ipb[j] = fpb;
+        inp[j] = fnp;
+        const int32_t *gp = gat + flo, *sp = sca + flo;   // uniform
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const uint32_t p = (uint32_t)max(min(fpb + i * RPI + mine, fnp - 1), 0);
+            gr[j][i] = gp[p];
+            sr[j][i] = sp[p];
+        }
+        return false;
+    };
+    const auto load_rows = [&](auto P) __attribute__((always_inline)) {
+        constexpr int j = decltype(P)::value;
+        sk[j] = ik[j];
+        spb[j] = ipb[j];
+        snp[j] = inp[j];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int32_t g = gr[j][i], o = sr[j][i];
+            const uint32_t at_row = (uint32_t)o - (uint32_t)row0;
+            const bool ok = (spb[j] + i * RPI + mine < snp[j]) & ((uint32_t)g < (uint32_t)n_x) &
+                            (at_row < (uint32_t)kWideRows);
+            lr[j][i] = ok ? (int32_t)at_row * CB : kWideRows * CB;
+            rv[j][i] = Xc[(uint64_t)(ok ? (uint32_t)g : 0u) * CH];
+        }
+    };
+    // weights of offset k for the wave's columns: lane (c, q) holds B_k[q KS + s][16 wc + c]
+    float w[KS], wn[KS];
+    const auto load_w = [&](int k, float (&v)[KS]) __attribute__((always_inline)) {
+        const int m = sel(k);
+        if constexpr (WT) {
+            const floatx4* src = reinterpret_cast<const floatx4*>(W + ((int64_t)m * CB + wc * 16 + r16) * CA + q * KS);
+#pragma unroll
+            for (int i = 0; i < KS / 4; ++i) {
+                const floatx4 t = src[i];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * i + e] = t[e];
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) v[s] = W[((int64_t)m * CA + q * KS + s) * CB + wc * 16 + r16];
+        }
+    };
+    // chunk c of row r of a step lies at r * CH + c with c's bits exchanged by the row's, so that the 16 rows of
+    // an operand read lie in different banks
+    const auto at = [](int r, int c) { return r * CH + (c ^ ((r / (16 / CH)) & (CH - 1))); };
+
+    const auto next_w = [&]() __attribute__((always_inline)) {
+        const int k = wleft ? __ffsll((long long)wleft) - 1 : 0;
+        wleft &= wleft - 1;
+        return k;
+    };
+    run_steps(load_idx, std::make_index_sequence<D>{});
+    load_w(next_w(), w);
+    load_w(next_w(), wn);
+    const auto fill = [&](auto P) __attribute__((always_inline)) {
+        load_rows(P);
+        load_idx(P);
+        return false;
+    };
+    run_steps(fill, std::make_index_sequence<D>{});
+    int buf = 0;
+    const auto step = [&](auto P) __attribute__((always_inline)) -> bool {
+        constexpr int j = decltype(P)::value;
+        const int ck = sk[j], cpb = spb[j], cnp = snp[j];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int r = i * RPI + mine;
+            rows[buf][at(r, tid % CH)] = rv[j][i];
+            lrow[buf][r] = lr[j][i];   // (the row's lanes write the same)
+        }
+        load_rows(P);
+        load_idx(P);
+        __syncthreads();
+        const auto operand = [&](int h, float (&a)[KS]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < KS / 4; ++i) {
+                const floatx4 t = rows[buf][at(16 * h + r16, q * (KS / 4) + i)];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[4 * i + e] = t[e];
+            }
+        };
+        float* col = acc + wc * 16 + r16;
+        const auto add = [&](const int4& l, const floatx4& d) __attribute__((always_inline)) {
+            // the pairs of a step have distinct rows, but for those that are none
+            const float s0 = col[l.x], s1 = col[l.y], s2 = col[l.z], s3 = col[l.w];
+            col[l.x] = s0 + d[0];
+            col[l.y] = s1 + d[1];
+            col[l.z] = s2 + d[2];
+            col[l.w] = s3 + d[3];
+        };
+        const int h0 = HW == 1 ? 0 : wh;   // the wave's first half
+        if (HW == 1 ? cpb + 16 < cnp : cpb + 16 * h0 < cnp) {   // uniform: both halves hold pairs, or the wave's own
+            const int4 l0 = *reinterpret_cast<const int4*>(&lrow[buf][16 * h0 + 4 * q]);
+            float a0[KS];
+            operand(h0, a0);
+            floatx4 d0 = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (HW == 1) {
+                const int4 l1 = *reinterpret_cast<const int4*>(&lrow[buf][16 + 4 * q]);
+                float a1[KS];
+                operand(1, a1);
+                floatx4 d1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[s], w[s], d0, 0, 0, 0);
+                    d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[s], w[s], d1, 0, 0, 0);
+                }
+                add(l0, d0);
+                add(l1, d1);
+            } else {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[s], w[s], d0, 0, 0, 0);
+                add(l0, d0);
+            }
+        } else if (HW == 1) {
+            const int4 l0 = *reinterpret_cast<const int4*>(&lrow[buf][4 * q]);
+            float a0[KS];
+            operand(0, a0);
+            floatx4 d0 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[s], w[s], d0, 0, 0, 0);
+            add(l0, d0);
+        }
+        buf ^= 1;
+        const int k = sk[(j + 1) % D];
+        if (k < 0) return true;
+        if (k != ck) {   // uniform: on to the next offset's weights, and ask for the ones after them
+#pragma unroll
+            for (int s = 0; s < KS; ++s) w[s] = wn[s];
+            load_w(next_w(), wn);
+        }
+        return false;
+    };
+    while (!run_steps(step, std::make_index_sequence<D>{})) {
+    }
+    }
+    __syncthreads();
+    for (int i = tid; i < kWideRows * CB / 4; i += kThreads) {
+        const int64_t row = row0 + i / (CB / 4);
+        if (row >= n_y) continue;
+        float4 v = reinterpret_cast<const float4*>(acc)[i];
+        if constexpr (EP) {
+            const int c = 4 * (i % (CB / 4));
+            float* vv = reinterpret_cast<float*>(&v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                vv[e] = epi_apply(vv[e], ep.scale ? ep.scale[c + e] : 1.f, ep.shift ? ep.shift[c + e] : 0.f, ep.relu);
+        }
+        reinterpret_cast<float4*>(Y)[row * (CB / 4) + i % (CB / 4)] = v;
     }
 }
 
@@ -665,6 +906,20 @@ static bool dw_f32_specialised(int ci, int co) {
 }
 
 template <int CA, int CB, bool WT, typename Sel>
+static void launch_f32_wide(const void* X, int64_t n_x, const void* W, const int32_t* gat, const int32_t* sca,
+                            const int64_t* gidx, int K, int64_t G, int64_t n_y, void* Y, Sel sel, const Epilogue& ep,
+                            hipStream_t s) {
+    const unsigned tiles = (unsigned)((n_y + kWideRows - 1) / kWideRows);
+    auto* kern = k_conv_f32_wide<CA, CB, WT, Sel, false>;
+    if constexpr (!WT) {   // the forward pass may carry an epilogue
+        if (ep.on()) kern = k_conv_f32_wide<CA, CB, WT, Sel, true>;
+    }
+    hipLaunchKernelGGL(kern, dim3(tiles), dim3(kThreads), 0, s, reinterpret_cast<const float*>(X), n_x,
+                       reinterpret_cast<const float*>(W), gat, sca, gidx, K, G, n_y, reinterpret_cast<float*>(Y), sel,
+                       ep);
+}
+
+template <int CA, int CB, bool WT, typename Sel>
 static void launch_f32(const void* X, int64_t n_x, const void* W, const int32_t* gat, const int32_t* sca,
                        const int64_t* gidx, const int32_t* perm, int K, int64_t G, int64_t n_y, void* Y, Sel sel,
                        hipStream_t s) {
@@ -684,20 +939,29 @@ static bool try_f32(int ca, int cb, const void* X, int64_t n_x, const void* W, c
         launch_f32<A, B, WT, Sel>(X, n_x, W, gat, sca, gidx, perm, K, G, n_y, Y, sel, s);      \
         return true;                                                                           \
     }
-    GSC_F32_CASE(16, 16) GSC_F32_CASE(16, 32) GSC_F32_CASE(32, 16) GSC_F32_CASE(32, 32)
-    GSC_F32_CASE(32, 64) GSC_F32_CASE(64, 32) GSC_F32_CASE(64, 64) GSC_F32_CASE(16, 64) GSC_F32_CASE(64, 16)
+    GSC_F32_CASE(16, 16) GSC_F32_CASE(16, 32) GSC_F32_CASE(32, 16) GSC_F32_CASE(16, 64) GSC_F32_CASE(64, 16)
 #undef GSC_F32_CASE
     return false;
 }
 
+// *fused (nullable): the kernel that ran has applied the epilogue.
 template <typename TIn, typename TOut, bool WT, typename Sel>
 static int launch_os(const void* X, int64_t n_x, const void* W, const int32_t* gat, const int32_t* sca,
                      const int64_t* gidx, const int32_t* perm, int K, int ca, int cb, int64_t n_y, void* Y, Sel sel,
-                     hipStream_t s) {
+                     hipStream_t s, const Epilogue& ep = Epilogue{}, bool* fused = nullptr) {
     if (n_y == 0) return GSC_OK;
     const int64_t tiles = (n_y + kTileRows - 1) / kTileRows;
     const int64_t G = (n_y + GSC_GROUP_ROWS - 1) / GSC_GROUP_ROWS;
     if constexpr (sizeof(TIn) == 4) {
+        if (K <= kWaveKMax && !perm && (ca == 32 || ca == 64) && (cb == 32 || cb == 64)) {
+#define GSC_WIDE_CASE(A, B) \
+    if (ca == A && cb == B) launch_f32_wide<A, B, WT, Sel>(X, n_x, W, gat, sca, gidx, K, G, n_y, Y, sel, ep, s);
+            GSC_WIDE_CASE(32, 32) GSC_WIDE_CASE(32, 64) GSC_WIDE_CASE(64, 32) GSC_WIDE_CASE(64, 64)
+#undef GSC_WIDE_CASE
+            if (fused) *fused = true;
+            GSC_LAUNCH_CHECK();
+            return GSC_OK;
+        }
         if (K <= kWaveKMax && try_f32<WT, Sel>(ca, cb, X, n_x, W, gat, sca, gidx, perm, K, G, n_y, Y, sel, s)) {
             GSC_LAUNCH_CHECK();
             return GSC_OK;
@@ -997,11 +1261,12 @@ static int conv_fwd(int32_t dtype, const void* X, int64_t n_in, int32_t c_in, co
         return blk_f32_ranges(c_in, c_out, reinterpret_cast<const float*>(X), n_in, reinterpret_cast<const float*>(W),
                               false, kNoSel, K, plan, n_out, reinterpret_cast<float*>(Y), s, ep);
     }
-    // row form: the sums are complete only once the call's kernels are done,
-    // so the epilogue is a pass of its own over Y
+    // row form: except where a kernel writes complete sums once, the epilogue
+    // is a pass of its own over Y
+    bool fused = false;
     if (dtype == GSC_F32) {
         rc = launch_os<float, float, false>(X, n_in, W, in_idx, out_idx, gidx, nullptr, K, c_in, c_out, n_out, Y,
-                                            WIdentity{}, s);
+                                            WIdentity{}, s, ep, &fused);
     } else if (fwd_uses_bf16_engine(dtype, c_in, c_out, K)) {
         if (n_out == 0) return GSC_OK;
         rc = transpose_w_bf16(W, K, c_in, c_out, ws, s);
@@ -1012,7 +1277,7 @@ static int conv_fwd(int32_t dtype, const void* X, int64_t n_in, int32_t c_in, co
         rc = launch_os<uint16_t, uint16_t, false>(X, n_in, W, in_idx, out_idx, gidx, nullptr, K, c_in, c_out, n_out,
                                                   Y, WIdentity{}, s);
     }
-    if (rc || !ep.on()) return rc;
+    if (rc || !ep.on() || fused) return rc;
     return affine_act(dtype, Y, n_out, c_out, ep, s);
 }
 

@@ -20,9 +20,6 @@
 // (v_mfma_f32_16x16x4f32) run last.  (Deeper pipelines measured no faster:
 // with 16 waves per CU the loads are not what the engine waits for.)  The loop body is unrolled over the slots, so each slot keeps its
 // registers (no copies of loads in flight).
-#include <type_traits>
-#include <utility>
-
 #include "conv_blk.h"
 
 namespace gsc {
@@ -56,13 +53,6 @@ struct BlkItem {
     int32_t b;
     bool last;
 };
-
-// f(0) || f(1) || ... || f(N-1) with compile-time arguments (stops at the
-// first true).
-template <typename F, size_t... I>
-__device__ __forceinline__ bool run_steps(F& f, std::index_sequence<I...>) {
-    return (f(std::integral_constant<int, (int)I>{}) || ...);
-}
 
 __device__ __forceinline__ int readlane_i32(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 __device__ __forceinline__ int64_t readlane_i64(int64_t v, int l) {

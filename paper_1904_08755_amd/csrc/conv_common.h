@@ -1,6 +1,9 @@
 // Device helpers shared by the convolution kernels (conv.hip, conv_bf16.hip).
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "gsc_internal.h"
 
 namespace gsc {
@@ -53,6 +56,13 @@ template <typename TIn, bool WT>
 __device__ __forceinline__ TIn w_at(const TIn* W, int w, int brow, int col, int ca, int cb) {
     if (WT) return W[((int64_t)w * cb + col) * ca + brow];
     return W[((int64_t)w * ca + brow) * cb + col];
+}
+
+// f(0) || f(1) || ... || f(N-1) with compile-time arguments (stops at the
+// first true).
+template <typename F, size_t... I>
+__device__ __forceinline__ bool run_steps(F& f, std::index_sequence<I...>) {
+    return (f(std::integral_constant<int, (int)I>{}) || ...);
 }
 
 // offset and pair range of a work item

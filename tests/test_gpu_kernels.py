@@ -279,3 +279,52 @@ def _plan_case(n, K):
                     blk = rows[16 * b:16 * b + 16]
                     assert np.array_equal(got[at], np.where(blk >= 0, nbr[k0 + k][blk], -1))
                     at += 1
+
+
+# --------------------------------------------------------------------------- #
+# float32 row form with 32 or 64 channels on both sides
+# --------------------------------------------------------------------------- #
+def _conv64(X, W, km):
+    Y = torch.zeros((km.n_out, W.shape[2]), dtype=torch.float64, device=DEV)
+    seg = km.seg.tolist()
+    for k in range(W.shape[0]):
+        i, o = km.in_idx[seg[k]:seg[k + 1]].long(), km.out_idx[seg[k]:seg[k + 1]].long()
+        Y[o] += X[i].double() @ W[k].double()
+    return Y
+
+
+# rows: remainders of a tile of 128, a tile, several; density: no pairs but the centre's to all offsets
+# full; offsets up to the 64 of a lane each
+@pytest.mark.parametrize("ca,cb", [(32, 32), (32, 64), (64, 32), (64, 64)])
+@pytest.mark.parametrize("n,span,region", [(1, 1, "cube3"), (63, 4, "cube3"), (128, 6, "cube3"), (129, 30, "cube3"),
+                                           (1000, 10, "cube3"), (1728, 12, "cube3"), (700, 9, "list64"),
+                                           (5, 2000, "one")])
+def test_conv_f32_wide_rows(n, span, region, ca, cb):
+    from paper_1904_08755_amd import gsc, regions
+    offs = {"cube3": regions.hypercube(3, 3), "one": np.zeros((1, 3), np.int32),
+            "list64": regions.hypercube(4, 3)}[region]
+    host = np.ascontiguousarray(_rows(n, n, 3, span, batch=1))
+    c = torch.from_numpy(host).to(DEV)
+    n, K = len(host), len(offs)
+    km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, offs)
+    g = torch.Generator(DEV).manual_seed(n + ca)
+    X = torch.randn((n, ca), generator=g, device=DEV)
+    W = torch.randn((K, ca, cb), generator=g, device=DEV) / (K * ca) ** 0.5
+    Y = gsc.gsc_sparse_conv_fwd(X, W, km)
+    ref = _conv64(X, W, km)
+    mag = _conv64(X.abs(), W.abs(), km)
+    bound = (ca + K + 2) * 2.0 ** -24          # products and additions of a sum, each half an ulp
+    assert ((Y.double() - ref).abs() <= mag * bound).all()
+    assert torch.equal(Y, gsc.gsc_sparse_conv_fwd(X, W, km))
+    scale, shift = 0.5 + torch.rand(cb, generator=g, device=DEV), torch.randn(cb, generator=g, device=DEV)
+    A = gsc.gsc_sparse_conv_fwd_affine(X, W, km, scale, shift, relu=True)
+    want = torch.clamp(Y.double() * scale.double() + shift.double(), min=0)
+    assert ((A.double() - want).abs() <= want.abs() * 2.0 ** -23 + 1e-30).all()
+    # input gradient: the role-reversed map's products with W^T
+    dY = torch.randn((n, ca), generator=g, device=DEV)
+    V = torch.randn((K, cb, ca), generator=g, device=DEV) / (K * ca) ** 0.5
+    tm = gsc.gsc_kernel_map_transpose(km, n)
+    dX, _ = gsc.gsc_sparse_conv_bwd(torch.zeros((n, cb), device=DEV), V, dY, km, tm, np.arange(K), need_dw=False)
+    T = V.transpose(1, 2).contiguous()
+    tk = type(km)(tm.in_idx, tm.out_idx, tm.seg, tm.gidx, km.n_pairs, n, tm.offsets)
+    assert ((dX.double() - _conv64(dY, T, tk)).abs() <= _conv64(dY.abs(), T.abs(), tk) * bound).all()
