@@ -736,7 +736,231 @@ k_dw_tile_bf16(const uint16_t* __restrict__ X, int64_t n_in, const uint16_t* __r
             for (int b = 0; b < C::NJ; ++b) out[(int64_t)(16 * a + 4 * q + i) * CO + 16 * b + i16] = acc[a][b][i];
 }
 
-bool dw_tile_bf16_supported(int ci, int co) { return ci == 256 && co == 256; }
+// ---------------------------------------------------------------------------
+// Weight gradient of layers of 64 and 128 channels: the kernel above with a
+// workgroup of four waves, two of which fit a CU (80 KiB of LDS each), so
+// that one computes while the other waits at its barrier.
+//
+// A step of 32 pairs of 128 x 128 is 16 products (256 cycles) per wave, 32 KiB
+// of operand reads (256 cycles of the CU's LDS) and 16 KiB of copied rows;
+// wave (r, c) keeps a (C_in / 2) x (C_out / 2) part of dW.  The byte offsets of
+// the item's rows are worked out once, into LDS (kTileNone for pairs out of
+// range and past the end), and each step's are read with the operands of the
+// step before, so the vector memory counter counts the copies alone.
+// 3.7 million pairs of 128 x 128 (480,288 rows): 350 us in k_dw_bf16, which
+// transposes through registers, 296 us here (6.4 TB/s of gathered rows; the
+// products alone would take 110).  64 x 128, 8 offsets over 480,288 rows:
+// 120 us in the kernel for any width, 33 us here.
+// ---------------------------------------------------------------------------
+constexpr int kDwLdsThreads = 256;
+
+template <int CI, int CO>
+struct DwLdsCfg {
+    static constexpr int NI = CI / 32, NJ = CO / 32;   // 16-channel blocks per wave
+    static constexpr int XI = CI / 64, YI = CO / 64;   // copy instructions per wave and step (1 KiB each)
+    static constexpr int LOADS = XI + YI;
+    static constexpr int XB = 32 * CI * 2, YB = 32 * CO * 2;   // bytes of a step's rows
+    static constexpr int CAP = CI * CO == 64 * 64 ? 1024 : 2048;   // pairs of a work item at most
+    static_assert((CI == 64 || CI == 128) && (CO == 64 || CO == 128), "widths");
+};
+
+#define GSC_TR2(a, b, in, off) "ds_read_b64_tr_b16 %" #a ", %" #in "\n ds_read_b64_tr_b16 %" #b ", %" #in " offset:%" #off "\n"
+#define GSC_IX(a, in) "ds_read_b32 %" #a ", %" #in "\n"
+#define GSC_IX16(a, in) "ds_read_b32 %" #a ", %" #in " offset:16\n"
+
+// The transpose reads of NA blocks of one operand and NB of the other (second
+// halves OA and OB bytes on) and the next row offsets, waited for in the same
+// block (see k_dw_tile_bf16).  One row offset per 64 channels of each operand:
+// a's at ia, b's at ib (the second 16 bytes on).
+template <int NA, int NB, int OA, int OB>
+__device__ __forceinline__ void dw_lds_read(const uint32_t (&a)[NA], const uint32_t (&b)[NB], uint32_t ia, uint32_t ib,
+                                            ts16x4 (&r)[2 * (NA + NB)], uint32_t (&na)[NA / 2], uint32_t (&nb)[NB / 2]) {
+    if constexpr (NA == 4 && NB == 4) {
+        asm volatile(GSC_TR2(0, 1, 20, 30) GSC_TR2(2, 3, 21, 30) GSC_TR2(4, 5, 22, 30) GSC_TR2(6, 7, 23, 30)
+                     GSC_TR2(8, 9, 24, 31) GSC_TR2(10, 11, 25, 31) GSC_TR2(12, 13, 26, 31) GSC_TR2(14, 15, 27, 31)
+                     GSC_IX(16, 28) GSC_IX16(17, 28) GSC_IX(18, 29) GSC_IX16(19, 29) "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]),
+                       "=&v"(r[7]), "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11]), "=&v"(r[12]), "=&v"(r[13]),
+                       "=&v"(r[14]), "=&v"(r[15]), "=&v"(na[0]), "=&v"(na[1]), "=&v"(nb[0]), "=&v"(nb[1])
+                     : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]),
+                       "v"(ia), "v"(ib), "n"(OA), "n"(OB)
+                     : "memory");
+    } else if constexpr (NA == 2 && NB == 4) {
+        asm volatile(GSC_TR2(0, 1, 15, 23) GSC_TR2(2, 3, 16, 23) GSC_TR2(4, 5, 17, 24) GSC_TR2(6, 7, 18, 24)
+                     GSC_TR2(8, 9, 19, 24) GSC_TR2(10, 11, 20, 24)
+                     GSC_IX(12, 21) GSC_IX(13, 22) GSC_IX16(14, 22) "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]),
+                       "=&v"(r[7]), "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11]), "=&v"(na[0]),
+                       "=&v"(nb[0]), "=&v"(nb[1])
+                     : "v"(a[0]), "v"(a[1]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(ia), "v"(ib), "n"(OA),
+                       "n"(OB)
+                     : "memory");
+    } else if constexpr (NA == 4 && NB == 2) {
+        asm volatile(GSC_TR2(0, 1, 15, 23) GSC_TR2(2, 3, 16, 23) GSC_TR2(4, 5, 17, 23) GSC_TR2(6, 7, 18, 23)
+                     GSC_TR2(8, 9, 19, 24) GSC_TR2(10, 11, 20, 24)
+                     GSC_IX(12, 21) GSC_IX16(13, 21) GSC_IX(14, 22) "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]),
+                       "=&v"(r[7]), "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11]), "=&v"(na[0]),
+                       "=&v"(na[1]), "=&v"(nb[0])
+                     : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(ia), "v"(ib), "n"(OA),
+                       "n"(OB)
+                     : "memory");
+    } else {
+        static_assert(NA == 2 && NB == 2, "blocks of a wave");
+        asm volatile(GSC_TR2(0, 1, 10, 16) GSC_TR2(2, 3, 11, 16) GSC_TR2(4, 5, 12, 17) GSC_TR2(6, 7, 13, 17)
+                     GSC_IX(8, 14) GSC_IX(9, 15) "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]),
+                       "=&v"(r[7]), "=&v"(na[0]), "=&v"(nb[0])
+                     : "v"(a[0]), "v"(a[1]), "v"(b[0]), "v"(b[1]), "v"(ia), "v"(ib), "n"(OA), "n"(OB)
+                     : "memory");
+    }
+}
+#undef GSC_TR2
+#undef GSC_IX
+#undef GSC_IX16
+
+template <int CI, int CO>
+__global__ void __launch_bounds__(kDwLdsThreads, 2)
+k_dw_lds_bf16(const uint16_t* __restrict__ X, int64_t n_in, const uint16_t* __restrict__ dY, int64_t n_out,
+              const int32_t* __restrict__ in_idx, const int32_t* __restrict__ out_idx,
+              const int64_t* __restrict__ seg, const int64_t* __restrict__ ibase, const int64_t* __restrict__ chunk,
+              int K, float* __restrict__ part) {
+    using C = DwLdsCfg<CI, CO>;
+    __shared__ __attribute__((aligned(1024))) uint8_t ring[4 * (C::XB + C::YB)];
+    __shared__ uint32_t xoff[C::CAP], yoff[C::CAP];
+
+    if ((int64_t)blockIdx.x >= ibase[K]) return;
+    const int64_t item = xcd_unit(blockIdx.x, ibase[K]);
+    int k;
+    int64_t p_begin, p_end;
+    if (!dw_item(ibase, chunk, seg, K, item, &k, &p_begin, &p_end)) return;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wr = wave >> 1, wc = wave & 1;
+    const int np = (int)min(p_end - p_begin, (int64_t)C::CAP);
+    const int steps = (np + 31) / 32;
+
+    const __amdgpu_buffer_rsrc_t xr =
+        __builtin_amdgcn_make_buffer_rsrc((void*)X, (short)0, (int)(n_in * CI * 2), kTileBufFlags);
+    const __amdgpu_buffer_rsrc_t yr =
+        __builtin_amdgcn_make_buffer_rsrc((void*)dY, (short)0, (int)(n_out * CO * 2), kTileBufFlags);
+
+    for (int i = tid; i < 32 * steps; i += kDwLdsThreads) {
+        const int64_t p = p_begin + min(i, np - 1);
+        const int32_t g = in_idx[p], o = out_idx[p];
+        const bool v = i < np && g >= 0 && g < n_in && o >= 0 && o < n_out;
+        xoff[i] = v ? (uint32_t)g * (uint32_t)(CI * 2) : kTileNone;
+        yoff[i] = v ? (uint32_t)o * (uint32_t)(CO * 2) : kTileNone;
+    }
+    __syncthreads();
+
+    // Copy instruction j of a wave covers rows RX (XI wave + j) .. of the step
+    // (RX = 64 / lanes per row); lane l fetches 16 bytes of its row: the
+    // data chunk that the permutation puts at position l.
+    constexpr int XL = CI / 8, YL = CO / 8;
+    auto lane_src = [&](int lanes_per_row) -> uint32_t {
+        const int u16 = lane % lanes_per_row, row = lane / lanes_per_row;   // rows start at multiples of 4
+        return (uint32_t)((((u16 >> 1) ^ (row & 3)) * 32) + (u16 & 1) * 16);
+    };
+    const uint32_t xsrc = lane_src(XL), ysrc = lane_src(YL);
+    // the wave's first row of step 0, in the offset tables
+    const int xrow = wave * C::XI * (64 / XL) + lane / XL, yrow = wave * C::YI * (64 / YL) + lane / YL;
+    // kTileNone + a lane's part is still past either buffer
+    auto issue = [&](const uint32_t(&xo)[C::XI], const uint32_t(&yo)[C::YI], int st, bool live) {
+        uint8_t* dx = ring + st * (C::XB + C::YB);
+        uint8_t* dy = dx + C::XB;
+#pragma unroll
+        for (int j = 0; j < C::XI; ++j) {
+            const uint32_t off = live ? xo[j] + xsrc : kTileNone;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                xr, (__attribute__((address_space(3))) void*)(dx + (wave * C::XI + j) * 1024), 16, off, 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < C::YI; ++j) {
+            const uint32_t off = live ? yo[j] + ysrc : kTileNone;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                yr, (__attribute__((address_space(3))) void*)(dy + (wave * C::YI + j) * 1024), 16, off, 0, 0, 0);
+        }
+    };
+
+    // transpose reads, as in k_dw_tile_bf16
+    const int i16 = lane & 15, q = lane >> 4;
+    const int trow = 8 * q + (i16 >> 2);
+    uint32_t xa[C::NI], yb[C::NJ];
+    const uint32_t base = (uint32_t)(uintptr_t)ring;
+#pragma unroll
+    for (int a = 0; a < C::NI; ++a)
+        xa[a] = base + trow * (CI * 2) + (((C::NI * wr + a) ^ (trow & 3)) * 32) + 8 * (i16 & 3);
+#pragma unroll
+    for (int b = 0; b < C::NJ; ++b)
+        yb[b] = base + C::XB + trow * (CO * 2) + (((C::NJ * wc + b) ^ (trow & 3)) * 32) + 8 * (i16 & 3);
+
+    floatx4 acc[C::NI][C::NJ];
+#pragma unroll
+    for (int a = 0; a < C::NI; ++a)
+#pragma unroll
+        for (int b = 0; b < C::NJ; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    // step s reads stage s % 4; the copies of step s + 3 go into the stage
+    // that step s - 1 has read; a step ends once step s + 1 is copied
+    uint32_t xo[C::XI], yo[C::YI];
+    for (int s = 0; s < 4; ++s) {   // the row offsets of steps 0 .. 3 (or of the last step)
+        const int sc = min(s, steps - 1) * 32;
+#pragma unroll
+        for (int j = 0; j < C::XI; ++j) xo[j] = xoff[sc + xrow + j * (64 / XL)];
+#pragma unroll
+        for (int j = 0; j < C::YI; ++j) yo[j] = yoff[sc + yrow + j * (64 / YL)];
+        if (s < 3) issue(xo, yo, s, s < steps);
+    }
+    __builtin_amdgcn_s_waitcnt(VmLgkmWait<2 * C::LOADS>::value);   // step 0 copied
+    tile_barrier();
+    const uint32_t xix = (uint32_t)(uintptr_t)(xoff + xrow), yix = (uint32_t)(uintptr_t)(yoff + yrow);
+    auto step = [&](int s, auto P) __attribute__((always_inline)) {
+        constexpr int p = decltype(P)::value;
+        constexpr uint32_t st = p * (C::XB + C::YB);
+        issue(xo, yo, (p + 3) % 4, s + 3 < steps);
+        const uint32_t sc = (uint32_t)min(s + 4, steps - 1) * 128u;
+        uint32_t ax[C::NI], by[C::NJ];
+#pragma unroll
+        for (int a = 0; a < C::NI; ++a) ax[a] = xa[a] + st;
+#pragma unroll
+        for (int b = 0; b < C::NJ; ++b) by[b] = yb[b] + st;
+        ts16x4 r[2 * (C::NI + C::NJ)];
+        dw_lds_read<C::NI, C::NJ, 4 * CI * 2, 4 * CO * 2>(ax, by, xix + sc, yix + sc, r, xo, yo);
+        auto join = [&](int i) __attribute__((always_inline)) {
+            const ts16x4 v8[2] = {r[2 * i], r[2 * i + 1]};
+            return __builtin_bit_cast(tbf16x8, v8);
+        };
+        __builtin_amdgcn_s_waitcnt(VmLgkmWait<2 * C::LOADS>::value);   // step s + 1's copies done
+#pragma unroll
+        for (int a = 0; a < C::NI; ++a)
+#pragma unroll
+            for (int b = 0; b < C::NJ; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(join(a), join(C::NI + b), acc[a][b], 0, 0, 0);
+        tile_barrier();
+    };
+    for (int s = 0; s < steps; s += 4) {
+        step(s, std::integral_constant<int, 0>{});
+        if (s + 1 < steps) step(s + 1, std::integral_constant<int, 1>{});
+        if (s + 2 < steps) step(s + 2, std::integral_constant<int, 2>{});
+        if (s + 3 < steps) step(s + 3, std::integral_constant<int, 3>{});
+    }
+    __builtin_amdgcn_s_waitcnt(VmLgkmWait<0>::value);   // the trailing (empty) copies
+
+    float* out = part + (item * CI + (CI / 2) * wr) * (int64_t)CO + (CO / 2) * wc;
+#pragma unroll
+    for (int a = 0; a < C::NI; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < C::NJ; ++b) out[(int64_t)(16 * a + 4 * q + i) * CO + 16 * b + i16] = acc[a][b][i];
+}
+
+// ch: pairs of a work item (the offset tables of the 64- and 128-channel kernels hold that many)
+bool dw_tile_bf16_supported(int ci, int co, int64_t ch) {
+    if (ci == 256 && co == 256) return true;
+    return (ci == 64 || ci == 128) && (co == 64 || co == 128) && ch <= (ci == 64 && co == 64 ? DwLdsCfg<64, 64>::CAP : DwLdsCfg<128, 128>::CAP);
+}
 
 int dw_tile_bf16(int ci, int co, const void* X, int64_t n_in, const void* dY, int64_t n_out, const int32_t* in_idx,
                  const int32_t* out_idx, const int64_t* seg, const int64_t* ibase, const int64_t* chunk, int K,
@@ -752,6 +976,16 @@ int dw_tile_bf16(int ci, int co, const void* X, int64_t n_in, const void* dY, in
     }
     GSC_DWT_CASE(256, 256)
 #undef GSC_DWT_CASE
+#define GSC_DWL_CASE(A, B)                                                                                    \
+    if (ci == A && co == B) {                                                                                 \
+        hipLaunchKernelGGL((k_dw_lds_bf16<A, B>), dim3((unsigned)items), dim3(kDwLdsThreads), 0, s,            \
+                           reinterpret_cast<const uint16_t*>(X), n_in, reinterpret_cast<const uint16_t*>(dY), n_out, \
+                           in_idx, out_idx, seg, ibase, chunk, K, part);                                      \
+        GSC_LAUNCH_CHECK();                                                                                   \
+        return GSC_OK;                                                                                        \
+    }
+    GSC_DWL_CASE(64, 64) GSC_DWL_CASE(64, 128) GSC_DWL_CASE(128, 64) GSC_DWL_CASE(128, 128)
+#undef GSC_DWL_CASE
     return fail(GSC_EINVAL, "dw_tile_bf16: unsupported channels %d x %d", ci, co);
 }
 

@@ -328,3 +328,40 @@ def test_conv_f32_wide_rows(n, span, region, ca, cb):
     T = V.transpose(1, 2).contiguous()
     tk = type(km)(tm.in_idx, tm.out_idx, tm.seg, tm.gidx, km.n_pairs, n, tm.offsets)
     assert ((dX.double() - _conv64(dY, T, tk)).abs() <= _conv64(dY.abs(), T.abs(), tk) * bound).all()
+
+
+# pairs of an offset: none, one, about a step of 32, about the ring's four steps, about a work item (1024 or
+# 2048 pairs) and several; rows out of range on either side add nothing
+@pytest.mark.parametrize("ci,co", [(64, 64), (64, 128), (128, 64), (128, 128), (256, 256)])
+def test_dw_bf16_pairs(ci, co):
+    from paper_1904_08755_amd import gsc, regions
+    sizes = [0, 1, 31, 32, 33, 96, 128, 129, 1024, 1025, 2047, 2048, 2049, 4300, 0]
+    K, n_in, n_out = len(sizes), 900, 900
+    host = np.ascontiguousarray(_rows(3, 50, 3, 6, batch=1))
+    c = torch.from_numpy(host).to(DEV)
+    km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, regions.hypercube(3, 3))
+    g = torch.Generator(DEV).manual_seed(ci + co)
+    P = sum(sizes)
+    ii = torch.randint(0, n_in, (P,), generator=g, device=DEV, dtype=torch.int32)
+    oi = torch.randint(0, n_out, (P,), generator=g, device=DEV, dtype=torch.int32)
+    seg = torch.tensor([0] + list(np.cumsum(sizes)), dtype=torch.int64, device=DEV)
+    bad = torch.rand(P, generator=g, device=DEV) < 0.02
+    bad[seg[2]:seg[4]] = False
+    in_bad, out_bad = ii.clone(), oi.clone()
+    in_bad[bad] = torch.tensor([-1, n_in], dtype=torch.int32, device=DEV)[torch.arange(int(bad.sum())) % 2]
+    out_bad[bad.roll(1)] = n_out
+    skip = bad | bad.roll(1)
+    m = type(km)(in_bad, out_bad, seg, km.gidx, P, n_out, np.zeros((K, 3), np.int32), n_bound=P)
+    X = torch.randn((n_in, ci), generator=g, device=DEV).bfloat16()
+    dY = torch.randn((n_out, co), generator=g, device=DEV).bfloat16()
+    W = torch.zeros((K, ci, co), device=DEV, dtype=torch.bfloat16)
+    run = lambda: gsc.gsc_sparse_conv_bwd(X, W, dY, m, m, np.arange(K), need_dx=False)[1]
+    dW = run()
+    for k in range(K):
+        a, b = int(seg[k]), int(seg[k + 1])
+        keep = ~skip[a:b]
+        x, y = X[ii[a:b].long()[keep]].double(), dY[oi[a:b].long()[keep]].double()
+        # products of bf16 are exact in float32; each addition is half an ulp off at most, or one where the
+        # matrix unit cuts off
+        assert ((dW[k].double() - x.t() @ y).abs() <= (x.abs().t() @ y.abs()) * (b - a + 2) * 2.0 ** -23).all()
+    assert torch.equal(dW, run())
