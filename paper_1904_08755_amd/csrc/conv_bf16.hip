@@ -22,7 +22,7 @@
 // transposed copy made by k_transpose_w.
 //
 // Weight gradient (k_dw_bf16; 128 x 256, 256 x 128, and what is too large for
-// the buffer loads of conv_tile.hip's kernels, 350 us against their 296 at 3.7
+// the buffer loads of conv_tile.hip's kernels, 350 us against their 190 at 3.7
 // million pairs of 128 x 128): split-K over the pairs of each offset.  The
 // reduction runs over pairs, so a workgroup stages 32 pairs' rows of X and
 // dY in LDS transposed (channel-major) and every lane then reads its 8

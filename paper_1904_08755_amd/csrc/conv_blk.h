@@ -61,11 +61,12 @@ int conv_tile_bf16(int ca, int cb, const void* X, int64_t n_x, const void* Bt, c
 // Weight gradient of a wide bf16 layer (conv_tile.hip), ci and co in {64,
 // 128} with items of at most 1024 (64 x 64) or 2048 pairs (ch), or both 256:
 // the partial sum of each work item (dw_item) over its pairs, written to
-// part[item] (ci x co float32); grid = items.  Asynchronous.
+// part[item] (ci x co float32); grid = items.  order (64 and 128 channels):
+// the t-th item to run (k_dw_items).  Asynchronous.
 bool dw_tile_bf16_supported(int ci, int co, int64_t ch);
 int dw_tile_bf16(int ci, int co, const void* X, int64_t n_in, const void* dY, int64_t n_out, const int32_t* in_idx,
-                 const int32_t* out_idx, const int64_t* seg, const int64_t* ibase, const int64_t* chunk, int K,
-                 int64_t items, float* part, hipStream_t s);
+                 const int32_t* out_idx, const int64_t* seg, const int64_t* ibase, const int64_t* chunk,
+                 const int32_t* order, int K, int64_t items, float* part, hipStream_t s);
 
 // Y (n x c, float32 or bf16 by dtype) = the epilogue applied in place (the
 // row-form paths, whose sums are complete only in Y).  Asynchronous.

@@ -748,9 +748,10 @@ k_dw_tile_bf16(const uint16_t* __restrict__ X, int64_t n_in, const uint16_t* __r
 // range and past the end), and each step's are read with the operands of the
 // step before, so the vector memory counter counts the copies alone.
 // 3.7 million pairs of 128 x 128 (480,288 rows): 350 us in k_dw_bf16, which
-// transposes through registers, 296 us here (6.4 TB/s of gathered rows; the
-// products alone would take 110).  64 x 128, 8 offsets over 480,288 rows:
-// 120 us in the kernel for any width, 33 us here.
+// transposes through registers, 190 us here (9.9 TB/s of gathered rows, half of
+// them from the L2s thanks to the items' order; the products alone would take
+// 110).  64 x 128, 8 offsets over 480,288 rows: 120 us in the kernel for any
+// width, 30 us here.
 // ---------------------------------------------------------------------------
 constexpr int kDwLdsThreads = 256;
 
@@ -824,13 +825,13 @@ __global__ void __launch_bounds__(kDwLdsThreads, 2)
 k_dw_lds_bf16(const uint16_t* __restrict__ X, int64_t n_in, const uint16_t* __restrict__ dY, int64_t n_out,
               const int32_t* __restrict__ in_idx, const int32_t* __restrict__ out_idx,
               const int64_t* __restrict__ seg, const int64_t* __restrict__ ibase, const int64_t* __restrict__ chunk,
-              int K, float* __restrict__ part) {
+              const int32_t* __restrict__ order, int K, float* __restrict__ part) {
     using C = DwLdsCfg<CI, CO>;
     __shared__ __attribute__((aligned(1024))) uint8_t ring[4 * (C::XB + C::YB)];
     __shared__ uint32_t xoff[C::CAP], yoff[C::CAP];
 
     if ((int64_t)blockIdx.x >= ibase[K]) return;
-    const int64_t item = xcd_unit(blockIdx.x, ibase[K]);
+    const int64_t item = order[xcd_unit(blockIdx.x, ibase[K])];
     int k;
     int64_t p_begin, p_end;
     if (!dw_item(ibase, chunk, seg, K, item, &k, &p_begin, &p_end)) return;
@@ -963,8 +964,8 @@ bool dw_tile_bf16_supported(int ci, int co, int64_t ch) {
 }
 
 int dw_tile_bf16(int ci, int co, const void* X, int64_t n_in, const void* dY, int64_t n_out, const int32_t* in_idx,
-                 const int32_t* out_idx, const int64_t* seg, const int64_t* ibase, const int64_t* chunk, int K,
-                 int64_t items, float* part, hipStream_t s) {
+                 const int32_t* out_idx, const int64_t* seg, const int64_t* ibase, const int64_t* chunk,
+                 const int32_t* order, int K, int64_t items, float* part, hipStream_t s) {
     if (items <= 0) return GSC_OK;
 #define GSC_DWT_CASE(A, B)                                                                                    \
     if (ci == A && co == B) {                                                                                 \
@@ -980,7 +981,7 @@ int dw_tile_bf16(int ci, int co, const void* X, int64_t n_in, const void* dY, in
     if (ci == A && co == B) {                                                                                 \
         hipLaunchKernelGGL((k_dw_lds_bf16<A, B>), dim3((unsigned)items), dim3(kDwLdsThreads), 0, s,            \
                            reinterpret_cast<const uint16_t*>(X), n_in, reinterpret_cast<const uint16_t*>(dY), n_out, \
-                           in_idx, out_idx, seg, ibase, chunk, K, part);                                      \
+                           in_idx, out_idx, seg, ibase, chunk, order, K, part);                                      \
         GSC_LAUNCH_CHECK();                                                                                   \
         return GSC_OK;                                                                                        \
     }

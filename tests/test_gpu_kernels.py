@@ -331,11 +331,13 @@ def test_conv_f32_wide_rows(n, span, region, ca, cb):
 
 
 # pairs of an offset: none, one, about a step of 32, about the ring's four steps, about a work item (1024 or
-# 2048 pairs) and several; rows out of range on either side add nothing
-@pytest.mark.parametrize("ci,co", [(64, 64), (64, 128), (128, 64), (128, 128), (256, 256)])
-def test_dw_bf16_pairs(ci, co):
+# 2048 pairs) and several; rows out of range on either side add nothing; more offsets than the items are
+# ordered over (128)
+@pytest.mark.parametrize("ci,co,rep", [(64, 64, 1), (64, 64, 9), (64, 128, 1), (128, 64, 1), (128, 128, 1),
+                                       (256, 256, 1)])
+def test_dw_bf16_pairs(ci, co, rep):
     from paper_1904_08755_amd import gsc, regions
-    sizes = [0, 1, 31, 32, 33, 96, 128, 129, 1024, 1025, 2047, 2048, 2049, 4300, 0]
+    sizes = [0, 1, 31, 32, 33, 96, 128, 129, 1024, 1025, 2047, 2048, 2049, 4300, 0] * rep
     K, n_in, n_out = len(sizes), 900, 900
     host = np.ascontiguousarray(_rows(3, 50, 3, 6, batch=1))
     c = torch.from_numpy(host).to(DEV)
