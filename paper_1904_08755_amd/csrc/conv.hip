@@ -708,15 +708,20 @@ __device__ __forceinline__ void dw_store_partial(float* sh, const floatx4 (&d)[4
     }
 }
 
-// Generic weight-gradient partial (any dtype, any width): a 64 x 64 tile of
-// X[in]^T dY[out] over one chunk of one offset's pairs.
-template <typename TIn>
+// Generic weight-gradient partial (any dtype, any width): a 16 NA x 16 NB tile
+// of X[in]^T dY[out] over one chunk of one offset's pairs, NA or NB 1 where
+// that side has at most 16 channels and 4 otherwise.  Bound by the latency of
+// its loads: 3 -> 16 channels over 2,000 rows took 38 us with one step of
+// 4 pairs at a time (and a tile of 64 x 64 whatever the width), 13 us with
+// eight.
+template <typename TIn, int NA, int NB>
 __global__ void __launch_bounds__(kThreads)
 k_dw_partial(const TIn* __restrict__ X, int64_t n_in, const TIn* __restrict__ dY, int64_t n_out,
              const int32_t* __restrict__ in_idx, const int32_t* __restrict__ out_idx, const int64_t* __restrict__ seg,
              const int64_t* __restrict__ ibase, const int64_t* __restrict__ chunk, int K, int ci, int co,
              float* __restrict__ part) {
-    __shared__ float sh[4 * kDwTile * (kDwTile + 1)];
+    constexpr int R = 16 * NA, C = 16 * NB;
+    __shared__ float sh[4 * R * (C + 1)];
     int k;
     int64_t p_begin, p_end;
     // the grid covers an upper bound of the items; order the real ones XCD-wise
@@ -735,28 +740,44 @@ k_dw_partial(const TIn* __restrict__ X, int64_t n_in, const TIn* __restrict__ dY
         for (int b = 0; b < 4; ++b) d[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     if constexpr (sizeof(TIn) == 4) {
-        // 4 pairs per MFMA step (reduction index kk = q); waves interleave steps
-        for (int64_t p0 = p_begin + 4 * wave; p0 < p_end; p0 += 16) {
-            const int64_t p = p0 + q;
-            int32_t g = p < p_end ? in_idx[p] : -1;
-            int32_t s = p < p_end ? out_idx[p] : -1;
-            const bool v = g >= 0 && g < n_in && s >= 0 && s < n_out;
-            float xa[4], yb[4];
+        // 4 pairs per MFMA step (reduction index kk = q); the waves interleave
+        // groups of U steps, whose row numbers and then rows are loaded together
+        // from clamped addresses: one step at a time is a chain of two loads
+        // per 4 pairs
+        constexpr int U = NA * NB == 1 ? 8 : 4;
+        if (n_in < 1 || n_out < 1) p_begin = p_end;   // no row to clamp to
+        for (int64_t p0 = p_begin + 4 * U * wave; p0 < p_end; p0 += 16 * U) {
+            int32_t g[U], s[U];
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int c = ci0 + 16 * a + r16;
-                xa[a] = (v && a < na && c < ci) ? to_f32(X[(int64_t)g * ci + c]) : 0.f;
+            for (int u = 0; u < U; ++u) {
+                const int64_t p = min(p0 + 4 * u + q, p_end - 1);
+                g[u] = in_idx[p];
+                s[u] = out_idx[p];
             }
+            float xa[U][NA], yb[U][NB];
+            bool v[U];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int c = co0 + 16 * b + r16;
-                yb[b] = (v && b < nbk && c < co) ? to_f32(dY[(int64_t)s * co + c]) : 0.f;
+            for (int u = 0; u < U; ++u) {
+                v[u] = p0 + 4 * u + q < p_end && g[u] >= 0 && g[u] < n_in && s[u] >= 0 && s[u] < n_out;
+                const TIn* xr = X + (int64_t)(v[u] ? g[u] : 0) * ci;
+                const TIn* yr = dY + (int64_t)(v[u] ? s[u] : 0) * co;
+#pragma unroll
+                for (int a = 0; a < NA; ++a)
+                    if (NA == 1 || a < na) xa[u][a] = to_f32(xr[min(ci0 + 16 * a + r16, ci - 1)]);
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    if (NB == 1 || b < nbk) yb[u][b] = to_f32(yr[min(co0 + 16 * b + r16, co - 1)]);
             }
+            // columns past the widths hold repeats, which are not stored
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (a < na && b < nbk) d[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[a], yb[b], d[a][b], 0, 0, 0);
+                for (int a = 0; a < NA; ++a)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        if ((NA == 1 || a < na) && (NB == 1 || b < nbk))
+                            d[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u] ? xa[u][a] : 0.f, v[u] ? yb[u][b] : 0.f,
+                                                                          d[a][b], 0, 0, 0);
         }
     } else {
         // 16 pairs per MFMA step: lane (r16, q) supplies pairs 4q .. 4q+3
@@ -770,32 +791,32 @@ k_dw_partial(const TIn* __restrict__ X, int64_t n_in, const TIn* __restrict__ dY
                 s[e] = p < p_end ? out_idx[p] : -1;
                 v[e] = g[e] >= 0 && g[e] < n_in && s[e] >= 0 && s[e] < n_out;
             }
-            shortx4 xa[4], yb[4];
+            shortx4 xa[NA], yb[NB];
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
+            for (int a = 0; a < NA; ++a) {
                 const int c = ci0 + 16 * a + r16;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     xa[a][e] = (v[e] && a < na && c < ci) ? (short)X[(int64_t)g[e] * ci + c] : (short)0;
             }
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 const int c = co0 + 16 * b + r16;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     yb[b][e] = (v[e] && b < nbk && c < co) ? (short)dY[(int64_t)s[e] * co + c] : (short)0;
             }
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int a = 0; a < NA; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+                for (int b = 0; b < NB; ++b)
                     if (a < na && b < nbk)
                         d[a][b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xa[a], yb[b], d[a][b], 0, 0, 0);
         }
     }
     // D[m][n]: m = 4q + j (input channel), n = r16 (output channel)
     const int rows = min(kDwTile, ci - ci0), cols = min(kDwTile, co - co0);
-    dw_store_partial<kDwTile, kDwTile>(sh, d, na, nbk, wave, q, r16, rows, cols,
+    dw_store_partial<R, C>(sh, d, na, nbk, wave, q, r16, rows, cols,
                                        part + (item * ci + ci0) * (int64_t)co + co0, co);
 }
 
@@ -1491,14 +1512,22 @@ int gsc_sparse_conv_bwd(int32_t dtype, const void* X, const void* W, const void*
             if (rc) return rc;
         } else {
             const unsigned tiles = (unsigned)dw_tiles(c_in, c_out);
-            if (dtype == GSC_F32)
-                hipLaunchKernelGGL(k_dw_partial<float>, dim3((unsigned)items, tiles), dim3(kThreads), 0, s,
-                                   reinterpret_cast<const float*>(X), n_in, reinterpret_cast<const float*>(dY), n_out,
-                                   in_idx, out_idx, seg, ibase, chunk, K, c_in, c_out, part);
-            else
-                hipLaunchKernelGGL(k_dw_partial<uint16_t>, dim3((unsigned)items, tiles), dim3(kThreads), 0, s,
-                                   reinterpret_cast<const uint16_t*>(X), n_in, reinterpret_cast<const uint16_t*>(dY),
-                                   n_out, in_idx, out_idx, seg, ibase, chunk, K, c_in, c_out, part);
+#define GSC_DWP_CASE(T, NA, NB)                                                                               \
+    hipLaunchKernelGGL((k_dw_partial<T, NA, NB>), dim3((unsigned)items, tiles), dim3(kThreads), 0, s,          \
+                       reinterpret_cast<const T*>(X), n_in, reinterpret_cast<const T*>(dY), n_out, in_idx, out_idx, \
+                       seg, ibase, chunk, K, c_in, c_out, part)
+#define GSC_DWP_WIDTHS(T)                             \
+    if (c_in <= 16 && c_out <= 16) GSC_DWP_CASE(T, 1, 1); \
+    else if (c_in <= 16) GSC_DWP_CASE(T, 1, 4);       \
+    else if (c_out <= 16) GSC_DWP_CASE(T, 4, 1);      \
+    else GSC_DWP_CASE(T, 4, 4)
+            if (dtype == GSC_F32) {
+                GSC_DWP_WIDTHS(float);
+            } else {
+                GSC_DWP_WIDTHS(uint16_t);
+            }
+#undef GSC_DWP_WIDTHS
+#undef GSC_DWP_CASE
         }
         GSC_LAUNCH_CHECK();
         const int64_t cc = (int64_t)c_in * c_out;

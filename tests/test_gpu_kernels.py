@@ -333,9 +333,11 @@ def test_conv_f32_wide_rows(n, span, region, ca, cb):
 # pairs of an offset: none, one, about a step of 32, about the ring's four steps, about a work item (1024 or
 # 2048 pairs) and several; rows out of range on either side add nothing; more offsets than the items are
 # ordered over (128)
-@pytest.mark.parametrize("ci,co,rep", [(64, 64, 1), (64, 64, 9), (64, 128, 1), (128, 64, 1), (128, 128, 1),
-                                       (256, 256, 1)])
-def test_dw_bf16_pairs(ci, co, rep):
+@pytest.mark.parametrize("ci,co,rep,dtype", [(64, 64, 1, "bf16"), (64, 64, 9, "bf16"), (64, 128, 1, "bf16"),
+                                             (128, 64, 1, "bf16"), (128, 128, 1, "bf16"), (256, 256, 1, "bf16")] +
+                         [(a, b, 1, t) for t in ("f32", "bf16")   # the kernel for any width: 16 and more on a side
+                          for a, b in ((1, 1), (3, 16), (16, 17), (17, 16), (24, 48), (70, 5))])
+def test_dw_pairs(ci, co, rep, dtype):
     from paper_1904_08755_amd import gsc, regions
     sizes = [0, 1, 31, 32, 33, 96, 128, 129, 1024, 1025, 2047, 2048, 2049, 4300, 0] * rep
     K, n_in, n_out = len(sizes), 900, 900
@@ -354,16 +356,17 @@ def test_dw_bf16_pairs(ci, co, rep):
     out_bad[bad.roll(1)] = n_out
     skip = bad | bad.roll(1)
     m = type(km)(in_bad, out_bad, seg, km.gidx, P, n_out, np.zeros((K, 3), np.int32), n_bound=P)
-    X = torch.randn((n_in, ci), generator=g, device=DEV).bfloat16()
-    dY = torch.randn((n_out, co), generator=g, device=DEV).bfloat16()
-    W = torch.zeros((K, ci, co), device=DEV, dtype=torch.bfloat16)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X = torch.randn((n_in, ci), generator=g, device=DEV).to(dt)
+    dY = torch.randn((n_out, co), generator=g, device=DEV).to(dt)
+    W = torch.zeros((K, ci, co), device=DEV, dtype=dt)
     run = lambda: gsc.gsc_sparse_conv_bwd(X, W, dY, m, m, np.arange(K), need_dx=False)[1]
     dW = run()
     for k in range(K):
         a, b = int(seg[k]), int(seg[k + 1])
         keep = ~skip[a:b]
         x, y = X[ii[a:b].long()[keep]].double(), dY[oi[a:b].long()[keep]].double()
-        # products of bf16 are exact in float32; each addition is half an ulp off at most, or one where the
-        # matrix unit cuts off
+        # a product is half an ulp off at most (none in bf16), an addition too, or one where the matrix unit
+        # cuts off
         assert ((dW[k].double() - x.t() @ y).abs() <= (x.abs().t() @ y.abs()) * (b - a + 2) * 2.0 ** -23).all()
     assert torch.equal(dW, run())
