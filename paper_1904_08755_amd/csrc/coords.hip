@@ -78,9 +78,12 @@ static int box_blocks(int64_t n, int64_t cap) {
 // of more rows clears that much before it knows the box, which at 300,000 rows
 // (14 MB) costs about 3 us.  Rooms voxelised at 2 cm have 112 to
 // 120 cells per row, at 4 to 5 cm 20 to 30; boxes past the limit are hashed.
+// Cells are numbered in 32 bits, so no grid has more than kGridMaxCells (from
+// 11 million rows on that is the nearer limit).
 // The environment variable GSC_TABLE_CAP_LIMIT (a test hook for the hashed
 // slots) turns grids off.
 constexpr int64_t kGridCells = 192;
+constexpr int64_t kGridMaxCells = (int64_t)1 << 31;
 constexpr int kSmallPer = 3, kSmallThreads = 1024;               // see k_small
 constexpr int kSmallRows = kSmallThreads * kSmallPer;
 constexpr int kSmallWords = kSmallRows * (int)kGridCells / 32;
@@ -92,7 +95,8 @@ static GridLayout grid_layout(int64_t n, int64_t cap) {
     const int64_t want = n <= kSmallRows ? kSmallWords * (int64_t)sizeof(GridWord) : n * (kGridCells / 4);
     const int64_t room = region - rows - part;
     const bool on = n > 0 && room >= 16 && cap >= 4 * n && !getenv("GSC_TABLE_CAP_LIMIT");
-    g.word_bytes = on ? std::min(want, room) / 16 * 16 : 0;
+    constexpr int64_t most = kGridMaxCells / 32 * (int64_t)sizeof(GridWord);
+    g.word_bytes = on ? std::min(std::min(want, room), most) / 16 * 16 : 0;
     g.max_cells = g.word_bytes / (int64_t)sizeof(GridWord) * 32;
     // the boxes lie behind the words (without a grid anywhere: the slots are set after they have been read)
     g.part = kHeaderBytes + (on ? (size_t)(region - rows - part) : 0);

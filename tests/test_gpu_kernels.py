@@ -171,6 +171,17 @@ def test_grid_limit_of_cells():
                 assert list(zip(i[seg[k]:seg[k + 1]].tolist(), o[seg[k]:seg[k + 1]].tolist())) == pairs
 
 
+def test_grid_cell_numbers_fit():
+    """A box of just over 2^32 cells at 128 cells a row: rows whose cells agree
+    in their low 32 bits are different rows."""
+    from paper_1904_08755_amd import gsc
+    i = torch.arange((1 << 25) + 100, dtype=torch.int64, device=DEV)
+    cell = i * 128 + (i & 127)
+    c = torch.stack([torch.zeros_like(i), cell >> 16, cell & 65535], 1).to(torch.int32)
+    km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, np.zeros((1, 2), np.int32))
+    assert torch.equal(km.in_idx.long(), i) and torch.equal(km.out_idx.long(), i)
+
+
 @pytest.mark.parametrize("n,K", [(300, 2187), (300, 1024), (64 * 65536, 2), (64 * 65536 + 1, 2)])
 def test_kernel_map_scan_limits(n, K):
     """Offsets and groups on both sides of the limits of the per-offset scan:
