@@ -1421,7 +1421,11 @@ int gsc_sparse_conv_bwd(int32_t dtype, const void* X, const void* W, const void*
     int32_t* dw_order =
         ws ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(ws) + 2 * al256((size_t)(K + 1) * sizeof(int64_t)))
            : nullptr;
-    const bool ordered = dtype == GSC_BF16 && dw_tile_bf16_supported(c_in, c_out, dw_ch) && c_in <= 128;
+    // conv_tile.hip's kernels copy 16 bytes at a time and number the rows' bytes in 32 bits; rows that start anywhere
+    // else take the kernels that load them into registers
+    const bool dw_tile = dtype == GSC_BF16 && dw_tile_bf16_supported(c_in, c_out, dw_ch) && aligned16(X) &&
+                         aligned16(dY) && blk_bf16_fits(n_in, c_in) && blk_bf16_fits(n_out, c_out);
+    const bool ordered = dw_tile && c_in <= 128;
     if (!ordered) dw_order = nullptr;
     const dim3 dw_items_grid(ordered ? (unsigned)((dw_items + kDwItemThreads - 1) / kDwItemThreads) : 1u);
     bool dw_items_done = false;
@@ -1502,8 +1506,7 @@ int gsc_sparse_conv_bwd(int32_t dtype, const void* X, const void* W, const void*
             GSC_DW_CASE(16, 16) GSC_DW_CASE(16, 32) GSC_DW_CASE(16, 64) GSC_DW_CASE(32, 16) GSC_DW_CASE(32, 32)
             GSC_DW_CASE(32, 64) GSC_DW_CASE(64, 16) GSC_DW_CASE(64, 32) GSC_DW_CASE(64, 64)
 #undef GSC_DW_CASE
-        } else if (dtype == GSC_BF16 && dw_tile_bf16_supported(c_in, c_out, dw_ch) && blk_bf16_fits(n_in, c_in) &&
-                   blk_bf16_fits(n_out, c_out)) {
+        } else if (dw_tile) {
             int rc = dw_tile_bf16(c_in, c_out, X, n_in, dY, n_out, in_idx, out_idx, seg, ibase, chunk, dw_order, K,
                                   items, part, s);
             if (rc) return rc;

@@ -343,8 +343,9 @@ def test_conv_f32_wide_rows(n, span, region, ca, cb):
 
 # pairs of an offset: none, one, about a step of 32, about the ring's four steps, about a work item (1024 or
 # 2048 pairs) and several; rows out of range on either side add nothing; more offsets than the items are
-# ordered over (128)
-@pytest.mark.parametrize("ci,co,rep,dtype", [(64, 64, 1, "bf16"), (64, 64, 9, "bf16"), (64, 128, 1, "bf16"),
+# ordered over (128); "bf16+1": rows that start 2 bytes past a multiple of 16
+@pytest.mark.parametrize("ci,co,rep,dtype", [(64, 64, 1, "bf16"), (64, 64, 1, "bf16+1"), (64, 128, 1, "bf16+1"),
+                                             (64, 64, 9, "bf16"), (64, 128, 1, "bf16"),
                                              (128, 64, 1, "bf16"), (128, 128, 1, "bf16"), (256, 256, 1, "bf16")] +
                          [(a, b, 1, t) for t in ("f32", "bf16")   # the kernel for any width: 16 and more on a side
                           for a, b in ((1, 1), (3, 16), (16, 17), (17, 16), (24, 48), (70, 5))])
@@ -367,9 +368,10 @@ def test_dw_pairs(ci, co, rep, dtype):
     out_bad[bad.roll(1)] = n_out
     skip = bad | bad.roll(1)
     m = type(km)(in_bad, out_bad, seg, km.gidx, P, n_out, np.zeros((K, 3), np.int32), n_bound=P)
-    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    X = torch.randn((n_in, ci), generator=g, device=DEV).to(dt)
-    dY = torch.randn((n_out, co), generator=g, device=DEV).to(dt)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    shift = int(dtype.endswith("+1"))
+    X = _offset_copy(torch.randn((n_in, ci), generator=g, device=DEV).to(dt), shift)
+    dY = _offset_copy(torch.randn((n_out, co), generator=g, device=DEV).to(dt), shift)
     W = torch.zeros((K, ci, co), device=DEV, dtype=dt)
     run = lambda: gsc.gsc_sparse_conv_bwd(X, W, dY, m, m, np.arange(K), need_dx=False)[1]
     dW = run()
