@@ -628,6 +628,13 @@ k_conv_f32_wide(const float* __restrict__ X, int64_t n_x, const float* __restric
 // counter (nullable) is set to 0 on the way (the input gradient's tile
 // counter, when that pass runs after this kernel).
 constexpr int kDwOrderMaxK = 128;
+// Items of up to kDwSplitMax pairs are halved while there are fewer than
+// kDwSplitItems of them (about one per CU), down to kDwSplitMin pairs: an item
+// is a serial chain (3 to 16 channels over 2,000 rows, 2,430 pairs: the call
+// 80 -> 73 us).  With more items shorter ones cost more than they balance
+// (896,000 pairs of 32 x 32 in items of 512: 312 -> 317 us), and items of 2048
+// pairs (128 channels) gain nothing (480,288 pairs of 64 x 128: 468 -> 471 us).
+constexpr int64_t kDwSplitMax = 1024, kDwSplitMin = 256, kDwSplitItems = 256;
 constexpr int kDwItemThreads = 256;
 
 __global__ void __launch_bounds__(kDwItemThreads) k_dw_items(const int64_t* __restrict__ seg, int K, int64_t ch,
@@ -635,6 +642,8 @@ __global__ void __launch_bounds__(kDwItemThreads) k_dw_items(const int64_t* __re
                                                              int32_t* __restrict__ order, int64_t cap,
                                                              unsigned* counter) {
     __shared__ int64_t base[kMaxKConv + 1];
+    if (ch <= kDwSplitMax)   // uniform
+        for (const int64_t pairs = seg[K] - seg[0]; ch > kDwSplitMin && pairs < kDwSplitItems * ch;) ch /= 2;
     if (threadIdx.x < 64) {   // 64 offsets per round, their item counts scanned with shuffles
         const int lane = threadIdx.x;
         if (counter && lane == 0 && blockIdx.x == 0) *counter = 0u;
@@ -964,7 +973,11 @@ static int64_t dw_chunk(int ci, int co) {
 }
 
 // upper bound of the work items for at most n_pairs pairs
-static int64_t dw_items_bound(int64_t n_pairs, int K, int64_t ch) { return (n_pairs + ch - 1) / ch + K; }
+static int64_t dw_items_bound(int64_t n_pairs, int K, int64_t ch) {
+    // halved items: fewer than 2 kDwSplitItems, each but an offset's last full
+    const int64_t few = ch <= kDwSplitMax ? std::min((n_pairs + kDwSplitMin - 1) / kDwSplitMin, 2 * kDwSplitItems) : 0;
+    return std::max((n_pairs + ch - 1) / ch, few) + K;
+}
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 

@@ -346,12 +346,16 @@ def test_conv_f32_wide_rows(n, span, region, ca, cb):
 # ordered over (128); "bf16+1": rows that start 2 bytes past a multiple of 16
 @pytest.mark.parametrize("ci,co,rep,dtype", [(64, 64, 1, "bf16"), (64, 64, 1, "bf16+1"), (64, 128, 1, "bf16+1"),
                                              (64, 64, 9, "bf16"), (64, 128, 1, "bf16"),
+                                             (64, 64, 0, "bf16"), (64, 128, 0, "bf16"), (128, 128, 0, "bf16"),
+                                             (64, 64, 0, "f32"), (32, 32, 1, "f32"), (3, 16, 0, "f32"),
                                              (128, 64, 1, "bf16"), (128, 128, 1, "bf16"), (256, 256, 1, "bf16")] +
                          [(a, b, 1, t) for t in ("f32", "bf16")   # the kernel for any width: 16 and more on a side
                           for a, b in ((1, 1), (3, 16), (16, 17), (17, 16), (24, 48), (70, 5))])
 def test_dw_pairs(ci, co, rep, dtype):
     from paper_1904_08755_amd import gsc, regions
-    sizes = [0, 1, 31, 32, 33, 96, 128, 129, 1024, 1025, 2047, 2048, 2049, 4300, 0] * rep
+    sizes = [0, 1, 31, 32, 33, 96, 128, 129, 1024, 1025, 2047, 2048, 2049, 4300, 0] * max(rep, 1)
+    if rep == 0:   # enough pairs for items of full size (1024 or 2048)
+        sizes += [256 * (1024 if ci * co <= 64 * 64 else 2048) + 7]
     K, n_in, n_out = len(sizes), 900, 900
     host = np.ascontiguousarray(_rows(3, 50, 3, 6, batch=1))
     c = torch.from_numpy(host).to(DEV)
