@@ -50,11 +50,13 @@ __device__ __forceinline__ bool header_ok(const TableHeader* h, int ncol) {
     return (h->magic == kTableMagic || h->magic == kGridMagic) && h->ncol == ncol && h->status == 0;
 }
 
-// Offsets probed together per lane on a hashed table.  Wide keys take one at a
-// time, so that their path needs no more registers than the others.
-constexpr int kBatch = 5;
-template <typename KeyT>
-constexpr int batch_of() { return sizeof(KeyT) > 8 ? 1 : kBatch; }
+// Offsets probed together per lane on a hashed table: 5 where a block has nine
+// offsets (two rounds, as with 4 for up to eight; 27 offsets of 1 million rows
+// 275 us, with 4 292 us), else 4 (7 and 8 offsets of 1 million rows 117 and
+// 115 us, with 5 123 and 124 us).  Wide keys take one at a time, so that their
+// path needs no more registers than the others.
+template <typename KeyT, int NB>
+constexpr int batch_of() { return sizeof(KeyT) > 8 ? 1 : NB; }
 
 // Key arithmetic in KeyT (uint32_t when the table's keys fit in 32 bits, the
 // usual case, uint64_t up to 62 bits, else the 128-bit wide key).  The packed
@@ -87,7 +89,7 @@ struct KeyOps<u128> {
 // the whole 16-byte slot, so a hit also yields the input row, which goes to
 // nbr[k * n_out + j] (-1 for a miss); hits are counted per 64-row group with
 // a wave ballot.
-template <typename KeyT, typename Offs>
+template <typename KeyT, int NBT, typename Offs>
 __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __restrict__ slots,
                                            const int32_t* __restrict__ out_coords, int64_t n_out, int ncol,
                                            const Offs& offs, int k_begin, int k_end, int64_t G,
@@ -125,7 +127,7 @@ __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __r
     in_b = in_b && (uint32_t)rel[0] <= (uint32_t)span[0];
     const int64_t g = j >> 6;
     const bool writer = __lane_id() == 0 && g < G;
-    constexpr int NB = batch_of<KeyT>();
+    constexpr int NB = batch_of<KeyT, NBT>();
     for (int k0 = k_begin; k0 < k_end; k0 += NB) {
         KeyT key[NB];
         unsigned long long pos[NB];
@@ -206,6 +208,15 @@ __device__ __forceinline__ void count_rows(const TableHeader* h, const Slot* __r
 // the rest), so a lane's loads are one chain of header, row, word and row
 // number, whatever K.
 constexpr int kGridBatch = 9;
+
+// The blocks of one row range and all its offsets run one after another on an
+// XCD where the map is hashed and has more rows than this: they read the same
+// lines of the table, which the XCD's L2 no longer holds once it has gone
+// through all other rows (27 offsets: 300,000 rows 103 -> 88 us, 1 million
+// 323 -> 275; 125 offsets of 1 million rows 1,633 -> 1,195).  With fewer rows,
+// and on a grid's words, the other order was as fast or faster (29 offsets of
+// 100,000 hashed rows 49 us against 52).
+constexpr int64_t kNearRows = 200000;
 
 template <int NC, typename Offs>
 __device__ __forceinline__ void count_rows_grid(const void* table, const int32_t* __restrict__ out_coords, bool vec,
@@ -319,19 +330,30 @@ __global__ void __launch_bounds__(kThreads) k_kmap_count(Offs offs, const void* 
     const Slot* __restrict__ slots = table_slots(table);
     const bool ok = header_ok(h, ncol);
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *err = ok ? 0 : 1;
-    const int64_t j = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
-    const int per = (K + gridDim.y - 1) / gridDim.y, k0 = blockIdx.y * per, k1 = min(K, k0 + per);
+    const int per = (K + gridDim.y - 1) / gridDim.y;
+    unsigned rows = (unsigned)xcd_unit(blockIdx.x, gridDim.x), part = blockIdx.y;
+    if (h->magic != kGridMagic && n_out > kNearRows) {   // uniform
+        const unsigned unit = (unsigned)xcd_unit(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+        rows = unit / gridDim.y;
+        part = unit - rows * gridDim.y;
+    }
+    const int64_t j = (int64_t)rows * kThreads + threadIdx.x;
+    const int k0 = (int)part * per, k1 = min(K, k0 + per);
     // uniform: all lanes take the same path
     if (ok && h->magic == kGridMagic) {
         if (ncol == 4) count_rows_grid<4>(table, out_coords, vec, n_out, ncol, offs, k0, k1, G, cnt, nbr, j);
         else if (ncol == 5) count_rows_grid<5>(table, out_coords, vec, n_out, ncol, offs, k0, k1, G, cnt, nbr, j);
         else count_rows_grid<kMaxCols>(table, out_coords, vec, n_out, ncol, offs, k0, k1, G, cnt, nbr, j);
     } else if (h->total_bits <= 32) {
-        count_rows<uint32_t>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
+        if (per > 8) count_rows<uint32_t, 5>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
+        else count_rows<uint32_t, 4>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
     } else if (h->total_bits <= kNarrowKeyBits) {
-        count_rows<unsigned long long>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
+        if (per > 8)
+            count_rows<unsigned long long, 5>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
+        else
+            count_rows<unsigned long long, 4>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
     } else {
-        count_rows<u128>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
+        count_rows<u128, 1>(h, slots, out_coords, n_out, ncol, offs, k0, k1, G, cnt, nbr, ok, j);
     }
 }
 

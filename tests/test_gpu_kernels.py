@@ -143,6 +143,46 @@ def test_table_forms(name, form, monkeypatch):
         assert up.in_idx.cpu().tolist() == list(range(len(seen)))
 
 
+def _sorted_pairs(src, dst, offs):
+    """[(input rows, output rows)] per offset by search of the sorted packed rows."""
+    lo = torch.minimum(src.amin(0), dst.amin(0)).long() - 8
+    ext = torch.maximum(src.amax(0), dst.amax(0)).long() + 9 - lo
+
+    def pack(r):
+        key = torch.zeros(len(r), dtype=torch.int64, device=r.device)
+        for d in range(r.shape[1]):
+            key = key * ext[d] + (r[:, d].long() - lo[d])
+        return key
+
+    keys, order = pack(src).sort()
+    out = []
+    for o in np.asarray(offs):
+        q = pack(dst + torch.tensor([0, *o.tolist()], dtype=torch.int32, device=dst.device))
+        at = torch.searchsorted(keys, q).clamp(max=len(keys) - 1)
+        hit = (keys[at] == q).nonzero()[:, 0]
+        out.append((order[at[hit]], hit))
+    return out
+
+
+# hashed maps on both sides of the row count from which a row range's blocks run one after another; blocks of 7, 8
+# and 9 offsets (batches of 4 and 5), equal and unequal (8 + 8 + 8 + 5, 5 + 5)
+@pytest.mark.parametrize("region", ["cross3", "cube2", "plane9", "cube3", "list29", "list10"])
+@pytest.mark.parametrize("n", [200000, 200001])
+def test_hashed_map_row_order(n, region, monkeypatch):
+    from paper_1904_08755_amd import gsc, regions
+    monkeypatch.setenv("GSC_TABLE_CAP_LIMIT", str(1 << 40))
+    cube = regions.hypercube(3, 3)
+    offs = {"cross3": regions.hypercross(3, 3), "cube2": regions.hypercube(2, 3), "plane9": cube[9:18], "cube3": cube,
+            "list29": np.concatenate([cube, [[2, 0, 0], [0, -3, 1]]]).astype(np.int32), "list10": cube[:10]}[region]
+    c = torch.from_numpy(np.ascontiguousarray(_rows(n, n, 3, 80))).to(DEV)
+    assert len(c) == n
+    km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, offs)
+    seg = km.seg.tolist()
+    for k, (i, o) in enumerate(_sorted_pairs(c, c, offs)):
+        assert torch.equal(km.in_idx[seg[k]:seg[k + 1]].long(), i)
+        assert torch.equal(km.out_idx[seg[k]:seg[k + 1]].long(), o)
+
+
 @pytest.mark.parametrize("form", ["any", "hash"])
 def test_table_forms_duplicates(form, monkeypatch):
     from paper_1904_08755_amd import gsc
