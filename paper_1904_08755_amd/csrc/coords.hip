@@ -51,58 +51,7 @@ __device__ __forceinline__ void load_row(const int32_t* __restrict__ coords, boo
     for (int c = 0; c < NC; ++c) v[c] = c > 0 && c < ncol ? floor_mul(raw[c], st.s[c], bad) : raw[c];
 }
 
-// The memory of a table for n rows of cap slots: the words of a grid, the box
-// kernel's per-block results, then one row number per row.
-struct GridLayout {
-    int64_t word_bytes;   // words that the build clears, and so the most a grid may use
-    size_t part;          // byte offsets from the table's start
-    size_t rowof;
-    int64_t max_cells;    // 0: hashed slots only
-};
-
-constexpr int kBoxThreads = 512;
-constexpr int kBoxBlocks = 256;                 // at most; four per lane of the wave that combines them
-constexpr int kBoxInts = 4 * kMaxCols + 1;      // lo, hi, or, and per column; out of range
 constexpr int kBoxRows = 4;                     // rows in flight per thread (half as many points)
-
-// blocks of the box kernel; their results fit the slots' memory
-static int box_blocks(int64_t n, int64_t cap) {
-    const int64_t per = kBoxThreads * 2;
-    const int64_t b = std::min((n + per - 1) / per, cap * (int64_t)sizeof(Slot) / (kBoxInts * 4));
-    return (int)std::clamp<int64_t>(b, 1, kBoxBlocks);
-}
-
-// A grid may have kGridCells cells per row (48 bytes of words each: three
-// quarters of the table's memory at its smallest), or, with few rows, as many
-// cells as kSmallRows rows where the table has room for their words.  The build
-// of more rows clears that much before it knows the box, which at 300,000 rows
-// (14 MB) costs about 3 us.  Rooms voxelised at 2 cm have 112 to
-// 120 cells per row, at 4 to 5 cm 20 to 30; boxes past the limit are hashed.
-// Cells are numbered in 32 bits, so no grid has more than kGridMaxCells (from
-// 11 million rows on that is the nearer limit).
-// The environment variable GSC_TABLE_CAP_LIMIT (a test hook for the hashed
-// slots) turns grids off.
-constexpr int64_t kGridCells = 192;
-constexpr int64_t kGridMaxCells = (int64_t)1 << 31;
-constexpr int kSmallPer = 3, kSmallThreads = 1024;               // see k_small
-constexpr int kSmallRows = kSmallThreads * kSmallPer;
-constexpr int kSmallWords = kSmallRows * (int)kGridCells / 32;
-
-static GridLayout grid_layout(int64_t n, int64_t cap) {
-    GridLayout g{};
-    const int64_t region = cap * (int64_t)sizeof(Slot);
-    const int64_t rows = (4 * n + 15) / 16 * 16, part = ((int64_t)box_blocks(n, cap) * kBoxInts * 4 + 15) / 16 * 16;
-    const int64_t want = n <= kSmallRows ? kSmallWords * (int64_t)sizeof(GridWord) : n * (kGridCells / 4);
-    const int64_t room = region - rows - part;
-    const bool on = n > 0 && room >= 16 && cap >= 4 * n && !getenv("GSC_TABLE_CAP_LIMIT");
-    constexpr int64_t most = kGridMaxCells / 32 * (int64_t)sizeof(GridWord);
-    g.word_bytes = on ? std::min(std::min(want, room), most) / 16 * 16 : 0;
-    g.max_cells = g.word_bytes / (int64_t)sizeof(GridWord) * 32;
-    // the boxes lie behind the words (without a grid anywhere: the slots are set after they have been read)
-    g.part = kHeaderBytes + (on ? (size_t)(region - rows - part) : 0);
-    g.rowof = kHeaderBytes + (on ? (size_t)(region - rows) : 0);
-    return g;
-}
 
 // Bounding box of a set of values per column.
 struct Box {
@@ -276,7 +225,7 @@ __global__ void __launch_bounds__(kBoxThreads, NC <= 5 ? 6 : 4) k_box(const int3
         h->capacity = cap;
         h->n = header_n;
         h->total = 0;
-        h->rowof16 = (uint32_t)(g.rowof / 16);
+        h->rowof = (int64_t)g.rowof;
     }
 }
 
@@ -311,7 +260,7 @@ __global__ void __launch_bounds__(kThreads) k_table_empty(TableHeader* h, Slot* 
     for (int c = 0; c < kMaxCols; ++c) {
         h->lo[c] = INT_MAX;
         h->hi[c] = INT_MIN;
-        h->shift[c] = h->bits[c] = h->vary[c] = 0;
+        h->shift[c] = h->bits[c] = 0;
     }
     h->nblk = 0;
     for (int i = 0; i < 3; ++i) h->blk_shift[i] = 0;
@@ -413,7 +362,6 @@ __device__ __forceinline__ void write_layout(TableHeader* h, const BoxPlan& bp, 
         h->hi[c] = in ? bp.hi[c] : INT_MIN;
         h->shift[c] = in ? shift[cc] : 0;
         h->bits[c] = in ? bits[cc] : 0;
-        h->vary[c] = in ? bp.vary[c] : 0;
         h->step[c] = in ? (int8_t)bp.step[c] : 0;
         h->cstride[c] = in ? mul[cc] : 0;
         // the lowest varying key bit of the first three spatial columns that vary (see home_slot)
@@ -616,7 +564,7 @@ __device__ __forceinline__ int find_or_insert(const TableView& tv, const int32_t
 // The row number that a table keeps at place s: a slot of a hash, an entry of
 // a grid's row numbers.
 __device__ __forceinline__ int32_t* row_number(void* table, bool grid, const TableHeader* h, unsigned long long s) {
-    return grid ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + (size_t)h->rowof16 * 16) + s
+    return grid ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + h->rowof) + s
                 : &table_slots(table)[s].val;
 }
 
@@ -811,7 +759,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
         h->capacity = cap;
         h->n = header_n;
         h->total = 0;
-        h->rowof16 = (uint32_t)(g.rowof / 16);
+        h->rowof = (int64_t)g.rowof;
         write_layout<NC>(h, bp, ncol, grid, mul);
     }
     if (bp.bad) return;

@@ -8,6 +8,7 @@
 #include <cstddef>
 
 #include "../../include/gsc.h"
+#include "table_layout.h"
 
 namespace gsc {
 
@@ -34,90 +35,17 @@ void clear_error();
 // ---------------------------------------------------------------------------
 // coordinate hash table (lives in caller memory)
 // ---------------------------------------------------------------------------
-constexpr int kMaxCols = 8;                       // 1 batch column + up to 7 spatial
-constexpr unsigned long long kEmptyKey = ~0ull;    // Slot::key holds <= 62 key bits
-constexpr uint32_t kTableMagic = 0x54435347u;      // "GSCT": hashed slots
-constexpr uint32_t kGridMagic = 0x47435347u;       // "GSCG": occupancy grid of the bounding box
-constexpr size_t kHeaderBytes = 256;
-// A packed key of up to kNarrowKeyBits bits lives in Slot::key alone; a wider
-// one (up to kMaxKeyBits) keeps its low 62 bits there and the rest in
-// Slot::hi, which the inserting thread writes right after claiming the slot
-// (kHiUnset until then).
-constexpr int kNarrowKeyBits = 62;
-constexpr int kMaxKeyBits = 92;
-constexpr int32_t kHiUnset = -1;
 typedef unsigned __int128 u128;
 
-enum : int { ST_DUP = 1, ST_FULL = 2, ST_RANGE = 4 };
-
-struct TableHeader {
-    uint32_t magic;
-    int32_t ncol;          // 1 + D
-    int64_t capacity;      // slots, power of two
-    int64_t n;             // number of keys
-    int32_t status;        // ST_* bits set on the device
-    int32_t total_bits;
-    int32_t lo[kMaxCols];  // bounding box, inclusive
-    int32_t hi[kMaxCols];
-    int32_t shift[kMaxCols];
-    int32_t bits[kMaxCols];
-    int32_t vary[kMaxCols];  // OR over rows of (row XOR first row): the bits that vary per column
-    int32_t nblk;            // spatial columns whose lowest varying key bit selects the slot in a line
-    int32_t blk_shift[3];    // that key bit, per blocked column
-    // a grid table (kGridMagic): cell of a row = sum over columns of
-    // ((x_c - lo_c) >> step_c) * cstride_c
-    int8_t step[kMaxCols];       // lowest varying bit of the column (coordinates of a coarser tensor stride)
-    uint32_t cstride[kMaxCols];
-    uint32_t total;              // occupied cells
-    uint32_t rowof16;            // byte offset of the row numbers from the table's start, / 16
-};
-static_assert(sizeof(TableHeader) <= kHeaderBytes, "header too large");
-
-// A grid table keeps, instead of slots, one bit per cell of the rows' bounding
-// box in words of 32 cells, each with the number of occupied cells that come
-// before it in the (arbitrary, but fixed) order of the row numbers:
-// the row at an occupied cell is rowof[before + occupied cells of the word
-// below it].  A query of an empty cell costs one 8-byte read, a neighbourhood
-// shares words, and a scene's words stay in the XCDs' L2, where the hashed
-// slots of the same rows (64 bytes or more per row) do not.
-struct alignas(8) GridWord {
-    uint32_t bits, before;
-};
 inline __host__ __device__ GridWord* grid_words(void* t) {
     return reinterpret_cast<GridWord*>(reinterpret_cast<char*>(t) + kHeaderBytes);
 }
 inline __host__ __device__ const GridWord* grid_words(const void* t) {
     return reinterpret_cast<const GridWord*>(reinterpret_cast<const char*>(t) + kHeaderBytes);
 }
-// The box of a grid table spans less than this per column, so that a query's
-// distance from the box plus an offset stays within 32 bits.
-constexpr int64_t kGridMaxSpan = (int64_t)1 << 30;
-
 // Place of an occupied cell's row number.
 __device__ __forceinline__ uint32_t grid_place(const GridWord& w, uint32_t cell) {
     return w.before + (uint32_t)__popc(w.bits & ((1u << (cell & 31)) - 1u));
-}
-
-struct alignas(16) Slot {
-    unsigned long long key;
-    int32_t val;
-    int32_t hi;   // key bits 62 and up of a wide key
-};
-static_assert(sizeof(Slot) == 16, "slot must be 16 bytes");
-
-// capacity: a power of two >= 4n (load factor <= 1/4) and >= 64.  The
-// environment variable GSC_TABLE_CAP_LIMIT (a test hook) caps it at the
-// largest power of two >= 64 not above its value, so that a table too small
-// for its rows, and the EFULL it reports, can be exercised; every insert and
-// query still stops after one pass over the slots.
-inline int64_t table_capacity(int64_t n) {
-    int64_t cap = 64;
-    while (cap < 4 * n) cap <<= 1;
-    if (const char* e = getenv("GSC_TABLE_CAP_LIMIT")) {
-        const long long lim = strtoll(e, nullptr, 10);
-        while (cap > 64 && cap > lim) cap >>= 1;
-    }
-    return cap;
 }
 
 inline __host__ __device__ Slot* table_slots(void* t) {

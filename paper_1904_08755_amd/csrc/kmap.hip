@@ -225,7 +225,7 @@ __device__ __forceinline__ void count_rows_grid(const void* table, const int32_t
     const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
     const GridWord* __restrict__ words = grid_words(table);
     const int32_t* __restrict__ rowof =
-        reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + (size_t)h->rowof16 * 16);
+        reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + h->rowof);
     const int D = ncol - 1;
     const bool valid = j < n_out;
     const int64_t jj = valid ? j : 0;

@@ -5,6 +5,8 @@ region lists against the oracle's, since the two are written independently."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -236,3 +238,47 @@ def test_negation_permutation():
     assert np.array_equal(offs[p], -offs)
     assert regions.is_symmetric(regions.hybrid(3, 4))
     assert not regions.is_symmetric(regions.hypercube(2, 3))
+
+
+LAYOUT_MAIN = r"""
+#include <cstdio>
+#include "table_layout.h"
+using namespace gsc;
+int main(int argc, char** argv) {
+    for (int i = 1; i < argc; ++i) {
+        const int64_t n = atoll(argv[i]), cap = table_capacity(n);
+        const GridLayout g = grid_layout(n, cap);
+        TableHeader h{};
+        h.rowof = g.rowof;   // as the kernels set it and read it back
+        printf("%lld %lld %lld %lld %lld %lld\n", (long long)n, (long long)cap, (long long)g.word_bytes,
+               (long long)g.part, (long long)g.max_cells, (long long)h.rowof);
+    }
+}
+"""
+
+
+def table_layouts(sizes, folder):
+    """[(n, slots, word bytes, parts' offset, most cells, the header's row number offset)] from the library's own
+    table_layout.h."""
+    src, exe = os.path.join(folder, "layout.cpp"), os.path.join(folder, "layout")
+    with open(src, "w") as f:
+        f.write(LAYOUT_MAIN)
+    csrc = os.path.join(ROOT, "paper_1904_08755_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-I", csrc, src, "-o", exe], check=True)
+    out = subprocess.run([exe, *map(str, sizes)], check=True, capture_output=True, text=True).stdout
+    return [tuple(map(int, line.split())) for line in out.splitlines()]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_table_layout(L, tmp_path):
+    """A grid's words, the box results and the row numbers follow each other inside the table's memory, and the
+    header holds the row numbers' place, up to the largest row count (a table of 128 GiB)."""
+    sizes = [1, 2, 15, 16, 17, 1200, 3072, 3073, 300_000, 11_184_810, 11_184_811, 2**28, 2**30, 2**30 + 1, 2**31 - 1]
+    for n, cap, words, part, cells, rowof in table_layouts(sizes, str(tmp_path)):
+        total = L.gsc_table_bytes(n)
+        assert total == 256 + 16 * cap and cap >= 4 * n
+        boxes = min(max((n + 1023) // 1024, 1), 256)
+        assert words % 16 == part % 16 == rowof % 16 == 0
+        assert 256 + words <= part and part + boxes * 33 * 4 <= rowof and rowof + 4 * n <= total
+        assert cells == 4 * words <= 2**31
+        assert cells == 2**31 if n > 11_184_810 else cells >= 192 * min(n, 3072) or n < 3073
