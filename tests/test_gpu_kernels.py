@@ -247,6 +247,23 @@ def test_kernel_map_scan_limits(n, K):
 
 
 @pytest.mark.parametrize("form", ["any", "hash"])
+@pytest.mark.parametrize("K", [9 * 65536 + 1, 7**7])
+def test_kernel_map_many_offsets(K, form, monkeypatch):
+    """More offsets than nine for each of the blocks that a launch's second dimension takes."""
+    from paper_1904_08755_amd import gsc
+    if form == "hash":
+        monkeypatch.setenv("GSC_TABLE_CAP_LIMIT", str(1 << 40))
+    c = torch.tensor([[0, 5], [0, 3], [0, 4]], dtype=torch.int32, device=DEV)
+    o = (np.arange(K, dtype=np.int64) - (K - 2)).astype(np.int32)[:, None]   # ..., 0, 1 at the end
+    km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, o, cap_pairs=16)
+    want = {-2: [(1, 0)], -1: [(2, 0), (1, 2)], 0: [(0, 0), (1, 1), (2, 2)], 1: [(2, 1), (0, 2)]}
+    pairs = [p for s in sorted(want) for p in want[s]]
+    assert list(zip(km.in_idx.tolist(), km.out_idx.tolist())) == pairs
+    seg = km.seg.cpu().numpy()
+    assert (seg[:K - 3] == 0).all() and seg[K - 3:].tolist() == [1, 3, 6, 8]
+
+
+@pytest.mark.parametrize("form", ["any", "hash"])
 @pytest.mark.parametrize("n", [1, 200, 3072, 3073, 9000])
 def test_quantize_sizes(n, form, monkeypatch):
     """Voxels, first points, labels and the inverse map by numpy, on both sides
