@@ -161,10 +161,10 @@ template <int CA>
 __device__ __forceinline__ void load_row_frag(const float* __restrict__ X, int64_t row, int q, bool ok,
                                               RowFrag<CA>& a) {
     constexpr int KS = CA / 4;
-    const float4* src = reinterpret_cast<const float4*>(X + row * CA + q * KS);
+    const floatx4u* src = reinterpret_cast<const floatx4u*>(X + row * CA + q * KS);
 #pragma unroll
     for (int i = 0; i < KS / 4; ++i) {
-        const float4 t = src[i];
+        const floatx4 t = src[i];
         a.v[4 * i + 0] = ok ? t.x : 0.f;
         a.v[4 * i + 1] = ok ? t.y : 0.f;
         a.v[4 * i + 2] = ok ? t.z : 0.f;
@@ -291,11 +291,11 @@ k_conv_f32(const float* __restrict__ X, int64_t n_x, const float* __restrict__ W
                 // W[w]^T: lane (r16, q) needs W[w][col][q*KS .. q*KS + KS), contiguous
 #pragma unroll
                 for (int nb = 0; nb < NNB; ++nb) {
-                    const float4* src =
-                        reinterpret_cast<const float4*>(W + ((int64_t)w * CB + nb * 16 + r16) * CA + q * KS);
+                    const floatx4u* src =
+                        reinterpret_cast<const floatx4u*>(W + ((int64_t)w * CB + nb * 16 + r16) * CA + q * KS);
 #pragma unroll
                     for (int i = 0; i < KS / 4; ++i) {
-                        const float4 t = src[i];
+                        const floatx4 t = src[i];
                         bfr[b][4 * i + 0][nb] = t.x;
                         bfr[b][4 * i + 1][nb] = t.y;
                         bfr[b][4 * i + 2][nb] = t.z;
@@ -441,7 +441,7 @@ k_conv_f32_wide(const float* __restrict__ X, int64_t n_x, const float* __restric
     constexpr int RPI = kThreads / CH;   // rows per round of the block
     constexpr int D = 3;
     const int mine = tid / CH;           // the thread's row of each round
-    const floatx4* Xc = reinterpret_cast<const floatx4*>(X) + tid % CH;
+    const floatx4u* Xc = reinterpret_cast<const floatx4u*>(X) + tid % CH;
     int sk[D], spb[D], snp[D];      // the steps whose rows are loaded
     int ik[D], ipb[D], inp[D];      // those whose indices are
     int32_t gr[D][PER], sr[D][PER];
@@ -482,7 +482,8 @@ k_conv_f32_wide(const float* __restrict__ X, int64_t n_x, const float* __restric
     const auto load_w = [&](int k, float (&v)[KS]) __attribute__((always_inline)) {
         const int m = sel(k);
         if constexpr (WT) {
-            const floatx4* src = reinterpret_cast<const floatx4*>(W + ((int64_t)m * CB + wc * 16 + r16) * CA + q * KS);
+            const floatx4u* src =
+                reinterpret_cast<const floatx4u*>(W + ((int64_t)m * CB + wc * 16 + r16) * CA + q * KS);
 #pragma unroll
             for (int i = 0; i < KS / 4; ++i) {
                 const floatx4 t = src[i];
@@ -591,15 +592,14 @@ k_conv_f32_wide(const float* __restrict__ X, int64_t n_x, const float* __restric
     for (int i = tid; i < kWideRows * CB / 4; i += kThreads) {
         const int64_t row = row0 + i / (CB / 4);
         if (row >= n_y) continue;
-        float4 v = reinterpret_cast<const float4*>(acc)[i];
+        floatx4 v = reinterpret_cast<const floatx4*>(acc)[i];
         if constexpr (EP) {
             const int c = 4 * (i % (CB / 4));
-            float* vv = reinterpret_cast<float*>(&v);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                vv[e] = epi_apply(vv[e], ep.scale ? ep.scale[c + e] : 1.f, ep.shift ? ep.shift[c + e] : 0.f, ep.relu);
+                v[e] = epi_apply(v[e], ep.scale ? ep.scale[c + e] : 1.f, ep.shift ? ep.shift[c + e] : 0.f, ep.relu);
         }
-        reinterpret_cast<float4*>(Y)[row * (CB / 4) + i % (CB / 4)] = v;
+        reinterpret_cast<floatx4u*>(Y)[row * (CB / 4) + i % (CB / 4)] = v;
     }
 }
 

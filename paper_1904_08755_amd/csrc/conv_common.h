@@ -11,6 +11,9 @@ namespace gsc {
 constexpr int kMaxKConv = 1024;   // offsets per convolution call
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+// Four floats of a caller's array, which may start at any float: the same 16-byte
+// loads and stores, without the promise of a 16-byte address to the compiler.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
 struct WSel {

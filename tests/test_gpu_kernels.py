@@ -398,6 +398,27 @@ def test_conv_f32_wide_rows(n, span, region, ca, cb):
     assert ((dX.double() - _conv64(dY, T, tk)).abs() <= _conv64(dY.abs(), T.abs(), tk) * bound).all()
 
 
+# features, weights, gradients and outputs that start 4 bytes past a multiple of 16
+@pytest.mark.parametrize("ca,cb", [(16, 32), (32, 32), (64, 64)])
+def test_conv_f32_misaligned(ca, cb):
+    from paper_1904_08755_amd import gsc, regions
+    offs = regions.hypercube(3, 3)
+    c = torch.from_numpy(_rows(5, 300, 3, 8, batch=1)).to(DEV)
+    n, K = len(c), len(offs)
+    km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, offs)
+    g = torch.Generator(DEV).manual_seed(ca + cb)
+    X, dY = torch.randn((n, ca), generator=g, device=DEV), torch.randn((n, cb), generator=g, device=DEV)
+    W = torch.randn((K, ca, cb), generator=g, device=DEV)
+    sel = gsc.negation_permutation(offs)
+    Y, (dX, dW) = gsc.gsc_sparse_conv_fwd(X, W, km), gsc.gsc_sparse_conv_bwd(X, W, dY, km, km, sel)
+    X1, W1, dY1 = (_offset_copy(t, 1) for t in (X, W, dY))
+    assert X1.data_ptr() % 16 == W1.data_ptr() % 16 == dY1.data_ptr() % 16 == 4
+    Y1, dX1 = _offset_copy(torch.full_like(Y, 7.0), 1), _offset_copy(torch.full_like(dX, 7.0), 1)
+    gsc.gsc_sparse_conv_fwd(X1, W1, km, Y=Y1)
+    dW1 = gsc.gsc_sparse_conv_bwd(X1, W1, dY1, km, km, sel, dX=dX1)[1]
+    assert torch.equal(Y1, Y) and torch.equal(dX1, dX) and torch.equal(dW1, dW)
+
+
 # pairs of an offset: none, one, about a step of 32, about the ring's four steps, about a work item (1024 or
 # 2048 pairs) and several; rows out of range on either side add nothing; more offsets than the items are
 # ordered over (128); "bf16+1": rows that start 2 bytes past a multiple of 16
