@@ -1085,12 +1085,12 @@ int affine_act(int dtype, void* Y, int64_t n, int c, const Epilogue& ep, hipStre
 // g = dy where the ReLU passed (y > 0; everywhere without it), dz = g * scale,
 // and per channel dscale = sum over rows of g * z, dshift = sum of g, with z
 // recovered from y as (y - shift) / scale on the rows where g counts.  The
-// division is by one number per channel, so the sums hold g * (y - shift) and
-// their total is divided once (a channel with scale 0 and a row that counts is
-// marked by a NaN partial).  Rows are split into kAbChunks chunks at most; a
-// block sums its chunk per channel (lane l of a channel takes rows l, l + L,
-// ...; the L lanes are added in lane order), the chunk sums go to part, and a
-// second kernel adds them in a fixed order (so the sums are deterministic).
+// division is by one number per channel, so the sums hold g * ((y - shift) p),
+// p the power of two of ab_factor, and their total is divided once.  Rows are
+// split into kAbChunks chunks at most; a block sums its chunk per channel (lane
+// l of a channel takes rows l, l + L, ...; the L lanes are added in lane
+// order), the chunk sums go to part, and a second kernel adds them in a fixed
+// order (so the sums are deterministic).
 //
 // Bound: HBM (two reads and a write of n x c).  A thread owns V adjacent
 // channels (16 bytes) of a row, kAbRows rows in flight, where rows are whole
@@ -1104,6 +1104,22 @@ constexpr int kAbRows = 4;
 static int64_t ab_chunks(int64_t n) {
     const int64_t c = (n + 63) / 64;
     return c < 1 ? 1 : (c > kAbChunks ? kAbChunks : c);
+}
+
+// The factor p of a channel's (y - shift): the power of two that brings |scale|
+// into [1/2, 1) (as near as float32's exponents allow), so (y - shift) p is
+// exact and no larger than the quotient, nor less than half of it: what the
+// sums hold neither overflows nor underflows where the quotients would not
+// (without it a scale of 1e-30 lost gradients below 1e-8).  Scale 0 or NaN: 1
+// / scale, and nothing is left to divide by; the sums are then the quotients'.
+__device__ __forceinline__ bool ab_no_quotient(float scale) { return scale == 0.f || scale != scale; }
+__device__ __forceinline__ float ab_factor(float scale) {
+    if (ab_no_quotient(scale)) return 1.f / scale;
+    const int e = (int)((__float_as_uint(scale) >> 23) & 255u);
+    return __uint_as_float((uint32_t)min(max(253 - e, 1), 254) << 23);
+}
+__device__ __forceinline__ double ab_divisor(float scale) {
+    return ab_no_quotient(scale) ? 1.0 : (double)scale * (double)ab_factor(scale);
 }
 
 // V elements of T as one load or store (16 bytes when V > 1)
@@ -1127,18 +1143,15 @@ __global__ void __launch_bounds__(kAbThreads) k_affine_act_bwd(const T* __restri
     const int lane = t / span, gi = t % span;
     for (int gb = 0; gb < cv; gb += span) {
         const int grp = gb + gi;
-        float gs[V], gt[V], sc[V], sh[V];
-        bool any[V];
+        float gs[V], gt[V], sc[V], sh[V], pre[V];
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-            gs[e] = gt[e] = 0.f;
-            any[e] = false;
-        }
+        for (int e = 0; e < V; ++e) gs[e] = gt[e] = 0.f;
         if (lane < L && grp < cv) {
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 sc[e] = ep.scale ? ep.scale[grp * V + e] : 1.f;
                 sh[e] = ep.shift ? ep.shift[grp * V + e] : 0.f;
+                pre[e] = ab_factor(sc[e]);
             }
             for (int64_t rb = r0 + lane; rb < r1; rb += kAbRows * L) {
                 Vec yv[kAbRows], gv[kAbRows];
@@ -1157,17 +1170,13 @@ __global__ void __launch_bounds__(kAbThreads) k_affine_act_bwd(const T* __restri
                         const float yf = to_f32(yv[i].v[e]);
                         const float g = ep.relu && !(yf > 0.f) ? 0.f : to_f32(gv[i].v[e]);
                         store_out(&o.v[e], g * sc[e]);
-                        const bool counts = g != 0.f;
-                        gs[e] += counts ? g * (yf - sh[e]) : 0.f;
+                        const float z = (yf - sh[e]) * pre[e];
+                        gs[e] = fmaf(g, g != 0.f ? z : 0.f, gs[e]);
                         gt[e] += g;
-                        any[e] = any[e] || counts;
                     }
                     reinterpret_cast<Vec*>(dz)[(rb + i * L) * cv + grp] = o;
                 }
             }
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-                if (sc[e] == 0.f && any[e]) gs[e] = __builtin_nanf("");
         }
         if (part_s) {
             __syncthreads();   // the previous channel groups' sums are read
@@ -1222,9 +1231,7 @@ k_affine_act_bwd_sum(const float* __restrict__ part_s, const float* __restrict__
         }
     }
     if (l == 0 && ch < c) {
-        const float sc = scale ? scale[ch] : 1.f;
-        // scale 0: the sum is NaN when a row counted, else 0
-        if (dscale) dscale[ch] = (float)(sc == 0.f ? sa[0][ci] : sa[0][ci] / (double)sc);
+        if (dscale) dscale[ch] = (float)(sa[0][ci] / ab_divisor(scale ? scale[ch] : 1.f));
         if (dshift) dshift[ch] = (float)sb[0][ci];
     }
 }

@@ -53,6 +53,33 @@ def test_affine_act_bwd_shapes(dtype, n, c, shift):
     assert torch.equal(again[1].nan_to_num(7.0), ds.nan_to_num(7.0)) and torch.equal(again[2], dt)
 
 
+# scales whose quotients are ordinary numbers while their products with a gradient leave float32's range: decayed and
+# grown ones, the smallest normal, a subnormal, the largest binade; and those with no quotient
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_affine_act_bwd_scale_range(dtype):
+    from paper_1904_08755_amd import gsc
+    inf = float("inf")
+    scale = torch.tensor([1e-30, -1e-30, 1e30, -3e38, 2.0 ** -126, 1e-40, 1.0, -0.75, 0.0, -0.0, inf, float("nan")],
+                         device=DEV)
+    n, c = 700, len(scale)
+    g = torch.Generator(DEV).manual_seed(3)
+    Z = torch.randn((n, c), generator=g, device=DEV).clamp(-0.9, 0.9)   # (0.9 x 3e38 stays finite)
+    Y = torch.where(torch.isfinite(scale), Z * scale, Z).to(dtype)
+    Y[:, 8:10] = 0.5   # (y - shift) / 0 is infinite
+    dY = (1e-16 * torch.randn((n, c), generator=g, device=DEV)).to(dtype)
+    dY[:, 9] = dY[:, 9].abs()
+    _, ds, dt = gsc.gsc_affine_act_bwd(Y, dY, scale)
+    y, gr = Y[:, :8].double(), dY[:, :8].double()
+    z = y / scale[:8].double()
+    bound = (n + 512) * 2.0 ** -24
+    assert ((ds[:8].double() - (gr * z).sum(0)).abs() <= (gr * z).abs().sum(0) * (bound + 2.0 ** -22)).all()
+    assert ((dt.double() - dY.double().sum(0)).abs() <= dY.double().abs().sum(0) * bound).all()
+    # sums of infinities of both signs, of one sign, of zeros, of NaN
+    assert torch.isnan(ds[8]) and ds[9] == -inf and ds[10] == 0 and torch.isnan(ds[11])
+    # rows that do not count add nothing to any of them
+    assert (gsc.gsc_affine_act_bwd(Y, torch.zeros_like(dY), scale)[1] == 0).all()
+
+
 # --------------------------------------------------------------------------- #
 # the two forms of a coordinate table: grid and hashed slots
 # --------------------------------------------------------------------------- #
