@@ -173,8 +173,8 @@ size_t gsc_quantize_ws_bytes(int64_t n, int32_t D);
  * in the order of each voxel's first point; *n_out (host) receives their
  * number.  rep (device, capacity n int32): the first point of each voxel (the
  * row whose features it takes).  labels (device, n int32, nullable) and
- * out_labels (device, capacity n, nullable): a voxel's label is its points'
- * common label, or ignore_label when they carry more than one.  inverse
+ * out_labels (device, capacity n, nullable; it may overlap labels): a voxel's
+ * label is its points' common label, or ignore_label when they carry more than one.  inverse
  * (device, n int32, nullable): the voxel row of every point.  out_table
  * (>= gsc_table_bytes(n) bytes) receives the hash table of the voxel
  * coordinates, usable by gsc_kernel_map.  Synchronises `stream` once.

@@ -698,6 +698,15 @@ __global__ void __launch_bounds__(kThreads) k_quant_labels(int64_t n, void* tabl
     if (out_labels && labels[r] != labels[rep[o]]) out_labels[o] = ignore_label;
 }
 
+// out[i] = labels[i] for the table's rows.
+__global__ void __launch_bounds__(kThreads) k_copy_labels(const void* table, int64_t n,
+                                                          const int32_t* __restrict__ labels,
+                                                          int32_t* __restrict__ out) {
+    const TableHeader* h = reinterpret_cast<const TableHeader*>(table);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n && i < h->n && h->status == 0) out[i] = labels[i];
+}
+
 // ---------------------------------------------------------------------------
 // Few rows: the whole build in one block
 // ---------------------------------------------------------------------------
@@ -858,6 +867,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
     if constexpr (MIN) {
         // number the representatives (the first row of each key) in row order
         unsigned long long rep[kSmallPer];
+        int32_t label[kSmallPer];   // read before any is written: out_labels may be the labels' array
 #pragma unroll
         for (int i = 0; i < kSmallPer; ++i) {
             const int r = i * kSmallThreads + t;
@@ -878,9 +888,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
         for (int i = 0; i < kSmallPer; ++i) {
             const int r = i * kSmallThreads + t;
             if (r >= n) continue;
+            if (out.out_labels) label[i] = out.labels[r];
             if (fst[i] == r) number[r] = base[i] + (int32_t)__popcll(rep[i] & lanemask_lt());
             // a point with another label than the voxel's first one (every writer stores the same)
-            else if (out.out_labels && out.labels[r] != out.labels[fst[i]]) differs[fst[i]] = 1;
+            else if (out.out_labels && label[i] != out.labels[fst[i]]) differs[fst[i]] = 1;
         }
         __syncthreads();
 #pragma unroll
@@ -896,7 +907,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
             if (grid) rowof[place[i]] = o;
             else slots[slot[i]].val = o;
             if (out.rep_row) out.rep_row[o] = r;
-            if (out.out_labels) out.out_labels[o] = differs[r] ? out.ignore_label : out.labels[r];
+            if (out.out_labels) out.out_labels[o] = differs[r] ? out.ignore_label : label[i];
         }
     }
 }
@@ -1155,7 +1166,7 @@ size_t gsc_quantize_ws_bytes(int64_t n, int32_t D) {
     b += al((size_t)n * sizeof(int64_t));                    // slot of each row
     b += al((size_t)groups * sizeof(int32_t));               // counts
     b += al((size_t)(groups + 1) * sizeof(int64_t));         // offsets
-    b += 2 * al((size_t)n * sizeof(int32_t));                // label min / max per voxel
+    b += al((size_t)n * sizeof(int32_t));                    // labels, while out_labels is still being read
     b += scan_ws_bytes(groups);
     return b + 256;
 }
@@ -1201,6 +1212,12 @@ int gsc_quantize(const float* points, const int32_t* batch, int64_t n, int32_t D
     w += al((size_t)groups * sizeof(int32_t));
     int64_t* off = reinterpret_cast<int64_t*>(w);
     w += al((size_t)(groups + 1) * sizeof(int64_t));
+    int32_t* own_labels = reinterpret_cast<int32_t*>(w);
+    w += al((size_t)n * sizeof(int32_t));
+    // the voxels' labels are written while the points' are read
+    const uintptr_t l0 = (uintptr_t)labels, o0 = (uintptr_t)out_labels, span = (uintptr_t)n * sizeof(int32_t);
+    const bool overlap = out_labels && l0 < o0 + span && o0 < l0 + span;
+    int32_t* lab = overlap ? own_labels : out_labels;
     const PointsArg pa{points, batch, qc, va};
     int rc = table_enqueue<true>(qc, n, ncol, unit_stride(), pa, out_table, 0, slot_of,
                                  SmallOut{out_coords, rep, inverse, out_labels, labels, ignore_label}, s);
@@ -1208,12 +1225,16 @@ int gsc_quantize(const float* points, const int32_t* batch, int64_t n, int32_t D
     const bool small = n <= kSmallRows;
     if (!small) {
         rc = reps_enqueue(qc, n, ncol, unit_stride(), out_table, slot_of, cnt, off, w, out_coords, rep, labels,
-                          out_labels, s);
+                          lab, s);
         if (rc) return rc;
     }
     if (!small && (out_labels || inverse)) {
         hipLaunchKernelGGL(k_quant_labels, dim3(grid_for(n)), dim3(kThreads), 0, s, n, out_table, slot_of, rep, labels,
-                           ignore_label, inverse, out_labels);
+                           ignore_label, inverse, lab);
+        GSC_LAUNCH_CHECK();
+    }
+    if (!small && overlap) {
+        hipLaunchKernelGGL(k_copy_labels, dim3(grid_for(n)), dim3(kThreads), 0, s, out_table, n, lab, out_labels);
         GSC_LAUNCH_CHECK();
     }
     TableHeader hh;

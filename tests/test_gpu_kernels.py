@@ -321,6 +321,27 @@ def test_quantize_sizes(n, form, monkeypatch):
     assert torch.equal(q2.coords, q.coords) and torch.equal(q2.inverse, q.inverse) and q2.labels is None
 
 
+@pytest.mark.parametrize("n,by", [(3000, 0), (9000, 0), (9000, 40), (9000, -40)])
+def test_quantize_labels_in_place(n, by):
+    """out_labels may be the array of the points' labels, or overlap it."""
+    from paper_1904_08755_amd import gsc
+    rng = np.random.default_rng(n)
+    dev = lambda a: torch.from_numpy(a).to(DEV)
+    pts, labels = dev((rng.random((n, 3)) * 6).astype(np.float32)), dev(rng.integers(0, 2, n).astype(np.int32))
+    want = gsc.gsc_quantize(pts, 0.5, None, labels, ignore_label=-7)
+    L, P, c = gsc.lib(), gsc._ptr, gsc.ctypes
+    buf = torch.empty(n + 100, dtype=torch.int32, device=DEV)
+    inp, out = buf[50:50 + n], buf[50 + by:50 + by + n]
+    inp.copy_(labels)
+    rows, rep = (torch.empty(s, dtype=torch.int32, device=DEV) for s in ((n, 4), (n,)))
+    table, ws = gsc._ws(gsc.gsc_table_bytes(n), DEV), gsc._ws(L.gsc_quantize_ws_bytes(n, 3), DEV)
+    m = c.c_int64(0)
+    gsc._check(L.gsc_quantize(P(pts), None, n, 3, (c.c_float * 3)(0.5, 0.5, 0.5), P(inp), -7, P(rows), c.byref(m),
+                              P(rep), P(out), None, P(table), table.numel(), P(ws), ws.numel(), gsc._stream(None)))
+    assert m.value == len(want.coords) and torch.equal(rows[:m.value], want.coords)
+    assert torch.equal(out[:m.value], want.labels) and (want.labels == -7).any() and (want.labels >= 0).any()
+
+
 # --------------------------------------------------------------------------- #
 # block plans at the edges of the sort's tiles and the counted block tiles
 # --------------------------------------------------------------------------- #
