@@ -379,22 +379,65 @@ __device__ __forceinline__ void write_layout(TableHeader* h, const BoxPlan& bp, 
     h->magic = grid ? kGridMagic : kTableMagic;
 }
 
+// Rows of which many may share a cell (points, coarse strides): what a block's
+// rows do to one word or place is combined in LDS first, so that the block sends
+// one atomic for it.  Atomics on one address take about 13 ns each, one after
+// another, and a hot cell (a sensor's surroundings) has thousands of rows.  The
+// larger the block the better (300,000 points around one spot, quantization in
+// us: each row by itself 305, blocks of 256 242, of 512 218, of 1024 185), but
+// few rows then leave CUs idle (14,490 points: 1024 106.9, 256 103.7).
+constexpr int kMergeThreads = 1024, kMergeFew = 256;
+constexpr int64_t kMergeMany = 65536;   // rows from which blocks of kMergeThreads take them
+// A stride whose cells hold at most this many rows merges only the runs of
+// equal words in a wave: 300,082 sorted 3D rows at stride 2 (8 a cell) 42 us
+// against 52, at stride 4 (64) 40 against 45; at stride 16 52 us against 39, the
+// same rows shuffled 150 against 99; 121,239 4D rows at stride 4 (256) 35.3
+// against 34.4, 100,000 7D rows at stride 2 (128; hashed) 59.8 against 62.2.
+constexpr int64_t kMergeCell = 128;
+
+template <int TB>
+struct MergeTable {
+    static constexpr int kBits = TB == 1024 ? 11 : 9, kSlots = 1 << kBits;
+    static_assert(kSlots == 2 * TB, "two slots per row");
+    uint32_t key[kSlots], val[kSlots];
+    __device__ __forceinline__ void clear(uint32_t v) {   // then a barrier
+#pragma unroll
+        for (int i = threadIdx.x; i < kSlots; i += TB) {
+            key[i] = ~0u;
+            val[i] = v;
+        }
+    }
+    // the entry of k, null when another key has taken its place
+    __device__ __forceinline__ uint32_t* entry(uint32_t k) {
+        const uint32_t s = (k * 0x9e3779b1u) >> (32 - kBits);
+        const uint32_t prev = atomicCAS(&key[s], ~0u, k);
+        return prev == ~0u || prev == k ? &val[s] : nullptr;
+    }
+};
+
 // Second kernel of a build: every block combines the boxes of the first one's
 // blocks and decides the table's form; block 0 writes the header.  A grid:
 // each row sets the bit of its cell, rows of a wave that share a word
 // (neighbours of a sorted row list) in one atomic.
-template <int NC>
-__global__ void __launch_bounds__(kThreads) k_mark(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol,
-                                                   StrideArg st, void* table, int64_t cap, GridLayout g, int parts,
-                                                   int32_t init_val) {
+template <int NC, int MERGE>
+__global__ void __launch_bounds__(MERGE > 0 ? MERGE : kThreads)
+k_mark(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol, StrideArg st, void* table, int64_t cap,
+       GridLayout g, int parts, int32_t init_val) {
+    constexpr int TB = MERGE > 0 ? MERGE : kThreads;
     __shared__ BoxPlan bp;
     TableHeader* h = reinterpret_cast<TableHeader*>(table);
-    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
+    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * TB + threadIdx.x;
+    MergeTable<TB>* merge = nullptr;
+    if constexpr (MERGE > 0) {
+        __shared__ MergeTable<TB> sh;
+        merge = &sh;
+        merge->clear(0u);
+    }
     int32_t v[NC];
     bool unused = false;   // the box kernel has found values outside int32
     load_row<NC>(coords, vec, r < n ? r : 0, ncol, st, v, &unused);   // in flight during the box
     const int32_t* part = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + g.part);
-    for (int c = threadIdx.x >> 6; c <= ncol; c += kThreads / 64) box_column(bp, part, parts, c, ncol);   // a wave per column
+    for (int c = threadIdx.x >> 6; c <= ncol; c += TB / 64) box_column(bp, part, parts, c, ncol);   // a wave per column
     __syncthreads();
     uint32_t mul[NC];
     const bool grid = grid_strides<NC>(bp, ncol, g, mul);
@@ -402,7 +445,7 @@ __global__ void __launch_bounds__(kThreads) k_mark(const int32_t* __restrict__ c
     if (!grid) {   // empty slots, but for those that hold the boxes, which other blocks may still read
         const SlotSpan p = part_slots(g, parts);
         Slot* slots = table_slots(table);
-        for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < cap; i += (int64_t)gridDim.x * kThreads)
+        for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < cap; i += (int64_t)gridDim.x * TB)
             if (i < p.first || i >= p.end) slots[i] = empty_slot(init_val);
         return;
     }
@@ -422,7 +465,19 @@ __global__ void __launch_bounds__(kThreads) k_mark(const int32_t* __restrict__ c
         if ((int)(threadIdx.x & 63) + d < 64 && ow == word) bits |= ob;
     }
     const uint32_t pw = __shfl_up(word, 1, 64);
-    if (r < n && ((threadIdx.x & 63) == 0 || pw != word)) atomicOr(&grid_words(table)[word].bits, bits);
+    const bool first = r < n && ((threadIdx.x & 63) == 0 || pw != word);
+    if constexpr (MERGE > 0) {
+        if (first) {
+            uint32_t* e = merge->entry(word);
+            atomicOr(e ? e : &grid_words(table)[word].bits, bits);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = threadIdx.x; i < merge->kSlots; i += TB)
+            if (merge->key[i] != ~0u) atomicOr(&grid_words(table)[merge->key[i]].bits, merge->val[i]);
+    } else {
+        if (first) atomicOr(&grid_words(table)[word].bits, bits);
+    }
 }
 
 // Third kernel.  A grid: the row numbers' places.  A block takes a share of
@@ -574,11 +629,13 @@ __device__ __forceinline__ int32_t* row_number(void* table, bool grid, const Tab
 // rows with the same key are often neighbouring lanes: only the first lane of
 // each run of equal keys updates the place (its row is the run's smallest)
 // and, in a hash, inserts; the others take its place by a shuffle.
-template <int NC, bool MIN>
-__global__ void __launch_bounds__(kThreads) k_place(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol,
-                                                    StrideArg st, void* table, int64_t* __restrict__ slot_of) {
+template <int NC, bool MIN, int MERGE>
+__global__ void __launch_bounds__(MERGE > 0 ? MERGE : kThreads)
+k_place(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol, StrideArg st, void* table,
+        int64_t* __restrict__ slot_of) {
+    constexpr int TB = MERGE > 0 ? MERGE : kThreads;
     TableHeader* h = reinterpret_cast<TableHeader*>(table);
-    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
+    const int64_t r = xcd_unit(blockIdx.x, gridDim.x) * TB + threadIdx.x;
     const bool valid = r < n;
     const bool grid = h->magic == kGridMagic;   // uniform
     if (h->status & ST_RANGE) {                 // uniform (set before this kernel)
@@ -603,8 +660,24 @@ __global__ void __launch_bounds__(kThreads) k_place(const int32_t* __restrict__ 
             return;
         }
         const uint32_t prev = __shfl_up(place, 1, 64);
-        if (valid && (lane == 0 || prev != place)) atomicMin(&rowof[place], (int32_t)r);
-        if (valid) slot_of[r] = (int64_t)place;
+        if constexpr (MERGE > 0) {   // (all of the block's rows come here)
+            __shared__ MergeTable<TB> merge;
+            merge.clear(INT_MAX);
+            __syncthreads();
+            if (valid && (lane == 0 || prev != place)) {
+                uint32_t* e = merge.entry(place);
+                if (e) atomicMin(e, (uint32_t)r);
+                else atomicMin(&rowof[place], (int32_t)r);
+            }
+            if (valid) slot_of[r] = (int64_t)place;
+            __syncthreads();
+#pragma unroll
+            for (int i = threadIdx.x; i < merge.kSlots; i += TB)
+                if (merge.key[i] != ~0u) atomicMin(&rowof[merge.key[i]], (int32_t)merge.val[i]);
+        } else {
+            if (valid && (lane == 0 || prev != place)) atomicMin(&rowof[place], (int32_t)r);
+            if (valid) slot_of[r] = (int64_t)place;
+        }
         return;
     }
     const TableView tv = table_view(h, ncol);
@@ -970,13 +1043,21 @@ static int table_enqueue_nc(const int32_t* coords, int64_t n, int ncol, const St
     hipLaunchKernelGGL(box, dim3((unsigned)(boxes + clear)), dim3(kBoxThreads), 0, s, coords, vec, n, ncol, st,
                        pa, table, cap, g, boxes, header_n, init);
     GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_mark<NC>, dim3(grid_for(n)), dim3(kThreads), 0, s, coords, vec, n, ncol, st, table, cap, g,
-                       boxes, init);
+    bool merge = MIN && pa.points;
+    for (int64_t c = 1, cell = 1; MIN && c < ncol && !merge; ++c) merge = (cell *= st.s[c]) > kMergeCell;
+    const bool large = n >= kMergeMany;
+    const int tb = !merge ? kThreads : (large ? kMergeThreads : kMergeFew);
+    auto* mark = k_mark<NC, 0>;
+    auto* place = k_place<NC, MIN, 0>;
+    if constexpr (MIN) {
+        if (merge) mark = large ? k_mark<NC, kMergeThreads> : k_mark<NC, kMergeFew>;
+        if (merge) place = large ? k_place<NC, MIN, kMergeThreads> : k_place<NC, MIN, kMergeFew>;
+    }
+    hipLaunchKernelGGL(mark, dim3(grid_for(n, tb)), dim3(tb), 0, s, coords, vec, n, ncol, st, table, cap, g, boxes, init);
     GSC_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_index, dim3(grid_for(n, kIndexThreads)), dim3(kIndexThreads), 0, s, table, g, boxes, init);
     GSC_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_place<NC, MIN>), dim3(grid_for(n)), dim3(kThreads), 0, s, coords, vec, n, ncol, st, table,
-                       slot_of);
+    hipLaunchKernelGGL(place, dim3(grid_for(n, tb)), dim3(tb), 0, s, coords, vec, n, ncol, st, table, slot_of);
     GSC_LAUNCH_CHECK();
     return GSC_OK;
 }

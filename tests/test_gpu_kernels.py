@@ -321,6 +321,46 @@ def test_quantize_sizes(n, form, monkeypatch):
     assert torch.equal(q2.coords, q.coords) and torch.equal(q2.inverse, q.inverse) and q2.labels is None
 
 
+def _first_rows(rows):
+    """(distinct rows in the order of their first ones, first rows, row of each) by numpy."""
+    _, first, inv = np.unique(rows, axis=0, return_index=True, return_inverse=True)
+    order = np.argsort(first)
+    place = np.empty_like(order)
+    place[order] = np.arange(len(order))
+    return rows[first[order]], first[order], place[inv.reshape(-1)]
+
+
+# rows merged per block before they reach the table: on both sides of the sizes of its two block widths and of the
+# most rows a stride's cell may hold unmerged (128); few cells with many rows each, shuffled, and distinct ones
+@pytest.mark.parametrize("n", [4000, 65535, 65536])
+@pytest.mark.parametrize("stride", [(4, 4, 8), (4, 4, 9), (16, 16, 16), (1, 1, 200), (1 << 20, 1, 1)])
+def test_stride_rows_per_cell(n, stride):
+    from paper_1904_08755_amd import gsc
+    rows = _rows(n, n, 3, 60)
+    out, table = gsc.gsc_coords_stride(torch.from_numpy(rows).to(DEV), stride)
+    want, _, _ = _first_rows(np.concatenate([rows[:, :1], rows[:, 1:] // stride * stride], 1))
+    assert np.array_equal(out.cpu().numpy(), want)
+    up = gsc.gsc_kernel_map(table, out, np.zeros((1, 3), np.int32))
+    assert torch.equal(up.in_idx.long(), torch.arange(len(want), device=DEV))
+
+
+@pytest.mark.parametrize("n", [4000, 65535, 65536, 200000])
+def test_quantize_hot_cells(n):
+    """Points most of which share a few voxels, in no order."""
+    from paper_1904_08755_amd import gsc
+    rng = np.random.default_rng(n)
+    pts = np.concatenate([rng.normal(0, 0.05, (n - n // 4, 3)), rng.uniform(-4, 4, (n // 4, 3))]).astype(np.float32)
+    pts = np.ascontiguousarray(rng.permutation(pts))
+    labels = (rng.random(n) < 1e-3).astype(np.int32)
+    q = gsc.gsc_quantize(torch.from_numpy(pts).to(DEV), 0.125, None, torch.from_numpy(labels).to(DEV), ignore_label=9)
+    rows = np.concatenate([np.zeros((n, 1), np.int32), np.floor(pts.astype(np.float64) / 0.125).astype(np.int32)], 1)
+    want, first, inverse = _first_rows(rows)
+    assert np.array_equal(q.coords.cpu().numpy(), want) and np.array_equal(q.rep.cpu().numpy(), first)
+    assert np.array_equal(q.inverse.cpu().numpy(), inverse)
+    ones, count = np.bincount(inverse, labels), np.bincount(inverse)
+    assert np.array_equal(q.labels.cpu().numpy(), np.where(ones == 0, 0, np.where(ones == count, 1, 9)))
+
+
 @pytest.mark.parametrize("n,by", [(3000, 0), (9000, 0), (9000, 40), (9000, -40)])
 def test_quantize_labels_in_place(n, by):
     """out_labels may be the array of the points' labels, or overlap it."""
