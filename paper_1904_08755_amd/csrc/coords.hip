@@ -785,9 +785,13 @@ __global__ void __launch_bounds__(kThreads) k_copy_labels(const void* table, int
 // ---------------------------------------------------------------------------
 // Up to kSmallRows rows, the steps above by one block whose grid words, row
 // numbers and output numbers lie in LDS; MIN also numbers the distinct keys
-// and writes the output rows (as k_rep_count to k_quant_labels do).  Bound:
-// latency.  At 2,000 rows the launches of the separate kernels take 4 to 7 us
-// each, one after another: a build four of them, a strided one seven, a
+// and writes the output rows (as k_rep_count to k_quant_labels do).  A hash is
+// claimed in LDS too: a slot's claim is the row that took it, compared by the
+// rows' keys, and the slots are written once at the end (inserted in global
+// memory, one block's chain of compare-and-swaps made a build of 2,000 rows 25
+// us with narrow keys and 62 with wide ones; here 15 and 28).
+// Bound: latency.  At 2,000 rows the launches of the separate kernels take 4 to
+// 7 us each, one after another: a build four of them, a strided one seven, a
 // quantization eight.
 struct SmallOut {   // MIN
     int32_t *out_coords, *rep_row, *inverse, *out_labels;
@@ -801,13 +805,24 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
                                                          GridLayout g, int64_t header_n, SmallOut out) {
     constexpr int W = kSmallThreads / 64;
     __shared__ BoxPlan bp;
+    __shared__ TableHeader hs;
     __shared__ int32_t sh[kBoxInts * W];
-    __shared__ uint32_t bits[kSmallWords];
-    __shared__ uint16_t before[kSmallWords];
-    __shared__ int32_t first[kSmallRows];    // a grid's row numbers
+    // a grid: its words; a hash: the slots' claims (kNoClaim or a row), the rows' keys
+    constexpr int kWordMem = kSmallWords * (int)(sizeof(uint32_t) + sizeof(uint16_t));
+    constexpr int kClaimMem = kSmallSlots * (int)sizeof(uint32_t);
+    constexpr int kKeyMem = kSmallRows * (int)(sizeof(unsigned long long) + sizeof(int32_t));
+    __shared__ __attribute__((aligned(16))) unsigned char mem[kWordMem > kClaimMem + kKeyMem ? kWordMem : kClaimMem + kKeyMem];
+    uint32_t* const bits = reinterpret_cast<uint32_t*>(mem);
+    uint16_t* const before = reinterpret_cast<uint16_t*>(mem + kSmallWords * sizeof(uint32_t));
+    uint32_t* const claim = reinterpret_cast<uint32_t*>(mem);
+    unsigned long long* const klo = reinterpret_cast<unsigned long long*>(mem + kClaimMem);
+    int32_t* const khi = reinterpret_cast<int32_t*>(mem + kClaimMem + kSmallRows * sizeof(unsigned long long));
+    constexpr uint32_t kNoClaim = ~0u;
+    __shared__ int32_t first[kSmallRows];    // a grid's row numbers; a hash: the smallest row of a claim's key
     __shared__ int32_t number[kSmallRows];   // output row of a representative, by its input row
     __shared__ uint8_t differs[MIN ? kSmallRows : 1];
     __shared__ int32_t wsum[W * kSmallPer];
+    __shared__ int32_t failed;               // ST_DUP, ST_FULL
     TableHeader* h = reinterpret_cast<TableHeader*>(table);
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     int32_t v[kSmallPer][NC];
@@ -836,17 +851,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
     __syncthreads();
     uint32_t mul[NC];
     const bool grid = grid_strides<NC>(bp, ncol, g, mul);   // (max_cells fits the words in LDS)
-    if (t == 0) {
-        h->ncol = ncol;
-        h->capacity = cap;
-        h->n = header_n;
-        h->total = 0;
-        h->rowof = (int64_t)g.rowof;
-        write_layout<NC>(h, bp, ncol, grid, mul);
+    if (t == 0) {   // the header; the table's copy is written when total and status are known
+        hs.ncol = ncol;
+        hs.capacity = cap;
+        hs.n = header_n;
+        hs.total = 0;
+        hs.rowof = (int64_t)g.rowof;
+        write_layout<NC>(&hs, bp, ncol, grid, mul);
+        if (bp.bad) *h = hs;
     }
     if (bp.bad) return;
     int32_t place[kSmallPer], fst[kSmallPer];
-    unsigned long long slot[kSmallPer];
     Slot* slots = table_slots(table);
     int32_t* rowof = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + g.rowof);
     if (grid) {
@@ -889,8 +904,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
             run += (uint32_t)__popc(bits[i]);
         }
         if (t == 0) {
-            h->total = total;
-            if (!MIN && total != (uint32_t)n) h->status |= ST_DUP;   // fewer cells than rows: a row occurs twice
+            hs.total = total;
+            if (!MIN && total != (uint32_t)n) hs.status |= ST_DUP;   // fewer cells than rows: a row occurs twice
+            *h = hs;
         }
         __syncthreads();
         GridWord* words = grid_words(table);
@@ -910,32 +926,72 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
 #pragma unroll
         for (int i = 0; i < kSmallPer; ++i) fst[i] = first[place[i]];
     } else {
-        for (int64_t i = t; i < cap; i += kSmallThreads) slots[i] = empty_slot(MIN ? INT_MAX : -1);
-        __threadfence();   // the header and the empty slots, before other waves use them
+        for (int i = t; i < (int)cap; i += kSmallThreads) claim[i] = kNoClaim;
+        for (int i = t; i < n; i += kSmallThreads) first[i] = INT_MAX;
+        if (t == 0) failed = 0;
         __syncthreads();
-        if (h->status & ST_RANGE) return;   // uniform: set by write_layout only
-        const TableView tv = table_view(h, ncol);
-        const int total_bits = h->total_bits;
+        if (hs.status & ST_RANGE) {   // uniform: set by write_layout only
+            if (t == 0) *h = hs;
+            return;
+        }
+        const TableView tv = table_view(&hs, ncol);
+        const bool wide = hs.total_bits > kNarrowKeyBits;   // uniform
+        uint32_t home[kSmallPer];
 #pragma unroll
         for (int i = 0; i < kSmallPer; ++i) {
             const int r = i * kSmallThreads + t;
-            slot[i] = 0;
             if (r >= n) continue;
-            const int res = find_or_insert<NC>(tv, v[i], total_bits, h, slots, &slot[i]);
-            if (MIN) {
-                if (res) atomicMin(&slots[slot[i]].val, r);
+            if (wide) {   // (a key outside the box cannot happen)
+                u128 key;
+                pack_key_wide<NC>(tv, v[i], &key);
+                klo[r] = wide_lo(key);
+                khi[r] = wide_hi(key);
+                home[i] = (uint32_t)home_slot_wide(tv.sh, key);
             } else {
-                if (res == 1) slots[slot[i]].val = r;
-                if (res == 2) atomicOr(&h->status, ST_DUP);
+                unsigned long long key;
+                pack_key<NC>(tv, v[i], &key);
+                klo[r] = key;
+                khi[r] = kHiUnset;
+                home[i] = (uint32_t)home_slot(tv.sh, key);
             }
         }
-        if (!MIN) return;
-        __threadfence();
         __syncthreads();
-        if (__hip_atomic_load(&h->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;   // full
+        const uint32_t mask = (uint32_t)cap - 1u;
 #pragma unroll
-        for (int i = 0; i < kSmallPer; ++i)
-            fst[i] = __hip_atomic_load(&slots[slot[i]].val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int r = i * kSmallThreads + t;
+            place[i] = 0;
+            if (r >= n) continue;
+            const unsigned long long lo = klo[r];
+            const int32_t hi = khi[r];
+            uint32_t s = home[i], owner = kNoClaim;
+            for (uint32_t step = 0; step <= mask; ++step, s = (s + 1) & mask) {
+                const uint32_t prev = atomicCAS(&claim[s], kNoClaim, (uint32_t)r);
+                if (prev == kNoClaim || (klo[prev] == lo && khi[prev] == hi)) {
+                    owner = prev == kNoClaim ? (uint32_t)r : prev;
+                    break;
+                }
+            }
+            if (owner == kNoClaim) atomicOr(&failed, ST_FULL);
+            else if (MIN) atomicMin(&first[owner], r);
+            else if (owner != (uint32_t)r) atomicOr(&failed, ST_DUP);
+            if (owner != kNoClaim) place[i] = (int32_t)owner;
+        }
+        __syncthreads();
+        if (t == 0) {
+            hs.status |= failed;
+            *h = hs;
+        }
+        if (!MIN) {
+            for (int i = t; i < (int)cap; i += kSmallThreads) {
+                const uint32_t c = claim[i];
+                slots[i] = c == kNoClaim ? empty_slot(-1) : Slot{klo[c], (int32_t)c, khi[c]};
+            }
+            return;
+        }
+        if (failed) return;   // full
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) fst[i] = first[place[i]];
     }
     if constexpr (MIN) {
         // number the representatives (the first row of each key) in row order
@@ -978,9 +1034,13 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
             for (int c = 0; c < NC; ++c)
                 if (c < ncol) out.out_coords[(int64_t)o * ncol + c] = v[i][c];
             if (grid) rowof[place[i]] = o;
-            else slots[slot[i]].val = o;
             if (out.rep_row) out.rep_row[o] = r;
             if (out.out_labels) out.out_labels[o] = differs[r] ? out.ignore_label : label[i];
+        }
+        if (grid) return;
+        for (int i = t; i < (int)cap; i += kSmallThreads) {
+            const uint32_t c = claim[i];
+            slots[i] = c == kNoClaim ? empty_slot(INT_MAX) : Slot{klo[c], number[first[c]], khi[c]};
         }
     }
 }

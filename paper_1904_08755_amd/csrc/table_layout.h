@@ -118,6 +118,8 @@ constexpr int64_t kGridMaxCells = (int64_t)1 << 31;
 constexpr int kSmallPer = 3, kSmallThreads = 1024;               // see k_small
 constexpr int kSmallRows = kSmallThreads * kSmallPer;
 constexpr int kSmallWords = kSmallRows * (int)kGridCells / 32;
+constexpr int kSmallSlots = 16384;                               // table_capacity(kSmallRows)
+static_assert(kSmallSlots >= 4 * kSmallRows && kSmallSlots / 2 < 4 * kSmallRows, "slots of kSmallRows rows");
 
 inline GridLayout grid_layout(int64_t n, int64_t cap) {
     GridLayout g{};
