@@ -37,12 +37,15 @@ template <int NC>
 __device__ __forceinline__ void load_row(const int32_t* __restrict__ coords, bool vec, int64_t r, int ncol,
                                          const StrideArg& st, int32_t* v, bool* bad) {
     int32_t raw[NC];
-    if (NC == 4 && vec) {   // uniform: rows of four columns from a 16-byte aligned array
-        const int4 q = reinterpret_cast<const int4*>(coords)[r];
-        raw[0] = q.x;
-        raw[1 % NC] = q.y;
-        raw[2 % NC] = q.z;
-        raw[3 % NC] = q.w;
+    if (NC % 4 == 0 && vec) {   // uniform: rows of four or eight columns from a 16-byte aligned array
+#pragma unroll
+        for (int i = 0; i < NC / 4; ++i) {
+            const int4 q = reinterpret_cast<const int4*>(coords)[r * (NC / 4) + i];
+            raw[4 * i] = q.x;
+            raw[(4 * i + 1) % NC] = q.y;
+            raw[(4 * i + 2) % NC] = q.z;
+            raw[(4 * i + 3) % NC] = q.w;
+        }
     } else {
 #pragma unroll
         for (int c = 0; c < NC; ++c) raw[c] = c < ncol ? coords[r * ncol + c] : 0;
@@ -272,32 +275,26 @@ struct BoxPlan {
     int32_t bad;
 };
 
-// Column c of the box of all rows from that of `count` parts (c == ncol: the
+// Column c of the box of all rows from that of `count` parts (with column 0 the
 // range flag), by one wave: four parts per lane, then the lanes.
-__device__ __forceinline__ void box_column(BoxPlan& bp, const int32_t* part, int count, int c, int ncol) {
+__device__ __forceinline__ void box_column(BoxPlan& bp, const int32_t* part, int count, int c) {
     const int lane = threadIdx.x & 63;
     constexpr int B = kBoxBlocks / 64;
-    const int f0 = c < ncol ? 4 * c : kBoxInts - 4;   // the range flag is the last field
-    int32_t f[4][B];
+    int32_t f[4][B], bad = 0;
 #pragma unroll
     for (int i = 0; i < B; ++i) {
         const int at = min(64 * i + lane, count - 1);   // (a repeated part changes nothing)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f[e][i] = c < ncol || e == 3 ? part[(f0 + e) * count + at] : 0;
+        for (int e = 0; e < 4; ++e) f[e][i] = part[(4 * c + e) * count + at];
+        if (c == 0) bad |= part[(kBoxInts - 1) * count + at];   // uniform
     }
-    int32_t lo = f[0][0], hi = f[1][0], all_or = f[2][0], all_and = f[3][0], bad = f[3][0];
+    int32_t lo = f[0][0], hi = f[1][0], all_or = f[2][0], all_and = f[3][0];
 #pragma unroll
     for (int i = 1; i < B; ++i) {
         lo = min(lo, f[0][i]);
         hi = max(hi, f[1][i]);
         all_or |= f[2][i];
         all_and &= f[3][i];
-        bad |= f[3][i];
-    }
-    if (c == ncol) {   // uniform
-        const bool any = __any(bad != 0);
-        if (lane == 0) bp.bad = any;
-        return;
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
@@ -306,11 +303,13 @@ __device__ __forceinline__ void box_column(BoxPlan& bp, const int32_t* part, int
         all_or |= __shfl_xor(all_or, d, 64);
         all_and &= __shfl_xor(all_and, d, 64);
     }
+    const bool any = __any(bad != 0);
     if (lane == 0) {
         bp.lo[c] = lo;
         bp.hi[c] = hi;
         bp.vary[c] = all_or ^ all_and;
         bp.step[c] = all_or != all_and ? __ffs(all_or ^ all_and) - 1 : 0;
+        if (c == 0) bp.bad = any;
     }
 }
 
@@ -437,7 +436,7 @@ k_mark(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol, Stride
     bool unused = false;   // the box kernel has found values outside int32
     load_row<NC>(coords, vec, r < n ? r : 0, ncol, st, v, &unused);   // in flight during the box
     const int32_t* part = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + g.part);
-    for (int c = threadIdx.x >> 6; c <= ncol; c += TB / 64) box_column(bp, part, parts, c, ncol);   // a wave per column
+    for (int c = threadIdx.x >> 6; c < ncol; c += TB / 64) box_column(bp, part, parts, c);   // a wave per column
     __syncthreads();
     uint32_t mul[NC];
     const bool grid = grid_strides<NC>(bp, ncol, g, mul);
@@ -847,7 +846,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(const int32_t* __restri
     box_wave<NC>(x, ncol);
     if (lane == 0) box_store<NC>(x, ncol, sh, W, wave);
     __syncthreads();
-    for (int c = wave; c <= ncol; c += W) box_column(bp, sh, W, c, ncol);
+    for (int c = wave; c < ncol; c += W) box_column(bp, sh, W, c);
     __syncthreads();
     uint32_t mul[NC];
     const bool grid = grid_strides<NC>(bp, ncol, g, mul);   // (max_cells fits the words in LDS)
@@ -1051,8 +1050,10 @@ static unsigned grid_for(int64_t n, int per = kThreads) {
     return (unsigned)g;
 }
 
-// rows that load as one 16-byte word each
-static bool rows_vec(const int32_t* coords, int ncol) { return ncol == 4 && ((uintptr_t)coords & 15) == 0; }
+// rows that load as whole 16-byte words
+static bool rows_vec(const int32_t* coords, int ncol) {
+    return (ncol == 4 || ncol == 8) && ((uintptr_t)coords & 15) == 0;
+}
 
 static int read_status(const void* table, hipStream_t s, TableHeader* out) {
     GSC_HIP(hipMemcpyAsync(out, table, sizeof(TableHeader), hipMemcpyDeviceToHost, s));

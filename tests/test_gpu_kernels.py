@@ -170,6 +170,22 @@ def test_table_forms(name, form, monkeypatch):
         assert up.in_idx.cpu().tolist() == list(range(len(seen)))
 
 
+@pytest.mark.parametrize("name", ["sparse_3d", "past_block_3d", "seven_7d", "big_seven_7d"])
+def test_table_rows_misaligned(name):
+    """Rows of four and eight columns that start 4 bytes past a multiple of 16."""
+    from paper_1904_08755_amd import gsc, regions
+    c = torch.from_numpy(GRID_ROWS[name]).to(DEV)
+    c1 = _offset_copy(c, 1)
+    assert c.data_ptr() % 16 == 0 and c1.data_ptr() % 16 == 4
+    offs = regions.hypercross(3, c.shape[1] - 1)
+    out, table = gsc.gsc_coords_stride(c, 2)
+    out1, table1 = gsc.gsc_coords_stride(c1, 2)
+    assert torch.equal(out, out1)
+    for t, t1, u in ((gsc.gsc_coords_build(c), gsc.gsc_coords_build(c1), c), (table, table1, out)):
+        m, m1 = gsc.gsc_kernel_map(t, u, offs), gsc.gsc_kernel_map(t1, _offset_copy(u, 1), offs)
+        assert m.n_pairs >= len(u) and torch.equal(m.in_idx, m1.in_idx) and torch.equal(m.out_idx, m1.out_idx)
+
+
 def _sorted_pairs(src, dst, offs):
     """[(input rows, output rows)] per offset by search of the sorted packed rows."""
     lo = torch.minimum(src.amin(0), dst.amin(0)).long() - 8
