@@ -265,7 +265,8 @@ def test_grid_cell_numbers_fit():
     assert torch.equal(km.in_idx.long(), i) and torch.equal(km.out_idx.long(), i)
 
 
-@pytest.mark.parametrize("n,K", [(300, 2187), (300, 1024), (64 * 65536, 2), (64 * 65536 + 1, 2)])
+@pytest.mark.parametrize("n,K", [(300, 2187), (300, 1024), (64 * 65536, 2), (64 * 65536 + 1, 2), (64 * 8192, 2),
+                                 (64 * 8192 + 1, 2)])
 def test_kernel_map_scan_limits(n, K):
     """Offsets and groups on both sides of the limits of the per-offset scan:
     rows on a line, offsets along it, so offset s pairs row j with j + s."""
