@@ -628,22 +628,25 @@ k_conv_f32_wide(const float* __restrict__ X, int64_t n_x, const float* __restric
 // counter (nullable) is set to 0 on the way (the input gradient's tile
 // counter, when that pass runs after this kernel).
 constexpr int kDwOrderMaxK = 128;
-// Items of up to kDwSplitMax pairs are halved while there are fewer than
-// kDwSplitItems of them (about one per CU), down to kDwSplitMin pairs: an item
-// is a serial chain (3 to 16 channels over 2,000 rows, 2,430 pairs: the call
-// 80 -> 73 us).  With more items shorter ones cost more than they balance
-// (896,000 pairs of 32 x 32 in items of 512: 312 -> 317 us), and items of 2048
-// pairs (128 channels) gain nothing (480,288 pairs of 64 x 128: 468 -> 471 us).
+// Items of up to kDwSplitMax pairs, and those of any size of the float32 kernel
+// for any width, are halved while they give fewer than kDwSplitItems workgroups
+// (about one per CU; an item has one for each 64 x 64 tile of dW), down to
+// kDwSplitMin pairs: an item is a serial chain (3 to 16 channels over 2,000
+// rows, 2,430 pairs: the call 80 -> 73 us; 96 x 96 over the same rows the weight
+// gradient 94 -> 23 us).  With more items shorter ones cost more than they
+// balance (896,000 pairs of 32 x 32 in items of 512: 312 -> 317 us), and bf16
+// items of 2048 pairs (128 channels) gain nothing (480,288 pairs of 64 x 128:
+// 468 -> 471 us).
 constexpr int64_t kDwSplitMax = 1024, kDwSplitMin = 256, kDwSplitItems = 256;
 constexpr int kDwItemThreads = 256;
 
-__global__ void __launch_bounds__(kDwItemThreads) k_dw_items(const int64_t* __restrict__ seg, int K, int64_t ch,
+__global__ void __launch_bounds__(kDwItemThreads) k_dw_items(const int64_t* __restrict__ seg, int K, int64_t ch, int64_t split,
                                                              int64_t* __restrict__ ibase, int64_t* __restrict__ chunk,
                                                              int32_t* __restrict__ order, int64_t cap,
                                                              unsigned* counter) {
     __shared__ int64_t base[kMaxKConv + 1];
-    if (ch <= kDwSplitMax)   // uniform
-        for (const int64_t pairs = seg[K] - seg[0]; ch > kDwSplitMin && pairs < kDwSplitItems * ch;) ch /= 2;
+    // split: items below which they are halved (uniform)
+    for (const int64_t pairs = seg[K] - seg[0]; ch > kDwSplitMin && pairs < split * ch;) ch /= 2;
     if (threadIdx.x < 64) {   // 64 offsets per round, their item counts scanned with shuffles
         const int lane = threadIdx.x;
         if (counter && lane == 0 && blockIdx.x == 0) *counter = 0u;
@@ -972,11 +975,18 @@ static int64_t dw_chunk(int ci, int co) {
     return t <= 1 ? 1024 : (t <= 4 ? 2048 : (t <= 16 ? 4096 : 8192));
 }
 
-// upper bound of the work items for at most n_pairs pairs
-static int64_t dw_items_bound(int64_t n_pairs, int K, int64_t ch) {
-    // halved items: fewer than 2 kDwSplitItems, each but an offset's last full
-    const int64_t few = ch <= kDwSplitMax ? std::min((n_pairs + kDwSplitMin - 1) / kDwSplitMin, 2 * kDwSplitItems) : 0;
-    return std::max((n_pairs + ch - 1) / ch, few) + K;
+// items below which k_dw_items halves them (where it does)
+static int64_t dw_split_items(int ci, int co) { return (kDwSplitItems + dw_tiles(ci, co) - 1) / dw_tiles(ci, co); }
+
+// upper bound of the work items for at most n_pairs pairs (of either dtype: the
+// workspace's size; or, with split false, of a kernel whose items are not
+// halved: its grid, as workgroups without an item push the others together on
+// the same CUs: bf16 96 x 96, 20 items in a grid for 129, 123 -> 156 us)
+static int64_t dw_items_bound(int64_t n_pairs, int K, int ci, int co, bool split = true) {
+    const int64_t ch = dw_chunk(ci, co), full = (n_pairs + ch - 1) / ch;
+    if (!split) return full + K;
+    // halved items: fewer than 2 dw_split_items, each but an offset's last full
+    return std::max(full, std::min((n_pairs + kDwSplitMin - 1) / kDwSplitMin, 2 * dw_split_items(ci, co))) + K;
 }
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -1399,7 +1409,7 @@ int gsc_sparse_conv_fwd_affine(int32_t dtype, const void* X, int64_t n_in, int32
 // Workspace of the backward pass: the weight gradient's chunk tables and
 // partial sums, then the tile counter of the input gradient's tile engine.
 static size_t bwd_counter_offset(int64_t n_pairs, int32_t c_in, int32_t c_out, int32_t K) {
-    const int64_t items = dw_items_bound(n_pairs, K, dw_chunk(c_in, c_out));
+    const int64_t items = dw_items_bound(n_pairs, K, c_in, c_out);
     return 2 * al256((size_t)(K + 1) * sizeof(int64_t)) + al256((size_t)items * sizeof(int32_t)) +
            al256((size_t)items * c_in * c_out * sizeof(float));
 }
@@ -1437,7 +1447,10 @@ int gsc_sparse_conv_bwd(int32_t dtype, const void* X, const void* W, const void*
     int64_t* dw_chunks =
         ws ? reinterpret_cast<int64_t*>(reinterpret_cast<char*>(ws) + al256((size_t)(K + 1) * sizeof(int64_t)))
            : nullptr;
-    const int64_t dw_items = dw_items_bound(n_pairs < 0 ? 0 : n_pairs, K, dw_ch);
+    const int64_t dw_room = dw_items_bound(n_pairs < 0 ? 0 : n_pairs, K, c_in, c_out);   // what ws holds
+    const int64_t dw_split =
+        dw_ch <= kDwSplitMax || (dtype == GSC_F32 && !dw_f32_specialised(c_in, c_out)) ? dw_split_items(c_in, c_out) : 0;
+    const int64_t dw_items = dw_items_bound(n_pairs < 0 ? 0 : n_pairs, K, c_in, c_out, dw_split > 0);
     int32_t* dw_order =
         ws ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(ws) + 2 * al256((size_t)(K + 1) * sizeof(int64_t)))
            : nullptr;
@@ -1478,8 +1491,8 @@ int gsc_sparse_conv_bwd(int32_t dtype, const void* X, const void* W, const void*
                     counter = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(ws) +
                                                           bwd_counter_offset(n_pairs, c_in, c_out, K));
                 if (counter && dW) {   // one small launch: the weight gradient's items and the tile counter
-                    hipLaunchKernelGGL(k_dw_items, dw_items_grid, dim3(kDwItemThreads), 0, s, seg, K, dw_ch, dw_ibase,
-                                       dw_chunks, dw_order, dw_items, counter);
+                    hipLaunchKernelGGL(k_dw_items, dw_items_grid, dim3(kDwItemThreads), 0, s, seg, K, dw_ch, dw_split,
+                                       dw_ibase, dw_chunks, dw_order, dw_items, counter);
                     GSC_LAUNCH_CHECK();
                     dw_items_done = true;
                 }
@@ -1510,10 +1523,10 @@ int gsc_sparse_conv_bwd(int32_t dtype, const void* X, const void* W, const void*
         int64_t* ibase = dw_ibase;
         int64_t* chunk = dw_chunks;
         float* part = reinterpret_cast<float*>(w + 2 * al256((size_t)(K + 1) * sizeof(int64_t)) +
-                                               al256((size_t)items * sizeof(int32_t)));
+                                               al256((size_t)dw_room * sizeof(int32_t)));
         if (!dw_items_done) {
-            hipLaunchKernelGGL(k_dw_items, dw_items_grid, dim3(kDwItemThreads), 0, s, seg, K, dw_ch, ibase, chunk, dw_order,
-                               dw_items, (unsigned*)nullptr);
+            hipLaunchKernelGGL(k_dw_items, dw_items_grid, dim3(kDwItemThreads), 0, s, seg, K, dw_ch, dw_split, ibase, chunk,
+                               dw_order, dw_items, (unsigned*)nullptr);
             GSC_LAUNCH_CHECK();
         }
         if (dtype == GSC_F32 && dw_f32_specialised(c_in, c_out)) {

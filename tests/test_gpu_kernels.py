@@ -532,6 +532,9 @@ def test_conv_f32_misaligned(ca, cb):
                                              (64, 64, 0, "bf16"), (64, 128, 0, "bf16"), (128, 128, 0, "bf16"),
                                              (64, 64, 0, "f32"), (32, 32, 1, "f32"), (3, 16, 0, "f32"),
                                              (128, 64, 1, "bf16"), (128, 128, 1, "bf16"), (256, 256, 1, "bf16")] +
+                         # the same with several tiles of 64 x 64: halved items, and items of full size
+                         [(96, 64, 1, "f32"), (96, 96, 1, "f32"), (130, 70, 1, "f32"), (96, 96, 0, "f32"),
+                          (96, 96, 1, "bf16")] +
                          [(a, b, 1, t) for t in ("f32", "bf16")   # the kernel for any width: 16 and more on a side
                           for a, b in ((1, 1), (3, 16), (16, 17), (17, 16), (24, 48), (70, 5))])
 def test_dw_pairs(ci, co, rep, dtype):
