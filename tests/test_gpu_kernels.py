@@ -237,21 +237,42 @@ def test_table_forms_duplicates(form, monkeypatch):
     assert e.value.code == gsc.GSC_EDUP
 
 
-def test_grid_limit_of_cells():
-    """Boxes on both sides of the most cells a grid may have (64 KiB of words
-    for few rows): the same map."""
+def _most_cells(n):
+    """Cells of the largest grid over n rows, as table_layout.h sizes it."""
+    cap = 64
+    while cap < 4 * n:
+        cap *= 2
+    up16 = lambda b: (b + 15) // 16 * 16
+    boxes = min(max((n + 1023) // 1024, 1), 256)
+    room = 16 * cap - up16(4 * n) - up16(boxes * 33 * 4)
+    return 4 * (min(18432 * 8 if n <= 3072 else 48 * n, room, 2**29) // 16 * 16)
+
+
+# the last grid and the first box that is hashed, in the one-block build (1,200 rows: the table's room for words;
+# 3,072 rows: all the words that LDS holds) and in the larger one (192 cells a row)
+@pytest.mark.parametrize("n,cells", [(1200, 504_000), (3072, 589_824), (3073, 590_016), (6000, 1_152_000)])
+@pytest.mark.parametrize("shape", ["line", "box"])
+def test_grid_limit_of_cells(n, cells, shape):
     from paper_1904_08755_amd import gsc, regions
-    for n in (1200, 6000):
-        for z in (170, 174, 178, 300):   # 1200 rows: room for 262,144 cells; 6000: 192 cells a row
-            side = 39 if n == 1200 else 81
-            rng = np.random.default_rng(z)
-            flat = np.unique(np.concatenate([rng.choice(side * side * z, n), [0, side * side * z - 1]]))
-            host = np.stack([0 * flat, flat // (side * z), flat // z % side, flat % z], 1).astype(np.int32)
-            c = torch.from_numpy(host).to(DEV)
-            km = gsc.gsc_kernel_map(gsc.gsc_coords_build(c), c, regions.hypercube(3, 3))
-            seg, i, o = km.seg.cpu().numpy(), km.in_idx.cpu().numpy(), km.out_idx.cpu().numpy()
-            for k, pairs in enumerate(_pairs(host, host, regions.hypercube(3, 3))):
-                assert list(zip(i[seg[k]:seg[k + 1]].tolist(), o[seg[k]:seg[k + 1]].tolist())) == pairs
+    assert cells == _most_cells(n)
+    z = next(d for d in (64, 16, 4) if cells % d == 0)
+    y = next(d for d in range(96, 0, -1) if cells // z % d == 0)
+    for extra in (0, 1):
+        # a line of any number of cells; a box of `cells`, or with one more layer
+        ext = [cells + extra] if shape == "line" else [cells // z // y + extra, y, z]
+        rng = np.random.default_rng(n + extra)
+        last = int(np.prod(ext)) - 1
+        flat = np.sort(np.concatenate([[0, last], 1 + rng.choice(last - 1, n - 2, replace=False)]))
+        host = np.stack([0 * flat, *np.unravel_index(flat, ext)], 1).astype(np.int32)
+        c = torch.from_numpy(host).to(DEV)
+        table = gsc.gsc_coords_build(c)
+        assert table[:4].cpu().numpy().tobytes() == (b"GSCT" if extra else b"GSCG")
+        offs = regions.hypercube(3, len(ext))
+        km = gsc.gsc_kernel_map(table, c, offs)
+        seg = km.seg.tolist()
+        for k, (i, o) in enumerate(_sorted_pairs(c, c, offs)):
+            assert torch.equal(km.in_idx[seg[k]:seg[k + 1]].long(), i)
+            assert torch.equal(km.out_idx[seg[k]:seg[k + 1]].long(), o)
 
 
 def test_grid_cell_numbers_fit():
