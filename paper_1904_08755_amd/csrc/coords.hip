@@ -487,6 +487,7 @@ k_mark(const int32_t* __restrict__ coords, bool vec, int64_t n, int ncol, Stride
 // that the second kernel left out.
 constexpr int kIndexThreads = 1024;
 constexpr int kIndexWords = 6;
+static_assert(kIndexWords * 32 >= kGridCells, "a thread per row takes all words of more than kSmallRows rows");
 
 __global__ void __launch_bounds__(kIndexThreads) k_index(void* table, GridLayout g, int parts,
                                                          int32_t init_val) {
@@ -505,39 +506,38 @@ __global__ void __launch_bounds__(kIndexThreads) k_index(void* table, GridLayout
     const int64_t cells = ((range0 >> h->step[0]) + 1) * (int64_t)h->cstride[0];
     const int64_t nw = (cells + 31) / 32;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // kIndexWords words per thread and round, in registers: one round from about 1,400 rows on
-    for (int64_t i0 = (int64_t)blockIdx.x * kIndexThreads; i0 < nw; i0 += kIndexWords * stride) {
-        uint32_t bits[kIndexWords];
-        uint32_t sum = 0;
+    // kIndexWords words per thread, in registers
+    const int64_t i0 = (int64_t)blockIdx.x * kIndexThreads;
+    if (i0 >= nw) return;   // uniform
+    uint32_t bits[kIndexWords];
+    uint32_t sum = 0;
 #pragma unroll
-        for (int u = 0; u < kIndexWords; ++u) {
-            const int64_t i = i0 + u * stride + threadIdx.x;
-            bits[u] = i < nw ? words[i].bits : 0u;
-        }
+    for (int u = 0; u < kIndexWords; ++u) {
+        const int64_t i = i0 + u * stride + threadIdx.x;
+        bits[u] = i < nw ? words[i].bits : 0u;
+    }
 #pragma unroll
-        for (int u = 0; u < kIndexWords; ++u) sum += (uint32_t)__popc(bits[u]);
-        uint32_t inc = sum;
+    for (int u = 0; u < kIndexWords; ++u) sum += (uint32_t)__popc(bits[u]);
+    uint32_t inc = sum;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t u = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += u;
-        }
-        __syncthreads();   // the previous round's sums have been read
-        if (lane == 63) wsum[wave] = inc;
-        __syncthreads();
-        uint32_t before = 0, all = 0;
-        for (int i = 0; i < kIndexThreads / 64; ++i) {
-            if (i < wave) before += wsum[i];
-            all += wsum[i];
-        }
-        if (threadIdx.x == 0) base_sh = all ? atomicAdd(&h->total, all) : 0u;
-        __syncthreads();
-        uint32_t run = base_sh + before + inc - sum;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t u = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += u;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (int i = 0; i < kIndexThreads / 64; ++i) {
+        if (i < wave) before += wsum[i];
+        all += wsum[i];
+    }
+    if (threadIdx.x == 0) base_sh = all ? atomicAdd(&h->total, all) : 0u;
+    __syncthreads();
+    uint32_t run = base_sh + before + inc - sum;
 #pragma unroll
-        for (int u = 0; u < kIndexWords; ++u) {
-            if (bits[u]) words[i0 + u * stride + threadIdx.x].before = run;   // (an empty word's is never read)
-            run += (uint32_t)__popc(bits[u]);
-        }
+    for (int u = 0; u < kIndexWords; ++u) {
+        if (bits[u]) words[i0 + u * stride + threadIdx.x].before = run;   // (an empty word's is never read)
+        run += (uint32_t)__popc(bits[u]);
     }
 }
 
