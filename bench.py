@@ -112,7 +112,11 @@ def forward_kernel(gsc, dtype: str, ci: int, co: int, K: int, planned: bool, epi
         if ci in (128, 256) and co in (128, 256):
             return f"k_conv_bf16_dma<{ci}, {co}, gsc::WIdentity>"
         return "k_conv_bf16"
-    return f"k_conv_f32<{ci}, {co}, false, gsc::WIdentity>"
+    if K <= 64 and ci in (32, 64) and co in (32, 64):
+        return f"k_conv_f32_wide<{ci}, {co}, false, gsc::WIdentity, {ep}>"
+    if K <= 64 and 16 in (ci, co) and {ci, co} <= {16, 32, 64}:
+        return f"k_conv_f32<{ci}, {co}, false, gsc::WIdentity>"
+    return "k_conv_os<float, float, false, gsc::WIdentity>"
 
 
 def measured_traffic(kernel: str, workload: str):

@@ -81,18 +81,19 @@ int gsc_abi_version(void);
 /* Bytes of a table for n coordinates: a 256-byte header (key packing,
  * bounding box, status) followed by the memory of a power-of-two number (>=
  * 4n, >= 64) of 16-byte slots.  The build chooses one of two forms on the
- * device.  A bounding box of up to about 192 cells per row becomes an
+ * device.  A bounding box of up to about 192 cells per row (up to 3,072 rows:
+ * as many cells as the slots' memory has words for, at most 589,824) becomes an
  * occupancy grid: words {uint32 bits, uint32 before} of 32 cells each (in
  * units of the coordinates' common power-of-two step), and the row numbers of
  * the occupied cells, a cell's at place before + the word's occupied cells
  * below it.  A larger box is hashed: slots {uint64 key, int32 row, int32 hi},
- * open addressing with linear probing; the key is the row packed into <= 92 bits relative to the
- * bounding box of the coordinates (batch column most significant): up to 62
- * bits in `key` alone, a wider key with its low 62 bits in `key` and the rest
- * in `hi` (an insert claims a slot by an atomic compare-and-swap on `key`
- * and then writes `hi`; an insert meeting the same low bits waits for that
- * write, boundedly: past the bound the build reports EFULL).  The home
- * slot keeps each 2 x 2 x 2 block of neighbouring coordinates in one 128-byte
+ * open addressing with linear probing; the key is the row packed into <= 92
+ * bits relative to the bounding box of the coordinates (batch column most
+ * significant): up to 62 bits in `key` alone, a wider key with its low 62 bits
+ * in `key` and the rest in `hi` (an insert claims a slot by an atomic
+ * compare-and-swap on `key` and then writes `hi`; an insert meeting the same
+ * low bits waits for that write, boundedly: past the bound the build reports
+ * EFULL).  The home slot keeps each 2 x 2 x 2 block of neighbouring coordinates in one 128-byte
  * line of slots, so a neighbourhood query touches few lines. */
 size_t gsc_table_bytes(int64_t n);
 

@@ -371,8 +371,8 @@ k_conv_f32(const float* __restrict__ X, int64_t n_x, const float* __restrict__ W
 // output row's products are added in increasing offset order.
 //
 // 239,878 rows, 1.84 M pairs, 64 x 64 (138 us of MFMA time at the clock the
-// run holds): forward 358 -> 244 us, input gradient 463 -> 263 us, MFMA busy
-// 51 %; 192 or 256 rows a tile leave two or one workgroups per CU (295 us);
+// run holds): forward 358 -> 244 us, input gradient 463 -> 263 us, the matrix
+// cores busy for 283 million SIMD cycles (47 % at 2.4 GHz); 192 or 256 rows a tile leave two or one workgroups per CU (295 us);
 // 32 x 32: 123 -> 94 and 159 -> 104 us, and no shape from 1,571 to 300,082
 // rows was faster on the kernel above.
 constexpr int kWideRows = 2 * GSC_GROUP_ROWS;   // three workgroups per CU (33 KB of sums and 16 KB of rows each)
@@ -613,7 +613,7 @@ k_conv_f32_wide(const float* __restrict__ X, int64_t n_x, const float* __restric
 // so that the workgroups of an XCD, which take consecutive t, share the rows
 // of one range in its L2 instead of each sweeping all rows for an offset of its
 // own.  k_dw_lds_bf16<128, 128>, 3.7 million pairs over 480,288 rows: 296 us
-// without, 190 with, half of its reads then hit the L2; the kernels that are
+// without, 190 with, 51 % of its requests then hit the L2; the kernels that are
 // not bound by the gathers (k_dw_f32, k_dw_bf16, 256 channels) were no faster
 // and run without.  The place of an item is counted, not sorted: for every
 // offset k', the chunks c' with (2c' + 1) n_k < (2c + 1) n_k' (or equal, and

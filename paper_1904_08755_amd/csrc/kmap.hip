@@ -5,7 +5,7 @@
 //          table nbr[k][j], and per offset a wave64 ballot of hits gives the
 //          pair count of every 64-row group;
 //   scan:  inclusive scan of each offset's group counts (one block per
-//          offset);
+//          offset; with many groups or offsets the device-wide scan);
 //   fill:  each hit is placed at its group start plus its rank among the
 //          wave's hits (popcount of the lower-lane mask), its input row read
 //          from the neighbour table; the group starts (the group index gidx)
