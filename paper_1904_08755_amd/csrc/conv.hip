@@ -371,10 +371,11 @@ k_conv_f32(const float* __restrict__ X, int64_t n_x, const float* __restrict__ W
 // output row's products are added in increasing offset order.
 //
 // 239,878 rows, 1.84 M pairs, 64 x 64 (138 us of MFMA time at the clock the
-// run holds): forward 358 -> 244 us, input gradient 463 -> 263 us, the matrix
-// cores busy for 283 million SIMD cycles (47 % at 2.4 GHz); 192 or 256 rows a tile leave two or one workgroups per CU (295 us);
-// 32 x 32: 123 -> 94 and 159 -> 104 us, and no shape from 1,571 to 300,082
-// rows was faster on the kernel above.
+// run holds), each call repeated by itself: forward 346 -> 245 us, input
+// gradient 447 -> 269 us, the matrix cores busy for 283 million SIMD cycles (47 %
+// at 2.4 GHz); among a block's other kernels 278 and 282 us.  192 or 256 rows a
+// tile leave two or one workgroups per CU (295 us).  32 x 32: 123 -> 92 and 161
+// -> 104 us, and no shape from 60 to 300,082 rows was faster on the kernel above.
 constexpr int kWideRows = 2 * GSC_GROUP_ROWS;   // three workgroups per CU (33 KB of sums and 16 KB of rows each)
 constexpr int kWidePairs = 32;                  // pairs of a step
 
