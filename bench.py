@@ -333,7 +333,7 @@ def run_pool(args):
     nbytes = pool_bytes(n_pairs, n_out, C, K, args.pool)
     ach = nbytes / (ms["fwd"] * 1e-3) / 1e9
     roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_pool_fwd",
+            "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_pool_fwd" if C % 4 else "k_pool_fwd4",
             "bytes_per_launch": int(nbytes), "avg_launch_us": round(ms["fwd"] * 1e3, 2)}
     cpu = None if args.no_cpu_baseline else pool_cpu_baseline(args.pool)
     out = {
